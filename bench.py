@@ -129,7 +129,7 @@ def roofline_objects(shard, prof_rows, classes, n_prof_steps, fused):
     gu_bytes = 2.0 * 2 * shard.ffn * m.hidden                           # one gate/up launch streams 2 F x H bf16 weights
     ms, n = classes[3]
     if n:
-        out["gate_up"] = {"kernel": "gemm_xs_kernel<.., kGemmSwiGLU> / gemm_xb_kernel (gate/up projection, SiLU*mul epilogue)",
+        out["gate_up"] = {"kernel": "gemm_xs_kernel<.., kGemmSwiGLU> / gemm_wide_kernel (gate/up projection, SiLU*mul epilogue)",
                           "bound": "hbm", "achieved": round(gu_bytes * n / (ms * 1e-3) / 1e9, 1), "peak": 8000.0, "unit": "GB/s",
                           "frac": round(gu_bytes * n / (ms * 1e-3) / HBM_PEAK, 4), "traffic": None, "launches": int(n),
                           "avg_launch_us": round(ms * 1e3 / n, 2), "algo_bytes_per_launch": gu_bytes}
@@ -145,7 +145,7 @@ def roofline_objects(shard, prof_rows, classes, n_prof_steps, fused):
     if n0:
         rest = w_bytes - gu_bytes * classes[3][1]
         out["other_projections"] = {"kernel": ("layer_fused_kernel (O, gate/up, down, next QKV per launch)" if fused else
-                                               "gemm_xs_kernel / gemm_xb_kernel (QKV, O, down, vocabulary head)"),
+                                               "gemm_xs_kernel / gemm_wide_kernel (QKV, O, down, vocabulary head)"),
                                     "bound": "hbm", "achieved": round(rest / (ms0 * 1e-3) / 1e9, 1), "peak": 8000.0, "unit": "GB/s",
                                     "frac": round(rest / (ms0 * 1e-3) / HBM_PEAK, 4), "traffic": None, "launches": int(n0),
                                     "avg_launch_us": round(ms0 * 1e3 / n0, 2)}

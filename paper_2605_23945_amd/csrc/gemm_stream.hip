@@ -9,16 +9,9 @@
 // B = 1.  Activations are fp32 split into two bf16 terms (hi + lo), giving
 // fp32-class products on the bf16 matrix cores; accumulation is fp32.
 //
-// Two kernels share the layouts:
-//  - gemm_xs_kernel (live batch <= 32): activation-stationary; each wave keeps its
-//    K slice of the activations in registers and streams row tiles past it
-//    (wave-level split-K, partial tiles summed through LDS in wave order).
-//  - gemm_xb_kernel (live batch 33..256): the batch is a real dense dimension; a
-//    workgroup owns up to 16 weight row tiles x ALL batch tiles x a K slice and
-//    stages the activations of one k-step at a time in LDS for its eight waves.
-// The full-batch kernel can split K across workgroups; the slice partials go to a
-// scratch tensor and gemm_reduce_kernel adds them in slice order, so results never
-// depend on timing.
+// gemm_xs_kernel (live batch <= 32) is activation-stationary: each wave keeps its K slice of the activations in
+// registers and streams row tiles past it (wave-level split-K, partial tiles summed through LDS in wave order).
+// Larger live batches: gemm_wide.hip.
 #include <algorithm>
 #include <cstdlib>
 #include <mutex>
@@ -27,14 +20,6 @@
 namespace pat {
 
 namespace {
-
-// K-slice partial of (row tile rt, quad, batch row b): part[kb][b][n_tiles*16]
-__device__ __forceinline__ void store_partial(const GemmArgs &a, int kb, int rt, int quad, int b, float4 v)
-{
-    if (b >= a.B) return;
-    const int64_t ldp = (int64_t)a.n_tiles * 16;
-    *reinterpret_cast<float4 *>(a.part + ((int64_t)kb * a.B + b) * ldp + rt * 16 + quad * 4) = v;
-}
 
 // ---- live batch <= 32: activation-stationary streaming ------------------------------
 // A workgroup owns a group of row tiles over the whole of K.  Each of its waves (8 or 16) owns a
@@ -203,218 +188,6 @@ __global__ __launch_bounds__(kXsWaves * 64) void gemm_xs_kernel(GemmArgs a)
     }
 }
 
-// ---- live batch 33..256: full-batch tiles ---------------------------------------------
-// The weights are streamed ONCE for the whole live batch.  A workgroup of NW waves owns a
-// contiguous range of row tiles x ALL batch tiles x a K slice and walks its rows in chunks of
-// WR * RA tiles.  The waves form a WR x WC grid: a wave keeps RA row tiles x RBT batch tiles of
-// accumulators, takes its weight fragments straight from HBM and the batch tiles' split-bf16
-// fragments from LDS, where a k-step of ALL batch tiles is a stage (one workgroup barrier per stage on
-// the 4- and 8-tile shapes, per two stages on the 12- and 16-tile shapes).
-// Rates per stage that shaped it (CDNA: 128 B/clk of LDS and 64 B/clk of vector memory per compute
-// unit, 16 clk per 16x16x32 matrix instruction and SIMD): a fragment read from LDS must feed at
-// least 4 matrix instructions (RA = 4, both halves), and a wave must request all of a stage's
-// fragments before its first matrix instruction, or the LDS latency is paid once per pair.
-// A stage is requested from memory D - 1 stages before it is used and waits in registers (a ring
-// of D register sets, written out so that every slot is a fixed set of registers).
-// Every workgroup re-reads the activations of its K slice once per chunk, out of L2 or the
-// memory-side cache; with 256 workgroups that traffic, not HBM and not the matrix cores, is what
-// bounds the kernel (about 9 TB/s delivered in all), hence chunks of 16 row tiles.
-template <int NW, int WC, int RBT, int RA, int D, int MODE>
-__global__ __launch_bounds__(NW * 64) void gemm_xb_kernel(GemmArgs a)
-{
-    constexpr int WR = NW / WC, NBT = WC * RBT, CH = WR * RA;
-    constexpr int NV = 2 * NBT * 64;                 // vectors per stage: [2 (hi, lo)][NBT][64]
-    constexpr int VPT = NV / (NW * 64);
-    static_assert(NV % (NW * 64) == 0 && VPT <= 4, "a stage is one to four vectors per thread");
-    static_assert(D == 2 || D == 4, "ring of two or four stages");
-    extern __shared__ uint4 xs[];                    // stage buffers: two (D == 4), four (D == 2)
-    // the wave index as a scalar: what derives from it (row tiles, fragment bases) stays in scalar registers
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wr = wave / WC, wc = wave - wr * WC;
-    const int KS = a.KS, kb = blockIdx.y;
-    const int ks0 = (int)((int64_t)kb * KS / a.Kb), ks1 = (int)((int64_t)(kb + 1) * KS / a.Kb);
-    const int rt0 = (int)((int64_t)blockIdx.x * a.n_tiles / a.Rg), rt1 = (int)((int64_t)(blockIdx.x + 1) * a.n_tiles / a.Rg);
-    const u32x4_t zero_v = {0u, 0u, 0u, 0u};
-    const int n_stage = ks1 - ks0;
-
-    // This thread's vector i of a stage is the same (half, batch tile, lane) for every k-step: a
-    // wave-uniform base (unit i * NW + wave of the stage) plus a 32-bit lane offset.  Batch rows past
-    // the live batch re-read the last live row (their columns are never stored).
-    auto xsrc = [&](int i) -> const uint4 * {
-        const int unit = i * NW + wave, bt = unit % NBT, half = unit / NBT;
-        const int bsel = min(bt * 16 + (lane & 15), a.B - 1);
-        const uint32_t off = (uint32_t)(bsel >> 4) * (uint32_t)(KS * 64) + (uint32_t)((lane >> 4) * 16 + (bsel & 15));
-        return (half ? a.xlo : a.xhi) + off;
-    };
-
-    for (int c0 = rt0; c0 < rt1; c0 += CH) {
-        const int t0 = c0 + wr * RA;
-        const int n_live = min(max(rt1 - t0, 0), RA);          // row tiles of this wave inside the range
-        const uint4 *wsrc[RA];
-#pragma unroll
-        for (int ra = 0; ra < RA; ++ra) wsrc[ra] = a.w + (int64_t)min(t0 + ra, rt1 - 1) * KS * 64;
-        floatx4_t acc[RA][RBT];
-#pragma unroll
-        for (int ra = 0; ra < RA; ++ra)
-#pragma unroll
-            for (int rb = 0; rb < RBT; ++rb) acc[ra][rb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-
-        // All loads are unconditional, from clamped (always valid) addresses: k-steps past the slice
-        // re-read its last one and are nulled through the weights, as are row tiles past the range.
-        struct XStage { u32x4_t v0, v1, v2, v3; };
-        XStage xr0, xr1, xr2, xr3;
-        u32x4_t wq0[RA], wq1[RA], wq2[RA], wq3[RA];
-#define PAT_XB_FETCH(stage_, xr_, wq_)                                                           \
-    {                                                                                            \
-        const int ks_ = ks0 + (stage_);                                                          \
-        const int ksc_ = min(ks_, ks1 - 1) * 64;                                                 \
-        xr_.v0 = ld16(xsrc(0) + ksc_);                                                           \
-        if (VPT > 1) xr_.v1 = ld16(xsrc(1) + ksc_);                                              \
-        if (VPT > 2) xr_.v2 = ld16(xsrc(2) + ksc_);                                              \
-        if (VPT > 3) xr_.v3 = ld16(xsrc(3) + ksc_);                                              \
-        _Pragma("unroll") for (int ra = 0; ra < RA; ++ra) {                                      \
-            const u32x4_t v_ = ld16(wsrc[ra] + ksc_ + lane);                                          \
-            wq_[ra] = (ks_ < ks1 && ra < n_live) ? v_ : zero_v;                                  \
-        }                                                                                        \
-    }
-#define PAT_XB_TO_LDS(dst_, xr_)                                                                 \
-    {                                                                                            \
-        st16(dst_ + tid, xr_.v0);                                                                \
-        if (VPT > 1) st16(dst_ + 1 * (NW * 64) + tid, xr_.v1);                                   \
-        if (VPT > 2) st16(dst_ + 2 * (NW * 64) + tid, xr_.v2);                                   \
-        if (VPT > 3) st16(dst_ + 3 * (NW * 64) + tid, xr_.v3);                                   \
-    }
-// multiply the stage in LDS buffer number b_: its fragments are read in groups of G (high halves first,
-// then low halves), the next group requested before the current one is multiplied
-#define PAT_XB_MUL(b_, wcur_)                                                                    \
-    if (n_live > 0) {                                                                            \
-        constexpr int G = (RA * RBT >= 32 || RBT % 4) ? 2 : 4, NG = 2 * RBT / G;           \
-        const uint4 *buf = xs + (b_) * NV + (wc * RBT) * 64 + lane;                              \
-        u32x4_t f[2][G];                                                                         \
-        _Pragma("unroll") for (int j = 0; j < G; ++j) f[0][j] = ld16(buf + j * 64);              \
-        _Pragma("unroll") for (int g = 0; g < NG; ++g) {                                         \
-            if (g + 1 < NG) {                                                                    \
-                const int half = (g + 1) / (RBT / G), rb0 = ((g + 1) % (RBT / G)) * G;           \
-                _Pragma("unroll") for (int j = 0; j < G; ++j)                                    \
-                    f[(g + 1) & 1][j] = ld16(buf + (half * NBT + rb0 + j) * 64);                 \
-            }                                                                                    \
-            __builtin_amdgcn_sched_barrier(0);                                                   \
-            const int rbc = (g % (RBT / G)) * G;                                                 \
-            _Pragma("unroll") for (int j = 0; j < G; ++j)                                        \
-                _Pragma("unroll") for (int ra = 0; ra < RA; ++ra)                                \
-                    acc[ra][rbc + j] = mfma16(wcur_[ra], f[g & 1][j], acc[ra][rbc + j]);         \
-        }                                                                                        \
-    }
-// stage t: request stage t + D - 1 into the ring slot freed last, multiply stage t out of LDS buffer
-// t & 1, then move stage t + 1 into the other buffer
-#define PAT_XB_STAGE(u_, ahead_, xfetch_, wfetch_, wcur_, xnext_)                                \
-    {                                                                                            \
-        PAT_XB_FETCH(tb + (u_) + (ahead_), xfetch_, wfetch_)                                     \
-        PAT_XB_MUL((u_) & 1, wcur_)                                                              \
-        uint4 *nxt = xs + (((u_) + 1) & 1) * NV;                                                 \
-        PAT_XB_TO_LDS(nxt, xnext_)                                                               \
-        __syncthreads();                                                                         \
-    }
-        // rounds of D stages; stages past the slice, when D does not divide its length, multiply
-        // nulled weights
-        PAT_XB_FETCH(0, xr0, wq0)
-        if (D == 4) {
-            PAT_XB_FETCH(1, xr1, wq1)
-            PAT_XB_FETCH(2, xr2, wq2)
-            PAT_XB_TO_LDS(xs, xr0)
-            __syncthreads();
-            for (int tb = 0; tb < n_stage; tb += 4) {
-                PAT_XB_STAGE(0, 3, xr3, wq3, wq0, xr1)
-                PAT_XB_STAGE(1, 3, xr0, wq0, wq1, xr2)
-                PAT_XB_STAGE(2, 3, xr1, wq1, wq2, xr3)
-                PAT_XB_STAGE(3, 3, xr2, wq2, wq3, xr0)
-            }
-        } else {
-            // The 12- and 16-tile shapes (a stage is long enough to cover a load): two stages per barrier.  Four
-            // LDS buffers; the batch fragments of stage t + 2 are requested at the start of stage t and written at
-            // its end (a buffer is rewritten two stages after it was read, with a barrier in between); the weight
-            // fragments wait one stage ahead in two register sets.  Half the workgroup barriers, and half the
-            // times the matrix pipes drain and wait for the first LDS read of a stage: 5-8 % on these shapes.
-#define PAT_XB_FETCH_X(stage_, xr_)                                                              \
-    {                                                                                            \
-        const int ksc_ = min(ks0 + (stage_), ks1 - 1) * 64;                                      \
-        xr_.v0 = ld16(xsrc(0) + ksc_);                                                           \
-        if (VPT > 1) xr_.v1 = ld16(xsrc(1) + ksc_);                                              \
-        if (VPT > 2) xr_.v2 = ld16(xsrc(2) + ksc_);                                              \
-        if (VPT > 3) xr_.v3 = ld16(xsrc(3) + ksc_);                                              \
-    }
-#define PAT_XB_FETCH_W(stage_, wq_)                                                              \
-    {                                                                                            \
-        const int ks_ = ks0 + (stage_);                                                          \
-        const int ksc_ = min(ks_, ks1 - 1) * 64;                                                 \
-        _Pragma("unroll") for (int ra = 0; ra < RA; ++ra) {                                      \
-            const u32x4_t v_ = ld16(wsrc[ra] + ksc_ + lane);                                     \
-            wq_[ra] = (ks_ < ks1 && ra < n_live) ? v_ : zero_v;                                  \
-        }                                                                                        \
-    }
-            PAT_XB_FETCH_X(0, xr0)
-            PAT_XB_FETCH_X(1, xr1)
-            PAT_XB_FETCH_W(0, wq0)
-            PAT_XB_TO_LDS(xs, xr0)
-            PAT_XB_TO_LDS(xs + NV, xr1)
-            __syncthreads();
-            for (int tb = 0; tb < n_stage; tb += 2) {
-                const int p = tb & 2;                                      // buffers of this pair of stages: p, p + 1
-                PAT_XB_FETCH_X(tb + 2, xr0)
-                PAT_XB_FETCH_W(tb + 1, wq1)
-                PAT_XB_MUL(p, wq0)
-                PAT_XB_TO_LDS(xs + (p ^ 2) * NV, xr0)
-                PAT_XB_FETCH_X(tb + 3, xr1)
-                PAT_XB_FETCH_W(tb + 2, wq0)
-                PAT_XB_MUL(p + 1, wq1)
-                PAT_XB_TO_LDS(xs + ((p ^ 2) + 1) * NV, xr1)
-                __syncthreads();
-            }
-#undef PAT_XB_FETCH_X
-#undef PAT_XB_FETCH_W
-        }
-#undef PAT_XB_MUL
-#undef PAT_XB_STAGE
-#undef PAT_XB_TO_LDS
-#undef PAT_XB_FETCH
-
-        // the epilogue's addresses are derived from a copy of the lane index that the compiler cannot see through:
-        // hoisted above the stages they would be spilled there and reloaded here, one dependent round trip each
-        int lane_e = lane;
-        asm volatile("" : "+v"(lane_e));
-#pragma unroll
-        for (int ra = 0; ra < RA; ++ra) {
-            if (ra >= n_live) continue;
-#pragma unroll
-            for (int rb = 0; rb < RBT; ++rb) {
-                const float4 v = make_float4(acc[ra][rb][0], acc[ra][rb][1], acc[ra][rb][2], acc[ra][rb][3]);
-                const int b = (wc * RBT + rb) * 16 + (lane_e & 15);
-                if (a.Kb == 1) gemm_epilogue<MODE>(a, t0 + ra, lane_e >> 4, b, v);
-                else store_partial(a, kb, t0 + ra, lane_e >> 4, b, v);
-                __builtin_amdgcn_sched_barrier(0);      // one tile's epilogue at a time: its reads gathered for all tiles would spill
-            }
-        }
-    }
-}
-
-// Sum of the K-slice partials in slice order, then the epilogue.  One thread per
-// (batch row, 4 consecutive output features).
-template <int MODE>
-__global__ void gemm_reduce_kernel(GemmArgs a)
-{
-    const int quads = a.n_tiles * 4;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)a.B * quads) return;
-    const int b = (int)(i / quads), q = (int)(i % quads);
-    const int64_t ldp = (int64_t)a.n_tiles * 16;
-    float4 v = *reinterpret_cast<const float4 *>(a.part + (int64_t)b * ldp + q * 4);
-    for (int kb = 1; kb < a.Kb; ++kb) {
-        const float4 t = *reinterpret_cast<const float4 *>(a.part + ((int64_t)kb * a.B + b) * ldp + q * 4);
-        v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
-    }
-    gemm_epilogue<MODE>(a, q >> 2, q & 3, b, v);
-}
-
 // one thread per 16-byte vector of the packed matrix
 __global__ void pack_weight_kernel(const uint16_t *w, const uint16_t *w2, int n, int k, int64_t ld, int KS, int64_t n_vec,
                                    uint4 *packed, int rope_rows, int d)
@@ -546,32 +319,6 @@ hipError_t launch_xs(const GemmArgs &a, int mode, hipStream_t s)
     return hipGetLastError();
 }
 
-// the four stage buffers of the 12- and 16-tile shapes exceed the default limit of dynamic LDS
-template <int NW, int WC, int RBT, int RA, int D>
-hipError_t xb_set_lds_limit()
-{
-    constexpr int lds = (D == 2 ? 4 : 2) * 2 * WC * RBT * 64 * (int)sizeof(uint4);
-    hipError_t e = hipFuncSetAttribute((const void *)gemm_xb_kernel<NW, WC, RBT, RA, D, kGemmStore>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)gemm_xb_kernel<NW, WC, RBT, RA, D, kGemmAccum>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)gemm_xb_kernel<NW, WC, RBT, RA, D, kGemmSwiGLU>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)gemm_xb_kernel<NW, WC, RBT, RA, D, kGemmQKV>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    return e;
-}
-
-template <int NW, int WC, int RBT, int RA, int D>
-hipError_t launch_xb(const GemmArgs &a, int mode, hipStream_t s)
-{
-    const dim3 grid(a.Rg, a.Kb);
-    constexpr size_t lds = (size_t)(D == 2 ? 4 : 2) * 2 * WC * RBT * 64 * sizeof(uint4);
-    switch (mode) {
-    case kGemmStore: gemm_xb_kernel<NW, WC, RBT, RA, D, kGemmStore><<<grid, NW * 64, lds, s>>>(a); break;
-    case kGemmAccum: gemm_xb_kernel<NW, WC, RBT, RA, D, kGemmAccum><<<grid, NW * 64, lds, s>>>(a); break;
-    case kGemmQKV: gemm_xb_kernel<NW, WC, RBT, RA, D, kGemmQKV><<<grid, NW * 64, lds, s>>>(a); break;
-    default: gemm_xb_kernel<NW, WC, RBT, RA, D, kGemmSwiGLU><<<grid, NW * 64, lds, s>>>(a); break;
-    }
-    return hipGetLastError();
-}
-
 }  // namespace
 
 // Once per device and process (the attribute belongs to the device's copy of the kernel); a bit per device id.
@@ -586,40 +333,13 @@ hipError_t gemm_prepare_device()
     if (dev >= 0 && dev < 64 && (done >> dev & 1)) return hipSuccess;
     e = xs_set_lds_limit<1, 8, 8, 16>();
     if (e == hipSuccess) e = xs_set_lds_limit<2, 8, 8, 8>();
-    if (e == hipSuccess) e = xb_set_lds_limit<8, 2, 6, 4, 2>();
-    if (e == hipSuccess) e = xb_set_lds_limit<8, 2, 8, 4, 2>();
+    if (e == hipSuccess) e = gemm_wide_prepare_device();
     if (e == hipSuccess && dev >= 0 && dev < 64) done |= 1ull << dev;
     return e;
 }
 
 static int g_target_wgs = 256;   // one resident workgroup per compute unit
 void gemm_set_compute_units(int n) { if (n > 0) g_target_wgs = n; }
-
-// Shape of the full-batch kernel for a live batch: batch tiles held, wave grid, k-steps per stage.
-struct XbShape { int NBT, NW, WC, RBT, RA; };
-static XbShape xb_shape(int B)
-{
-    if (B <= 64) return {4, 8, 1, 4, 2};
-    if (B <= 128) return {8, 8, 2, 4, 4};
-    if (B <= 192) return {12, 8, 2, 6, 4};
-    return {16, 8, 2, 8, 4};
-}
-
-// Row ranges and K slices of the full-batch kernel.  Measured on MI355X (7B shapes, live batch 64 to
-// 256): the time of a launch follows the k-steps a workgroup walks, so the chip is covered with about
-// one workgroup per compute unit, each holding ONE chunk of at most 16 row tiles (every further
-// chunk re-reads the activations), and K is split only as far as that needs (each slice costs a
-// round trip of partial sums).
-static void plan_xb(int n_tiles, int KS, int B, GemmPlan &p)
-{
-    const XbShape sh = xb_shape(B);
-    const int CH = (sh.NW / sh.WC) * sh.RA;
-    const int chunks = (n_tiles + CH - 1) / CH;
-    int kb = std::max(1, std::min(8, g_target_wgs / chunks));
-    while (kb > 1 && KS / kb < 8) --kb;                         // at least 8 k-steps per slice
-    const int rg = std::max(1, std::min(n_tiles, g_target_wgs / kb));   // more than 16 tiles each: several chunks
-    p.Kb = kb; p.Rg = rg; p.NB = sh.NBT; p.MT = sh.NW;
-}
 
 GemmPlan gemm_plan(int n_tiles, int KS, int B)
 {
@@ -629,11 +349,13 @@ GemmPlan gemm_plan(int n_tiles, int KS, int B)
         p.Rg = n_tiles < g_target_wgs ? n_tiles : g_target_wgs;
         p.NB = B <= 16 ? 1 : 2; p.MT = B <= 16 ? 16 : 8;
     } else {
-        p.algo = kAlgoXb;
-        plan_xb(n_tiles, KS, B, p);
+        p.algo = kAlgoWide;
+        plan_wide(n_tiles, KS, B, g_target_wgs, p);
     }
     return p;
 }
+
+int64_t gemm_scratch_bytes(int n_tiles, int KS, int B) { return B <= 32 ? 0 : gemm_wide_scratch_bytes(n_tiles, KS, B, g_target_wgs); }
 
 hipError_t launch_gemm(const GemmArgs &a0, int mode, hipStream_t s)
 {
@@ -642,26 +364,13 @@ hipError_t launch_gemm(const GemmArgs &a0, int mode, hipStream_t s)
     GemmArgs a = a0;
     const GemmPlan p = gemm_plan(a.n_tiles, a.KS, a.B);
     a.Kb = p.Kb; a.Rg = p.Rg;
-    if ((a.ngains != nullptr || a.sstats != nullptr) && a.B > 32) return hipErrorInvalidValue;      // folded RMSNorm: small-batch kernels only
-    if (a.ngains != nullptr && (a.n_valid % 32 != 0 || !a.npk_hi || !a.npk_lo || !a.nstats)) return hipErrorInvalidValue;
-    if (a.Kb > 1 && (a.part == nullptr || (int64_t)a.Kb * a.B * a.n_tiles * 64 > a.part_bytes)) return hipErrorInvalidValue;
-    // measured on MI355X: 16 waves x 8 resident k-steps is best for one batch tile, 8 x 8 for two
+    if (a.sstats != nullptr && a.B > 32) return hipErrorInvalidValue;      // the consumer side of a folded RMSNorm: small-batch kernels only
+    if (a.ngains != nullptr && (a.n_valid % 32 != 0 || !a.npk_hi || !a.npk_lo || (a.B <= 32 && !a.nstats))) return hipErrorInvalidValue;
     { const hipError_t e = gemm_prepare_device(); if (e != hipSuccess) return e; }
+    // measured on MI355X: 16 waves x 8 resident k-steps is best for one batch tile, 8 x 8 for two
     if (a.B <= 16) return launch_xs<1, 8, 8, 16>(a, mode, s);
     if (a.B <= 32) return launch_xs<2, 8, 8, 8>(a, mode, s);
-    const hipError_t e = p.NB == 4 ? launch_xb<8, 1, 4, 2, 4>(a, mode, s)
-                       : p.NB == 8 ? launch_xb<8, 2, 4, 4, 4>(a, mode, s)
-                       : p.NB == 12 ? launch_xb<8, 2, 6, 4, 2>(a, mode, s) : launch_xb<8, 2, 8, 4, 2>(a, mode, s);
-    if (e != hipSuccess || a.Kb == 1) return e;
-    const int64_t n = (int64_t)a.B * a.n_tiles * 4;
-    const unsigned blocks = (unsigned)((n + 255) / 256);
-    switch (mode) {
-    case kGemmStore: gemm_reduce_kernel<kGemmStore><<<blocks, 256, 0, s>>>(a); break;
-    case kGemmAccum: gemm_reduce_kernel<kGemmAccum><<<blocks, 256, 0, s>>>(a); break;
-    case kGemmQKV: gemm_reduce_kernel<kGemmQKV><<<blocks, 256, 0, s>>>(a); break;
-    default: gemm_reduce_kernel<kGemmSwiGLU><<<blocks, 256, 0, s>>>(a); break;
-    }
-    return hipGetLastError();
+    return launch_gemm_wide(a, p, mode, s);
 }
 
 hipError_t launch_pack_weight(const uint16_t *w, const uint16_t *w2, int n, int k, int64_t ld, uint4 *packed, hipStream_t s)

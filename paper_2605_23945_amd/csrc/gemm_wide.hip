@@ -1,0 +1,360 @@
+// Projections of a live batch of 33..256 rows, where the batch is a real dense dimension: the weights are streamed
+// ONCE for the whole batch, by a kernel that keeps both operand streams several k-steps ahead of the matrix cores.
+//
+// A workgroup of four waves (one per SIMD) owns RA row tiles x ALL batch tiles (4 RB) x a K slice; wave w holds the
+// accumulators of all RA row tiles against its own RB batch tiles.  So a batch fragment is needed by one wave only and
+// goes straight from memory to its registers (a ring of XD + 1 k-steps), while the weight fragments, needed by all four
+// waves, go straight from memory to LDS (`global_load_lds`, 1 KiB per instruction, a ring of WS k-steps) without
+// touching a register.  One workgroup barrier per k-step; every row tile's step is one LDS read, up to one request and
+// 2 RB matrix instructions (high and low halves), so requests, LDS reads and products interleave evenly.
+//
+// What bounds it: up to 128 rows the weight stream from HBM (the per-k-step requests of all workgroups in flight,
+// up to 130 KB per compute unit, are what hides its latency); at 256 rows the chip's power limit (random operands run
+// 25-40 % slower than all-zero ones at the same instruction stream).  Measured against the kernel it replaces (batch
+// fragments staged through registers into LDS, two k-steps ahead; same box, reduction included), microseconds:
+//     rows          60            101           180           256
+//     22016 x 4096  49.4 -> 42.0  69.9 -> 51.4  82.3 -> 69.0  107  -> 86
+//     5120 x 6912   26.3 -> 23.0  37.5 -> 30.4  44.1 -> 36.4  56.5 -> 42.0
+//     1280 x 8192   22.0 -> 14.0  30.8 -> 17.5  34.1 -> 23.1  38.3 -> 27.3
+//     4096 x 1024   13.7 -> 10.0  17.2 -> 12.5  20.4 -> 16.5  22.5 -> 21.1
+//
+// K can be split across workgroups (`plan_wide`); the slices' partial sums go to a scratch tensor and a reduction
+// kernel adds them in slice order and runs the epilogue, so results never depend on timing.
+#include <algorithm>
+#include "gemm_dev.h"
+
+namespace pat {
+
+namespace {
+
+typedef __attribute__((address_space(3))) void *lds_ptr_t;
+
+// 64 lanes x 16 bytes from base + lane_off to the LDS bytes lds_off .. + 1023 (lane order), as a streaming read.
+// Inline assembly because the compiler, told of this load, waits for ALL outstanding loads before the next use of any
+// register loaded from memory; unknown to it, the load only makes its counted waits a little stricter.  The data is
+// waited for by hand (sync in the kernel below).
+__device__ __forceinline__ void load_to_lds(const u32x4_t *base, uint32_t lane_off, uint32_t lds_off)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_off), "v"(lane_off), "s"(base) : "memory");
+}
+
+// Depth of the two rings per tile shape: batch fragments XD k-steps ahead in registers (RA RB 4 accumulator registers
+// beside them), weights WS - 1 k-steps ahead in LDS.  Loads complete in order, so a wait for a batch fragment also waits
+// for the weights requested before it: XD bounds how much of the weight stream is in flight.
+template <int RA, int RB> struct WideRings;
+template <> struct WideRings<4, 1> { static constexpr int XD = 7, WS = 14; };
+template <> struct WideRings<8, 1> { static constexpr int XD = 7, WS = 12; };
+template <> struct WideRings<12, 1> { static constexpr int XD = 7, WS = 11; };
+template <> struct WideRings<4, 2> { static constexpr int XD = 7, WS = 12; };
+template <> struct WideRings<8, 2> { static constexpr int XD = 7, WS = 11; };
+template <> struct WideRings<12, 2> { static constexpr int XD = 5, WS = 9; };
+template <> struct WideRings<4, 3> { static constexpr int XD = 5, WS = 10; };
+template <> struct WideRings<8, 3> { static constexpr int XD = 5, WS = 8; };
+template <> struct WideRings<12, 3> { static constexpr int XD = 5, WS = 8; };
+template <> struct WideRings<4, 4> { static constexpr int XD = 5, WS = 9; };
+template <> struct WideRings<8, 4> { static constexpr int XD = 5, WS = 8; };
+template <> struct WideRings<12, 4> { static constexpr int XD = 4, WS = 7; };
+
+template <int RA, int RB> constexpr int wide_lds_bytes() { return WideRings<RA, RB>::WS * RA * 1024; }
+
+// MODE kPartial: the tile's sums go to a.part[kb][b][n_tiles * 16] (kb = K slice); otherwise (one slice) the epilogue runs here.
+constexpr int kPartial = -1;
+template <int RA, int RB, int MODE>
+__global__ __launch_bounds__(256) void gemm_wide_kernel(GemmArgs a)
+{
+    constexpr int XD = WideRings<RA, RB>::XD, WS = WideRings<RA, RB>::WS;
+    constexpr int CW = RA / 4, CX = 2 * RB, PER = CW + CX;      // requests per wave and k-step: weights, batch fragments
+    constexpr int U = XD + 1, DA = WS - 1, PF = 4;              // DA: k-steps the weights are requested ahead; PF: LDS reads in flight
+    static_assert(RA % 4 == 0 && DA >= XD + 1 && (DA - 2) * PER <= 63, "the hand-counted waits fit the counter");
+    extern __shared__ u32x4_t wring[];                          // [WS][RA][64]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int KS = a.KS;
+    // Workgroups are dealt round robin to the eight XCDs (blockIdx % 8); giving each XCD consecutive work items, slice
+    // major, lets its workgroups share one K slice of the activations in their L2.
+    const int id = blockIdx.x, total = a.Kb * a.Rg;
+    const int item = (id & 7) * (total >> 3) + min(id & 7, total & 7) + (id >> 3);
+    const int kb = item / a.Rg, rg = item - kb * a.Rg;
+    const int ks0 = (int)((int64_t)kb * KS / a.Kb), n = (int)((int64_t)(kb + 1) * KS / a.Kb) - ks0;
+    const int rt0 = (int)((int64_t)rg * a.n_tiles / a.Rg), rt1 = (int)((int64_t)(rg + 1) * a.n_tiles / a.Rg);
+    const int bt_last = (a.B - 1) >> 4;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)wring;
+
+    // All requests are unconditional, from clamped (always valid) addresses, so that every wave issues the same number
+    // per k-step: row tiles past the range repeat its last one and batch tiles past the live batch the last live one
+    // (neither is stored), k-steps past the slice repeat its last one (never multiplied).
+    const u32x4_t *wsrc[CW], *xsrc[CX];
+#pragma unroll
+    for (int i = 0; i < CW; ++i) wsrc[i] = reinterpret_cast<const u32x4_t *>(a.w) + ((int64_t)min(rt0 + wave * CW + i, rt1 - 1) * KS + ks0) * 64;
+#pragma unroll
+    for (int i = 0; i < CX; ++i)
+        xsrc[i] = reinterpret_cast<const u32x4_t *>(i / RB ? a.xlo : a.xhi) + ((int64_t)min(wave * RB + i % RB, bt_last) * KS + ks0) * 64;
+    int s_req = 0, s_cur = 0;                                   // ring slots: of the next request, of the current k-step
+    auto request_w = [&](int t, int i) { load_to_lds(wsrc[i] + min(t, n - 1) * 64, lane * 16, lds0 + (s_req * RA + wave * CW + i) * 1024); };
+    auto request_x = [&](int t, int i) -> u32x4_t { return *(xsrc[i] + min(t, n - 1) * 64 + lane); };
+
+    floatx4_t acc[RA][RB];
+#pragma unroll
+    for (int ra = 0; ra < RA; ++ra)
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) acc[ra][rb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+    u32x4_t x[U][CX], w[PF];
+    // the requests of the k-steps -DA .. -1, in the order the loop would have issued them
+#pragma unroll
+    for (int s = -DA; s < 0; ++s) {
+#pragma unroll
+        for (int i = 0; i < CW; ++i) request_w(s + DA, i);
+        ++s_req;
+        if (s + XD >= 0) {
+#pragma unroll
+            for (int i = 0; i < CX; ++i) x[s + XD][i] = request_x(s + XD, i);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // W(0), W(1): at least (DA - 2) CW younger requests are outstanding or done
+    asm volatile("s_waitcnt vmcnt(%c0)\n\ts_barrier" ::"i"((DA - 2) * CW) : "memory");
+#pragma unroll
+    for (int p = 0; p < PF - 1; ++p) w[p] = wring[p * 64 + lane];
+
+    // One k-step.  The wait covers this wave's part of W(t + 1) (its requests are followed by those of DA - 2 whole
+    // k-steps); after the barrier all parts are in LDS and every wave is done with the slot of W(t - 1), which takes W(t + DA).
+    auto step = [&](int t, const u32x4_t (&xc)[CX], u32x4_t (&xn)[CX]) {
+        asm volatile("s_waitcnt vmcnt(%c0)\n\ts_barrier" ::"i"((DA - 2) * PER) : "memory");
+        const int s_nxt = s_cur + 1 == WS ? 0 : s_cur + 1;
+        const u32x4_t *cur = wring + s_cur * RA * 64 + lane, *nxt = wring + s_nxt * RA * 64 + lane;
+#pragma unroll
+        for (int r = 0; r < RA; ++r) {
+#pragma unroll
+            for (int v = (r * PER) / RA; v < ((r + 1) * PER) / RA; ++v) { if (v < CW) request_w(t + DA, v); else xn[v - CW] = request_x(t + XD, v - CW); }
+            w[(r + PF - 1) % PF] = r + PF - 1 < RA ? cur[(r + PF - 1) * 64] : nxt[(r + PF - 1 - RA) * 64];
+#pragma unroll
+            for (int i = 0; i < CX; ++i) acc[r][i % RB] = mfma16(w[r % PF], xc[i], acc[r][i % RB]);
+            __builtin_amdgcn_sched_barrier(0);                  // keeps the interleaving, and every LDS read of a k-step before the next barrier
+        }
+        s_cur = s_nxt; s_req = s_req + 1 == WS ? 0 : s_req + 1;
+    };
+    int t = 0;
+    for (; t + U <= n; t += U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) step(t + u, x[u], x[(u + XD) % U]);
+    }
+#pragma unroll
+    for (int u = 0; u < U - 1; ++u)
+        if (t + u < n) step(t + u, x[u], x[(u + XD) % U]);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // no write to LDS may be in flight when the workgroup ends
+
+    // the epilogue's addresses are derived from a copy of the lane index that the compiler cannot see through:
+    // hoisted above the loop they would occupy registers it needs
+    int lane_e = lane;
+    asm volatile("" : "+v"(lane_e));
+#pragma unroll
+    for (int ra = 0; ra < RA; ++ra) {
+        const int rt = rt0 + ra;
+        if (rt >= rt1) continue;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const float4 v = make_float4(acc[ra][rb][0], acc[ra][rb][1], acc[ra][rb][2], acc[ra][rb][3]);
+            const int b = (wave * RB + rb) * 16 + (lane_e & 15), quad = lane_e >> 4;
+            if (MODE == kPartial) {
+                if (b < a.B) *reinterpret_cast<float4 *>(a.part + ((int64_t)kb * a.B + b) * ((int64_t)a.n_tiles * 16) + rt * 16 + quad * 4) = v;
+            } else gemm_epilogue<MODE == kPartial ? 0 : MODE>(a, rt, quad, b, v);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
+// The four consecutive features 4 q .. of batch row b, summed over the K slices in slice order.
+__device__ __forceinline__ float4 sum_slices(const GemmArgs &a, int b, int q)
+{
+    const int64_t ldp = (int64_t)a.n_tiles * 16;
+    float4 v = *reinterpret_cast<const float4 *>(a.part + (int64_t)b * ldp + q * 4);
+    for (int kb = 1; kb < a.Kb; ++kb) {
+        const float4 t = *reinterpret_cast<const float4 *>(a.part + ((int64_t)kb * a.B + b) * ldp + q * 4);
+        v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
+    }
+    return v;
+}
+
+// Slice sums, then the epilogue: one thread per (row tile, batch row, quad), quads fastest, then batch rows, so that a
+// wave reads 64-byte runs of 16 rows and its SwiGLU results (packed operand, 4 bytes per lane) form 256-byte runs.
+template <int MODE>
+__global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs a)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int per_tile = a.B * 4;
+    const int rt = (int)(i / per_tile), r = (int)(i - (int64_t)rt * per_tile);
+    if (rt >= a.n_tiles) return;
+    const int b = r >> 2, quad = r & 3;
+    gemm_epilogue<MODE>(a, rt, quad, b, sum_slices(a, b, rt * 4 + quad));
+}
+
+// Slice sums of a residual projection, y += sums, and the RMSNorm that the next projection applies to y, written as
+// its packed split-bf16 operand: one workgroup per batch row, so that the row's sum of squares is at hand without a
+// kernel (and a pass over y) of its own.  Up to 4 x 2048 features stay in registers; wider rows re-read their y.
+// A reduction and a norm launch took 7.7 + 7.2 us at 256 rows of 4096 features, 4.7 + 5.1 us at 60.
+constexpr int kNormThreads = 512;
+__global__ __launch_bounds__(kNormThreads) void gemm_reduce_norm_kernel(GemmArgs a)
+{
+    constexpr int KEEP = 4;
+    __shared__ float wsum[kNormThreads / 64];
+    const int b = blockIdx.x, quads = a.n_tiles * 4, KSo = a.n_tiles >> 1;
+    float *y = a.y + (int64_t)b * a.ldy;
+    float4 keep[KEEP];
+    float ss = 0.f;
+    auto take = [&](int q) {
+        float4 v = sum_slices(a, b, q);
+        const float4 c = *reinterpret_cast<const float4 *>(y + q * 4);
+        v.x += c.x; v.y += c.y; v.z += c.z; v.w += c.w;
+        *reinterpret_cast<float4 *>(y + q * 4) = v;
+        ss += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
+        return v;
+    };
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i) {
+        const int q = threadIdx.x + i * kNormThreads;
+        keep[i] = q < quads ? take(q) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    for (int q = threadIdx.x + KEEP * kNormThreads; q < quads; q += kNormThreads) (void)take(q);
+    ss = wave_sum(ss);
+    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = ss;
+    __syncthreads();
+    float tot = 0.f;
+#pragma unroll
+    for (int w = 0; w < kNormThreads / 64; ++w) tot += wsum[w];
+    const float inv = 1.0f / sqrtf(tot / (float)a.s_h + a.s_eps);
+    auto emit = [&](int q, float4 v) {
+        const uint2 gv = *reinterpret_cast<const uint2 *>(a.ngains + q * 4);
+        uint16_t h[4], l[4];
+        split_bf16(v.x * inv * bf16lo(gv.x), h[0], l[0]); split_bf16(v.y * inv * bf16hi(gv.x), h[1], l[1]);
+        split_bf16(v.z * inv * bf16lo(gv.y), h[2], l[2]); split_bf16(v.w * inv * bf16hi(gv.y), h[3], l[3]);
+        const int64_t off = packed_elem_offset(b, q * 4, KSo);
+        *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(a.npk_hi) + off) = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
+        *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(a.npk_lo) + off) = make_uint2((uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16));
+    };
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i) {
+        const int q = threadIdx.x + i * kNormThreads;
+        if (q < quads) emit(q, keep[i]);
+    }
+    for (int q = threadIdx.x + KEEP * kNormThreads; q < quads; q += kNormThreads) emit(q, *reinterpret_cast<const float4 *>(y + q * 4));
+}
+
+template <int RA, int RB, int MODE>
+hipError_t launch_wide_t(const GemmArgs &a, hipStream_t s)
+{
+    gemm_wide_kernel<RA, RB, MODE><<<(unsigned)(a.Rg * a.Kb), 256, wide_lds_bytes<RA, RB>(), s>>>(a);
+    return hipGetLastError();
+}
+
+// mode: kPartial, kGemmStore, or (12 row tiles only) any other epilogue in the kernel
+template <int RB>
+hipError_t launch_wide_rb(const GemmArgs &a, int RA, int mode, hipStream_t s)
+{
+    if (RA == 4) return mode == kPartial ? launch_wide_t<4, RB, kPartial>(a, s) : launch_wide_t<4, RB, kGemmStore>(a, s);
+    if (RA == 8) return mode == kPartial ? launch_wide_t<8, RB, kPartial>(a, s) : launch_wide_t<8, RB, kGemmStore>(a, s);
+    switch (mode) {
+    case kPartial: return launch_wide_t<12, RB, kPartial>(a, s);
+    case kGemmStore: return launch_wide_t<12, RB, kGemmStore>(a, s);
+    case kGemmAccum: return launch_wide_t<12, RB, kGemmAccum>(a, s);
+    case kGemmQKV: return launch_wide_t<12, RB, kGemmQKV>(a, s);
+    default: return launch_wide_t<12, RB, kGemmSwiGLU>(a, s);
+    }
+}
+
+template <int RA, int RB, int MODE>
+hipError_t wide_set_lds_limit() { return hipFuncSetAttribute((const void *)gemm_wide_kernel<RA, RB, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, wide_lds_bytes<RA, RB>()); }
+
+template <int RB>
+hipError_t wide_set_lds_limits()
+{
+    hipError_t e = wide_set_lds_limit<4, RB, kPartial>();
+    if (e == hipSuccess) e = wide_set_lds_limit<4, RB, kGemmStore>();
+    if (e == hipSuccess) e = wide_set_lds_limit<8, RB, kPartial>();
+    if (e == hipSuccess) e = wide_set_lds_limit<8, RB, kGemmStore>();
+    if (e == hipSuccess) e = wide_set_lds_limit<12, RB, kPartial>();
+    if (e == hipSuccess) e = wide_set_lds_limit<12, RB, kGemmStore>();
+    if (e == hipSuccess) e = wide_set_lds_limit<12, RB, kGemmAccum>();
+    if (e == hipSuccess) e = wide_set_lds_limit<12, RB, kGemmQKV>();
+    if (e == hipSuccess) e = wide_set_lds_limit<12, RB, kGemmSwiGLU>();
+    return e;
+}
+
+// How many K slices a projection may be cut into: about one workgroup of 16 row tiles per compute unit and at least
+// 8 k-steps per slice.  The bound on the partial sums' scratch follows from it, so it is kept apart from the choice below.
+int max_slices(int n_tiles, int KS, int n_cu)
+{
+    const int chunks = (n_tiles + 15) / 16;
+    int kb = std::max(1, std::min(8, n_cu / chunks));
+    while (kb > 1 && KS / kb < 8) --kb;
+    return kb;
+}
+
+}  // namespace
+
+hipError_t gemm_wide_prepare_device()
+{
+    hipError_t e = wide_set_lds_limits<1>();
+    if (e == hipSuccess) e = wide_set_lds_limits<2>();
+    if (e == hipSuccess) e = wide_set_lds_limits<3>();
+    if (e == hipSuccess) e = wide_set_lds_limits<4>();
+    return e;
+}
+
+// Row tiles per workgroup (4, 8, 12) and K slices, by a cost model fitted to 122 measured launches (40 shapes of
+// 1280..22016 features, K 1024..11008, 60..256 rows; rms error 8 %, and on all but three shapes the cut it picks was the
+// best or within 3 % of the best measured): a launch takes 7.5 us plus its k-steps, each the longest of the matrix
+// products (0.020 us per tile pair), the operand fetch (0.014 us per KiB and workgroup) and the weight stream (0.050 us
+// per KiB and workgroup with all 256 busy), plus 0.48 us per MB of partial sums.  Few row tiles per workgroup
+// and few slices suit narrow projections (1280 x 8192, 256 rows: 4 tiles 27.3 us, 8 tiles 33.6), many tiles wide ones
+// (22016 x 4096, 256 rows: 12 tiles 86 us, 8 tiles 98).  A projection that may not be cut at all has no scratch for
+// partial sums: it takes the 12-tile kernels, which exist with every epilogue.
+void plan_wide(int n_tiles, int KS, int B, int n_cu, GemmPlan &p)
+{
+    const int RB = (B + 63) / 64, kb_max = max_slices(n_tiles, KS, n_cu);
+    double best = 0.0;
+    for (int RA = kb_max == 1 ? 12 : 4; RA <= 12; RA += 4)
+        for (int kb = 1; kb <= kb_max; ++kb) {
+            const int rg = (n_tiles + RA - 1) / RA, wgs = rg * kb, rounds = (wgs + n_cu - 1) / n_cu;
+            const double busy = std::min(1.0, (double)wgs / n_cu);
+            const double step = std::max({0.0203 * RA * RB, 0.0058 + 0.0142 * (RA + 8 * RB), 0.0502 * RA * busy});
+            const double cost = 7.5 + rounds * ((KS + kb - 1) / kb) * step + 0.476e-6 * 4.0 * kb * B * n_tiles * 16.0 + (kb > 1 ? 1.0 : 0.0);
+            if (best == 0.0 || cost < best) { best = cost; p.Kb = kb; p.Rg = rg; p.MT = RA; }
+        }
+    p.NB = 4 * RB;
+}
+
+// Bytes of partial sums a launch may need (an upper bound over the cuts plan_wide chooses from).
+int64_t gemm_wide_scratch_bytes(int n_tiles, int KS, int B, int n_cu)
+{
+    const int kb = max_slices(n_tiles, KS, n_cu);
+    return kb > 1 ? (int64_t)kb * B * n_tiles * 64 : 0;
+}
+
+hipError_t launch_gemm_wide(const GemmArgs &a0, const GemmPlan &p, int mode, hipStream_t s)
+{
+    GemmArgs a = a0;
+    const bool direct = p.Kb == 1 && (mode == kGemmStore || p.MT == 12);
+    if (!direct && (a.part == nullptr || (int64_t)a.Kb * a.B * a.n_tiles * 64 > a.part_bytes)) return hipErrorInvalidValue;
+    const int m = direct ? mode : kPartial;
+    if (direct) a.ngains = nullptr;          // the epilogue's own hand-over is the small-batch one (x * gains and per-tile statistics)
+    const hipError_t e = p.NB == 4 ? launch_wide_rb<1>(a, p.MT, m, s) : p.NB == 8 ? launch_wide_rb<2>(a, p.MT, m, s)
+                       : p.NB == 12 ? launch_wide_rb<3>(a, p.MT, m, s) : launch_wide_rb<4>(a, p.MT, m, s);
+    if (e != hipSuccess) return e;
+    if (direct) {
+        if (mode == kGemmAccum && a0.ngains != nullptr) return launch_rmsnorm_pack(a.y, a0.ngains, a.B, a.s_h, a.s_eps, a.npk_hi, a.npk_lo, s);
+        return hipSuccess;
+    }
+    if (mode == kGemmAccum && a.ngains != nullptr) {
+        gemm_reduce_norm_kernel<<<(unsigned)a.B, kNormThreads, 0, s>>>(a);
+        return hipGetLastError();
+    }
+    const unsigned blocks = (unsigned)(((int64_t)a.B * a.n_tiles * 4 + 255) / 256);
+    switch (mode) {
+    case kGemmStore: gemm_reduce_kernel<kGemmStore><<<blocks, 256, 0, s>>>(a); break;
+    case kGemmAccum: gemm_reduce_kernel<kGemmAccum><<<blocks, 256, 0, s>>>(a); break;
+    case kGemmQKV: gemm_reduce_kernel<kGemmQKV><<<blocks, 256, 0, s>>>(a); break;
+    default: gemm_reduce_kernel<kGemmSwiGLU><<<blocks, 256, 0, s>>>(a); break;
+    }
+    return hipGetLastError();
+}
+
+}  // namespace pat

@@ -166,10 +166,7 @@ void layouts(const pat_cfg *c, const Shard &s, WorkLayout *w, WeightLayout *wt, 
                                 {s.H / 16, s.F / 32}, {s.Vs / 16, s.H / 32}};
         int64_t need = 0;
         for (auto &mt : mats)
-            for (int b = 33; b <= std::min(256, MB); ++b) {
-                const int kb = gemm_plan(mt[0], mt[1], b).Kb;
-                if (kb > 1) need = std::max(need, (int64_t)kb * b * mt[0] * 16 * 4);
-            }
+            need = std::max(need, gemm_scratch_bytes(mt[0], mt[1], std::min(256, MB)));      // grows with the batch
         w->gemm_part_bytes = std::max<int64_t>(need, 256);
         w->gemm_part = take(w->gemm_part_bytes);
 
@@ -274,11 +271,15 @@ hipError_t gemm_groups(GemmArgs g, int mode, hipStream_t st)
         h.xhi = g.xhi + t0 * g.KS * 64; h.xlo = g.xlo + t0 * g.KS * 64;
         if (g.y) h.y = g.y + (int64_t)b0 * g.ldy;
         if (g.yhi) { h.yhi = g.yhi + t0 * g.KS_out * 64; h.ylo = g.ylo + t0 * g.KS_out * 64; }
+        if (g.ngains) { h.npk_hi = g.npk_hi + t0 * (g.n_tiles / 2) * 64; h.npk_lo = g.npk_lo + t0 * (g.n_tiles / 2) * 64; }
+        const bool norm_after = g.ngains && B > 32 && h.B <= 32;         // a last small group has no finished norm: a launch of its own
+        if (norm_after) h.ngains = nullptr;
         if (g.kv_len) {
             h.kv_len = g.kv_len + b0;
             if (g.row_slot) h.row_slot = g.row_slot + b0; else h.page_table = g.page_table + (int64_t)b0 * g.max_pages;
         }
         hipError_t e = launch_gemm(h, mode, st);
+        if (e == hipSuccess && norm_after) e = launch_rmsnorm_pack(h.y, g.ngains, h.B, g.s_h, g.s_eps, h.npk_hi, h.npk_lo, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -627,9 +628,10 @@ static int run_layers(pat_ctx *c, int B, int C, int64_t n_chunks, const int32_t 
         g.sstats = after_embedding ? at<float>(W, w.stats_e) : nstats;
         g.s_parts = after_embedding ? 1 : n_parts; g.s_h = s.H; g.s_eps = c->cfg.rms_eps;
     };
-    auto produce = [&](GemmArgs &g, const void *gains) {
-        if (!fold) return;
-        g.ngains = (const uint16_t *)gains; g.npk_hi = a_hi; g.npk_lo = a_lo; g.nstats = nstats;
+    auto produce = [&](GemmArgs &g, const void *gains) {      // above 32 rows: the finished operand, from the reduction of the K slices
+        g.ngains = (const uint16_t *)gains; g.npk_hi = a_hi; g.npk_lo = a_lo;
+        if (fold) g.nstats = nstats;
+        else { g.s_h = s.H; g.s_eps = c->cfg.rms_eps; }
     };
     AttnArgs aa{};
     aa.kv = c->kv; aa.qkv = qkv; aa.ldq = s.qkv_rows; aa.hq = s.hq; aa.B = B; aa.kv_len = pos; aa.row_slot = row_slot;
@@ -639,7 +641,7 @@ static int run_layers(pat_ctx *c, int B, int C, int64_t n_chunks, const int32_t 
 
     for (int l = 0; l < s.NL; ++l) {
         char *L = Wb + c->wt.layer0 + c->wt.layer_stride * l;
-        if (!fold) { TimeScope t(c, 2); PAT_HIP(c, launch_rmsnorm_pack(x, (const uint16_t *)(L + c->wt.g1), B, s.H, c->cfg.rms_eps, a_hi, a_lo, st)); }
+        if (!fold && l == 0) { TimeScope t(c, 2); PAT_HIP(c, launch_rmsnorm_pack(x, (const uint16_t *)(L + c->wt.g1), B, s.H, c->cfg.rms_eps, a_hi, a_lo, st)); }
         {   // QKV projection; its epilogue rotates q and k and appends k, v to the cache
             GemmArgs g = gemm_args(L + c->wt.wqkv, s.qkv_rows, s.H, a_hi, a_lo, B, qkv, s.qkv_rows, gpart, w.gemm_part_bytes);
             consume(g, l == 0);
@@ -669,7 +671,6 @@ static int run_layers(pat_ctx *c, int B, int C, int64_t n_chunks, const int32_t 
             produce(g, L + c->wt.g2);
             TimeScope t(c, 0); PAT_HIP(c, gemm_groups(g, kGemmAccum, st));
         }
-        if (!fold) { TimeScope t(c, 2); PAT_HIP(c, launch_rmsnorm_pack(x, (const uint16_t *)(L + c->wt.g2), B, s.H, c->cfg.rms_eps, a_hi, a_lo, st)); }
         {
             GemmArgs g = gemm_args(L + c->wt.wgu, 2 * s.F, s.H, a_hi, a_lo, B, nullptr, 0, gpart, w.gemm_part_bytes);
             g.yhi = b_hi; g.ylo = b_lo; g.KS_out = s.F / 32;
@@ -820,7 +821,7 @@ int pat_decode_step(pat_ctx *c, pat_step_report *report_host, int32_t *next_tok_
             else PAT_HIP(c, launch_embed((const uint16_t *)(Wb + c->wt.embed), s.H, c->st.tok, B, x, st));
         }
         if (int rc = run_layers(c, B, C, n_chunks, c->st.kv_len, nullptr, 0)) return rc;
-        if (!fold) { TimeScope t(c, 2); PAT_HIP(c, launch_rmsnorm_pack(x, (const uint16_t *)(Wb + c->wt.gf), B, s.H, c->cfg.rms_eps, a_hi, a_lo, st)); }
+        if (!fold && s.NL == 0) { TimeScope t(c, 2); PAT_HIP(c, launch_rmsnorm_pack(x, (const uint16_t *)(Wb + c->wt.gf), B, s.H, c->cfg.rms_eps, a_hi, a_lo, st)); }
         {
             GemmArgs g = gemm_args(Wb + c->wt.wlm, s.Vs, s.H, a_hi, a_lo, B, logits, s.Vs, gpart, w.gemm_part_bytes);
             if (fold) {
@@ -1175,8 +1176,7 @@ int pat_op_pack_act(const float *x, int32_t b, int32_t k, void *xhi, void *xlo, 
 int64_t pat_op_gemm_scratch_bytes(int32_t n, int32_t k, int32_t b)
 {
     if (n <= 0 || k <= 0 || k % 32 || b <= 0 || b > 256) return -1;
-    const int kb = gemm_plan(cdiv(n, 16), k / 32, b).Kb;
-    return kb > 1 ? (int64_t)kb * b * cdiv(n, 16) * 16 * 4 : 0;
+    return gemm_scratch_bytes(cdiv(n, 16), k / 32, b);
 }
 
 int pat_op_gemm_plan(int32_t n, int32_t k, int32_t b, int32_t plan[4])

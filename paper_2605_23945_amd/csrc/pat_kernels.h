@@ -36,6 +36,7 @@ struct GemmArgs {
     // RMSNorm folded into the small-batch projections (live batch <= 32), both NULL-able:
     //  * producer side (kGemmAccum): besides y += ..., write y * gains as the packed split-bf16 operand of the
     //    projection that consumes RMSNorm(y), and the tile's sums of squares of y: nstats[tile][16 * batch tiles];
+    //    (live batch > 32: npk receives the finished RMSNorm(y) * gains instead, with s_h and s_eps; no nstats);
     //  * consumer side (any mode): the operand is such an x * gains; results are multiplied by 1 / rms of their
     //    batch row, from the per-part sums of squares sstats[part][16 * batch tiles] (fixed summation order).
     const uint16_t *ngains; uint4 *npk_hi, *npk_lo; float *nstats;
@@ -45,9 +46,14 @@ struct GemmArgs {
     int Kb, Rg;                // set by launch_gemm from gemm_plan
 };
 // How a [16 n_tiles, 32 KS] projection at live batch B is cut: K slices across workgroups and row groups.
-enum GemmAlgo { kAlgoXs = 0, kAlgoXb = 3 };
-struct GemmPlan { int Kb, Rg, NB, MT, algo; };
+enum GemmAlgo { kAlgoXs = 0, kAlgoWide = 3 };
+struct GemmPlan { int Kb, Rg, NB, MT, algo; };      // MT: waves per workgroup (small-batch kernel) or row tiles per workgroup (gemm_wide)
 GemmPlan gemm_plan(int n_tiles, int KS, int B);
+int64_t gemm_scratch_bytes(int n_tiles, int KS, int B);      // room for partial sums that launch_gemm may need
+void plan_wide(int n_tiles, int KS, int B, int n_cu, GemmPlan &p);
+int64_t gemm_wide_scratch_bytes(int n_tiles, int KS, int B, int n_cu);
+hipError_t gemm_wide_prepare_device();
+hipError_t launch_gemm_wide(const GemmArgs &a, const GemmPlan &p, int mode, hipStream_t s);
 void gemm_set_compute_units(int n);
 
 // [n, k] (or gate/up pair w, w2) row-major with `ld` elements between rows -> streaming layout

@@ -1,0 +1,45 @@
+"""The full-batch projection kernel (33..256 rows) at the edges of its tiles, rings and K slices, through the C ABI,
+against float64 products of the same operands."""
+import numpy as np
+import pytest
+import torch
+
+import pat_inputs as pi
+from gpu_util import DEV
+
+pytestmark = pytest.mark.gpu
+
+# rows: both sides of every batch-tile count; row tiles: one, a workgroup's 4 / 8 / 12 and one more, several ranges;
+# k-steps: fewer than the rings hold, a multiple of their unrolling and one more or less, slices of unequal length
+CASES = [(16, 32, 33), (16, 160, 64), (64, 192, 65), (80, 224, 128), (128, 256, 129), (192, 288, 192), (208, 352, 193),
+         (400, 416, 256), (64, 512, 34), (80, 544, 255), (784, 608, 63), (144, 1056, 127), (208, 2080, 191), (1200, 832, 80),
+         (3088, 544, 40), (3088, 480, 250), (33024, 96, 36), (33024, 64, 200)]
+
+
+@pytest.mark.parametrize("n,k,b", CASES)
+def test_edges_of_tiles_rings_and_slices(n, k, b):
+    import paper_2605_23945_amd as pat
+    lib = pat.load_library()
+    w = pi.normal_bf16(pi.stream_key(0x31DE, n, k), torch.arange(n * k, dtype=torch.int64, device=DEV), 0.05).view(n, k)
+    x = torch.randn(b, k, device=DEV, generator=torch.Generator(device=DEV).manual_seed(b))
+    hi, lo = pat.pat_op_pack_act(x)
+    ref = x.double().cpu().numpy() @ w.double().cpu().numpy().T
+    # operands hi + lo are good to 2^-17, sums are fp32: a few units of 2^-17 of the row scale (the same bound as the
+    # other projection tests)
+    tol = 1e-4 * float(np.sqrt(np.mean(ref * ref)))
+    wp = pat.pat_op_pack_weight(w)
+    y = torch.full((b, n), 7.0, device=DEV)
+    pat.pat_op_gemm(wp, n, k, hi, lo, b, y, mode=0)
+    assert np.max(np.abs(y.double().cpu().numpy() - ref)) <= tol
+    y2 = torch.full((b, n), 0.25, device=DEV)
+    pat.pat_op_gemm(wp, n, k, hi, lo, b, y2, mode=1)
+    assert np.max(np.abs(y2.double().cpu().numpy() - 0.25 - ref)) <= tol + 1e-6
+    if (n // 2) % 32 == 0:
+        wg = pat.pat_op_pack_weight(w[: n // 2], w[n // 2:])
+        nb = lib.pat_op_packed_act_bytes(b, n // 2)
+        yh = torch.zeros(nb, dtype=torch.uint8, device=DEV)
+        yl = torch.zeros_like(yh)
+        pat.pat_op_gemm(wg, n, k, hi, lo, b, None, mode=2, y_hi=yh, y_lo=yl)
+        g, u = ref[:, : n // 2], ref[:, n // 2:]
+        want = g / (1.0 + np.exp(-g)) * u
+        assert np.max(np.abs(pat.unpack_act(yh, yl, b, n // 2) - want)) <= 2e-4 * float(np.sqrt(np.mean(want * want))) + 2 * tol * float(np.max(np.abs(ref)))
