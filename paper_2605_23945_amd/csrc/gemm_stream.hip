@@ -232,45 +232,45 @@ __global__ void pack_act_kernel(const float *x, int b, int k, int KS, uint4 *hi,
                         l[6] | (uint32_t)l[7] << 16);
 }
 
-// RMSNorm of one row per workgroup, written as packed split-bf16 activations.
-__global__ __launch_bounds__(256) void rmsnorm_pack_kernel(const float *x, const uint16_t *g, int h, int KS,
-                                                           float eps, uint4 *hi, uint4 *lo)
+// RMSNorm of four rows per workgroup, written as packed split-bf16 activations.  In the packed operand the 16-byte
+// pieces of neighbouring rows are neighbours, so the lanes of a wave take 16 pieces of each of the four rows (rows
+// fastest): 512-byte reads of every row and 64-byte runs of the output.  One row per workgroup scattered its output in
+// 16-byte pieces and was bound by those writes (1024 rows of 8192 features: 30 us).  Up to kKeep x 1024 features of a row
+// stay in registers between the sum of squares and the scaling; wider rows are read again.
+constexpr int kPackRows = 4, kPackThreads = 512, kPackLanes = kPackThreads / kPackRows;      // lanes per row
+__global__ __launch_bounds__(kPackThreads) void rmsnorm_pack_kernel(const float *x, const uint16_t *g, int b, int h, int KS,
+                                                                    float eps, uint4 *hi, uint4 *lo)
 {
-    // The row is read once: up to kKeep x 2048 features stay in registers between the sum of squares
-    // and the scaling (the rest, for wider models, is read again), and the gains are requested with it.
-    constexpr int kKeep = 4;
-    __shared__ float part[4];
-    const int row = blockIdx.x;
-    const float *xr = x + (int64_t)row * h;
+    constexpr int kKeep = 8;
+    __shared__ float part[kPackThreads / 64][kPackRows];
+    const int r = threadIdx.x & (kPackRows - 1), c0 = threadIdx.x / kPackRows;
+    const int row = blockIdx.x * kPackRows + r;
+    const float *xr = x + (int64_t)min(row, b - 1) * h;
     float4 xp[kKeep], xq[kKeep];
-    uint4 gk[kKeep];
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i) {
+        const int k0 = min((c0 + i * kPackLanes) * 8, h - 8);                 // past the row: a clamped, unused load
+        xp[i] = *reinterpret_cast<const float4 *>(xr + k0);
+        xq[i] = *reinterpret_cast<const float4 *>(xr + k0 + 4);
+    }
     float ss = 0.f;
+    auto square = [&](float4 p, float4 q) { ss += p.x * p.x + p.y * p.y + p.z * p.z + p.w * p.w + q.x * q.x + q.y * q.y + q.z * q.z + q.w * q.w; };
 #pragma unroll
-    for (int i = 0; i < kKeep; ++i) {
-        const int k0 = threadIdx.x * 8 + i * 2048;
-        const int kc = min(k0, h - 8);                        // past the row: a clamped, unused load
-        xp[i] = *reinterpret_cast<const float4 *>(xr + kc);
-        xq[i] = *reinterpret_cast<const float4 *>(xr + kc + 4);
-        gk[i] = *reinterpret_cast<const uint4 *>(g + kc);
-    }
+    for (int i = 0; i < kKeep; ++i)
+        if ((c0 + i * kPackLanes) * 8 < h) square(xp[i], xq[i]);
+    for (int k0 = (c0 + kKeep * kPackLanes) * 8; k0 < h; k0 += kPackLanes * 8)
+        square(*reinterpret_cast<const float4 *>(xr + k0), *reinterpret_cast<const float4 *>(xr + k0 + 4));
 #pragma unroll
-    for (int i = 0; i < kKeep; ++i) {
-        if (threadIdx.x * 8 + i * 2048 < h) {
-            const float4 p = xp[i], q = xq[i];
-            ss += p.x * p.x + p.y * p.y + p.z * p.z + p.w * p.w + q.x * q.x + q.y * q.y + q.z * q.z + q.w * q.w;
-        }
-    }
-    for (int k0 = threadIdx.x * 8 + kKeep * 2048; k0 < h; k0 += 2048) {
-        const float4 p = *reinterpret_cast<const float4 *>(xr + k0);
-        const float4 q = *reinterpret_cast<const float4 *>(xr + k0 + 4);
-        ss += p.x * p.x + p.y * p.y + p.z * p.z + p.w * p.w + q.x * q.x + q.y * q.y + q.z * q.z + q.w * q.w;
-    }
-    ss = wave_sum(ss);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
+    for (int o = 32; o >= kPackRows; o >>= 1) ss += __shfl_xor(ss, o, 64);
+    if ((threadIdx.x & 63) < kPackRows) part[threadIdx.x >> 6][r] = ss;
     __syncthreads();
-    const float tot = (part[0] + part[1]) + (part[2] + part[3]);
+    float tot = 0.f;
+#pragma unroll
+    for (int w = 0; w < kPackThreads / 64; ++w) tot += part[w][r];
     const float inv = 1.0f / sqrtf(tot / (float)h + eps);
-    auto emit = [&](int k0, float4 p, float4 q, uint4 gv) {
+    if (row >= b) return;
+    auto emit = [&](int k0, float4 p, float4 q) {
+        const uint4 gv = *reinterpret_cast<const uint4 *>(g + k0);
         const float v[8] = {p.x * inv * bf16lo(gv.x), p.y * inv * bf16hi(gv.x), p.z * inv * bf16lo(gv.y),
                             p.w * inv * bf16hi(gv.y), q.x * inv * bf16lo(gv.z), q.y * inv * bf16hi(gv.z),
                             q.z * inv * bf16lo(gv.w), q.w * inv * bf16hi(gv.w)};
@@ -285,12 +285,11 @@ __global__ __launch_bounds__(256) void rmsnorm_pack_kernel(const float *x, const
     };
 #pragma unroll
     for (int i = 0; i < kKeep; ++i) {
-        const int k0 = threadIdx.x * 8 + i * 2048;
-        if (k0 < h) emit(k0, xp[i], xq[i], gk[i]);
+        const int k0 = (c0 + i * kPackLanes) * 8;
+        if (k0 < h) emit(k0, xp[i], xq[i]);
     }
-    for (int k0 = threadIdx.x * 8 + kKeep * 2048; k0 < h; k0 += 2048)
-        emit(k0, *reinterpret_cast<const float4 *>(xr + k0), *reinterpret_cast<const float4 *>(xr + k0 + 4),
-             *reinterpret_cast<const uint4 *>(g + k0));
+    for (int k0 = (c0 + kKeep * kPackLanes) * 8; k0 < h; k0 += kPackLanes * 8)
+        emit(k0, *reinterpret_cast<const float4 *>(xr + k0), *reinterpret_cast<const float4 *>(xr + k0 + 4));
 }
 
 // the kernels' dynamic LDS exceeds the default limit: raised per device by gemm_prepare_device()
@@ -341,16 +340,16 @@ hipError_t gemm_prepare_device()
 static int g_target_wgs = 256;   // one resident workgroup per compute unit
 void gemm_set_compute_units(int n) { if (n > 0) g_target_wgs = n; }
 
-GemmPlan gemm_plan(int n_tiles, int KS, int B)
+GemmPlan gemm_plan(int n_tiles, int KS, int B, int64_t part_bytes)
 {
-    GemmPlan p{1, 1, 1, 16, kAlgoXs};
+    GemmPlan p{1, 1, 1, 16, kAlgoXs, 1, B};
     if (B <= 32) {
         p.Kb = 1;                                              // a workgroup walks all of K itself
         p.Rg = n_tiles < g_target_wgs ? n_tiles : g_target_wgs;
         p.NB = B <= 16 ? 1 : 2; p.MT = B <= 16 ? 16 : 8;
     } else {
         p.algo = kAlgoWide;
-        plan_wide(n_tiles, KS, B, g_target_wgs, p);
+        plan_wide(n_tiles, KS, B, g_target_wgs, part_bytes, p);
     }
     return p;
 }
@@ -360,10 +359,10 @@ int64_t gemm_scratch_bytes(int n_tiles, int KS, int B) { return B <= 32 ? 0 : ge
 hipError_t launch_gemm(const GemmArgs &a0, int mode, hipStream_t s)
 {
     if (a0.B <= 0 || a0.n_tiles <= 0) return hipSuccess;
-    if (a0.B > 256 || a0.KS < 1) return hipErrorInvalidValue;
+    if (a0.KS < 1) return hipErrorInvalidValue;
     GemmArgs a = a0;
-    const GemmPlan p = gemm_plan(a.n_tiles, a.KS, a.B);
-    a.Kb = p.Kb; a.Rg = p.Rg;
+    const GemmPlan p = gemm_plan(a.n_tiles, a.KS, a.B, a.part ? a.part_bytes : 0);
+    a.Kb = p.Kb; a.Rg = p.Rg; a.NG = p.NG; a.GB = p.GB;
     if (a.sstats != nullptr && a.B > 32) return hipErrorInvalidValue;      // the consumer side of a folded RMSNorm: small-batch kernels only
     if (a.ngains != nullptr && (a.n_valid % 32 != 0 || !a.npk_hi || !a.npk_lo || (a.B <= 32 && !a.nstats))) return hipErrorInvalidValue;
     { const hipError_t e = gemm_prepare_device(); if (e != hipSuccess) return e; }
@@ -403,7 +402,7 @@ hipError_t launch_rmsnorm_pack(const float *x, const uint16_t *g, int b, int h, 
                                hipStream_t s)
 {
     if (b <= 0) return hipSuccess;
-    rmsnorm_pack_kernel<<<b, 256, 0, s>>>(x, g, h, h / 32, eps, hi, lo);
+    rmsnorm_pack_kernel<<<(unsigned)((b + kPackRows - 1) / kPackRows), kPackThreads, 0, s>>>(x, g, b, h, h / 32, eps, hi, lo);
     return hipGetLastError();
 }
 

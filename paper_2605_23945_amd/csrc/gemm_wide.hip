@@ -18,6 +18,10 @@
 //     1280 x 8192   22.0 -> 14.0  30.8 -> 17.5  34.1 -> 23.1  38.3 -> 27.3
 //     4096 x 1024   13.7 -> 10.0  17.2 -> 12.5  20.4 -> 16.5  22.5 -> 21.1
 //
+// More than 256 rows (prefill passes, large live batches) are cut into NG equal groups of up to 256 rows in ONE launch:
+// the groups of a row range are neighbours on one XCD and share its weight stream in L2, and the grid they fill is one
+// that K need not be split for (8192 x 3584 at 1024 rows: four launches of 256 rows took 172 us, one takes 80).
+//
 // K can be split across workgroups (`plan_wide`); the slices' partial sums go to a scratch tensor and a reduction
 // kernel adds them in slice order and runs the epilogue, so results never depend on timing.
 #include <algorithm>
@@ -26,17 +30,6 @@
 namespace pat {
 
 namespace {
-
-typedef __attribute__((address_space(3))) void *lds_ptr_t;
-
-// 64 lanes x 16 bytes from base + lane_off to the LDS bytes lds_off .. + 1023 (lane order), as a streaming read.
-// Inline assembly because the compiler, told of this load, waits for ALL outstanding loads before the next use of any
-// register loaded from memory; unknown to it, the load only makes its counted waits a little stricter.  The data is
-// waited for by hand (sync in the kernel below).
-__device__ __forceinline__ void load_to_lds(const u32x4_t *base, uint32_t lane_off, uint32_t lds_off)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_off), "v"(lane_off), "s"(base) : "memory");
-}
 
 // Depth of the two rings per tile shape: batch fragments XD k-steps ahead in registers (RA RB 4 accumulator registers
 // beside them), weights WS - 1 k-steps ahead in LDS.  Loads complete in order, so a wait for a batch fragment also waits
@@ -71,13 +64,14 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(GemmArgs a)
     const int KS = a.KS;
     // Workgroups are dealt round robin to the eight XCDs (blockIdx % 8); giving each XCD consecutive work items, slice
     // major, lets its workgroups share one K slice of the activations in their L2.
-    const int id = blockIdx.x, total = a.Kb * a.Rg;
+    const int id = blockIdx.x, total = a.Kb * a.Rg * a.NG;
     const int item = (id & 7) * (total >> 3) + min(id & 7, total & 7) + (id >> 3);
-    const int kb = item / a.Rg, rg = item - kb * a.Rg;
+    const int part = item / a.NG, grp = item - part * a.NG, kb = part / a.Rg, rg = part - kb * a.Rg;
+    const int b0 = grp * a.GB, nb = min(a.GB, a.B - b0);        // this workgroup's batch rows b0 .. b0 + nb - 1
     const int ks0 = (int)((int64_t)kb * KS / a.Kb), n = (int)((int64_t)(kb + 1) * KS / a.Kb) - ks0;
     const int rt0 = (int)((int64_t)rg * a.n_tiles / a.Rg), rt1 = (int)((int64_t)(rg + 1) * a.n_tiles / a.Rg);
-    const int bt_last = (a.B - 1) >> 4;
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)wring;
+    const int bt0 = b0 >> 4, bt_last = (nb - 1) >> 4;
+    const uint32_t lds0 = lds_offset(wring);
 
     // All requests are unconditional, from clamped (always valid) addresses, so that every wave issues the same number
     // per k-step: row tiles past the range repeat its last one and batch tiles past the live batch the last live one
@@ -87,9 +81,9 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(GemmArgs a)
     for (int i = 0; i < CW; ++i) wsrc[i] = reinterpret_cast<const u32x4_t *>(a.w) + ((int64_t)min(rt0 + wave * CW + i, rt1 - 1) * KS + ks0) * 64;
 #pragma unroll
     for (int i = 0; i < CX; ++i)
-        xsrc[i] = reinterpret_cast<const u32x4_t *>(i / RB ? a.xlo : a.xhi) + ((int64_t)min(wave * RB + i % RB, bt_last) * KS + ks0) * 64;
+        xsrc[i] = reinterpret_cast<const u32x4_t *>(i / RB ? a.xlo : a.xhi) + ((int64_t)(bt0 + min(wave * RB + i % RB, bt_last)) * KS + ks0) * 64;
     int s_req = 0, s_cur = 0;                                   // ring slots: of the next request, of the current k-step
-    auto request_w = [&](int t, int i) { load_to_lds(wsrc[i] + min(t, n - 1) * 64, lane * 16, lds0 + (s_req * RA + wave * CW + i) * 1024); };
+    auto request_w = [&](int t, int i) { load_to_lds_stream(wsrc[i] + min(t, n - 1) * 64, lane * 16, lds0 + (s_req * RA + wave * CW + i) * 1024); };
     auto request_x = [&](int t, int i) -> u32x4_t { return *(xsrc[i] + min(t, n - 1) * 64 + lane); };
 
     floatx4_t acc[RA][RB];
@@ -153,7 +147,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(GemmArgs a)
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
             const float4 v = make_float4(acc[ra][rb][0], acc[ra][rb][1], acc[ra][rb][2], acc[ra][rb][3]);
-            const int b = (wave * RB + rb) * 16 + (lane_e & 15), quad = lane_e >> 4;
+            const int bl = (wave * RB + rb) * 16 + (lane_e & 15), b = bl < nb ? b0 + bl : a.B, quad = lane_e >> 4;     // b == a.B: not stored
             if (MODE == kPartial) {
                 if (b < a.B) *reinterpret_cast<float4 *>(a.part + ((int64_t)kb * a.B + b) * ((int64_t)a.n_tiles * 16) + rt * 16 + quad * 4) = v;
             } else gemm_epilogue<MODE == kPartial ? 0 : MODE>(a, rt, quad, b, v);
@@ -162,16 +156,32 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(GemmArgs a)
     }
 }
 
-// The four consecutive features 4 q .. of batch row b, summed over the K slices in slice order.
-__device__ __forceinline__ float4 sum_slices(const GemmArgs &a, int b, int q)
+// The four consecutive features 4 q .. of batch row b, summed over the K slices in slice order; the slices' loads are
+// issued together (a loop over a run-time count would wait for each).
+template <int KB>
+__device__ __forceinline__ float4 sum_slices_n(const GemmArgs &a, int b, int q)
 {
     const int64_t ldp = (int64_t)a.n_tiles * 16;
-    float4 v = *reinterpret_cast<const float4 *>(a.part + (int64_t)b * ldp + q * 4);
-    for (int kb = 1; kb < a.Kb; ++kb) {
-        const float4 t = *reinterpret_cast<const float4 *>(a.part + ((int64_t)kb * a.B + b) * ldp + q * 4);
-        v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
-    }
+    float4 t[KB];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) t[kb] = *reinterpret_cast<const float4 *>(a.part + ((int64_t)kb * a.B + b) * ldp + q * 4);
+    float4 v = t[0];
+#pragma unroll
+    for (int kb = 1; kb < KB; ++kb) { v.x += t[kb].x; v.y += t[kb].y; v.z += t[kb].z; v.w += t[kb].w; }
     return v;
+}
+__device__ __forceinline__ float4 sum_slices(const GemmArgs &a, int b, int q)
+{
+    switch (a.Kb) {                                             // max_slices() is at most 8
+    case 1: return sum_slices_n<1>(a, b, q);
+    case 2: return sum_slices_n<2>(a, b, q);
+    case 3: return sum_slices_n<3>(a, b, q);
+    case 4: return sum_slices_n<4>(a, b, q);
+    case 5: return sum_slices_n<5>(a, b, q);
+    case 6: return sum_slices_n<6>(a, b, q);
+    case 7: return sum_slices_n<7>(a, b, q);
+    default: return sum_slices_n<8>(a, b, q);
+    }
 }
 
 // Slice sums, then the epilogue: one thread per (row tile, batch row, quad), quads fastest, then batch rows, so that a
@@ -241,40 +251,52 @@ __global__ __launch_bounds__(kNormThreads) void gemm_reduce_norm_kernel(GemmArgs
 template <int RA, int RB, int MODE>
 hipError_t launch_wide_t(const GemmArgs &a, hipStream_t s)
 {
-    gemm_wide_kernel<RA, RB, MODE><<<(unsigned)(a.Rg * a.Kb), 256, wide_lds_bytes<RA, RB>(), s>>>(a);
+    gemm_wide_kernel<RA, RB, MODE><<<(unsigned)(a.Rg * a.Kb * a.NG), 256, wide_lds_bytes<RA, RB>(), s>>>(a);
     return hipGetLastError();
 }
 
-// mode: kPartial, kGemmStore, or (12 row tiles only) any other epilogue in the kernel
+template <int RA, int RB>
+hipError_t launch_wide_modes(const GemmArgs &a, int mode, hipStream_t s)
+{
+    switch (mode) {
+    case kPartial: return launch_wide_t<RA, RB, kPartial>(a, s);
+    case kGemmStore: return launch_wide_t<RA, RB, kGemmStore>(a, s);
+    case kGemmAccum: return launch_wide_t<RA, RB, kGemmAccum>(a, s);
+    case kGemmQKV: return launch_wide_t<RA, RB, kGemmQKV>(a, s);
+    default: return launch_wide_t<RA, RB, kGemmSwiGLU>(a, s);
+    }
+}
+
+// mode: kPartial, kGemmStore, or (8 and 12 row tiles) any other epilogue in the kernel
 template <int RB>
 hipError_t launch_wide_rb(const GemmArgs &a, int RA, int mode, hipStream_t s)
 {
     if (RA == 4) return mode == kPartial ? launch_wide_t<4, RB, kPartial>(a, s) : launch_wide_t<4, RB, kGemmStore>(a, s);
-    if (RA == 8) return mode == kPartial ? launch_wide_t<8, RB, kPartial>(a, s) : launch_wide_t<8, RB, kGemmStore>(a, s);
-    switch (mode) {
-    case kPartial: return launch_wide_t<12, RB, kPartial>(a, s);
-    case kGemmStore: return launch_wide_t<12, RB, kGemmStore>(a, s);
-    case kGemmAccum: return launch_wide_t<12, RB, kGemmAccum>(a, s);
-    case kGemmQKV: return launch_wide_t<12, RB, kGemmQKV>(a, s);
-    default: return launch_wide_t<12, RB, kGemmSwiGLU>(a, s);
-    }
+    if (RA == 8) return launch_wide_modes<8, RB>(a, mode, s);
+    return launch_wide_modes<12, RB>(a, mode, s);
 }
 
 template <int RA, int RB, int MODE>
 hipError_t wide_set_lds_limit() { return hipFuncSetAttribute((const void *)gemm_wide_kernel<RA, RB, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, wide_lds_bytes<RA, RB>()); }
+
+template <int RA, int RB>
+hipError_t wide_set_lds_limit_modes()
+{
+    hipError_t e = wide_set_lds_limit<RA, RB, kPartial>();
+    if (e == hipSuccess) e = wide_set_lds_limit<RA, RB, kGemmStore>();
+    if (e == hipSuccess) e = wide_set_lds_limit<RA, RB, kGemmAccum>();
+    if (e == hipSuccess) e = wide_set_lds_limit<RA, RB, kGemmQKV>();
+    if (e == hipSuccess) e = wide_set_lds_limit<RA, RB, kGemmSwiGLU>();
+    return e;
+}
 
 template <int RB>
 hipError_t wide_set_lds_limits()
 {
     hipError_t e = wide_set_lds_limit<4, RB, kPartial>();
     if (e == hipSuccess) e = wide_set_lds_limit<4, RB, kGemmStore>();
-    if (e == hipSuccess) e = wide_set_lds_limit<8, RB, kPartial>();
-    if (e == hipSuccess) e = wide_set_lds_limit<8, RB, kGemmStore>();
-    if (e == hipSuccess) e = wide_set_lds_limit<12, RB, kPartial>();
-    if (e == hipSuccess) e = wide_set_lds_limit<12, RB, kGemmStore>();
-    if (e == hipSuccess) e = wide_set_lds_limit<12, RB, kGemmAccum>();
-    if (e == hipSuccess) e = wide_set_lds_limit<12, RB, kGemmQKV>();
-    if (e == hipSuccess) e = wide_set_lds_limit<12, RB, kGemmSwiGLU>();
+    if (e == hipSuccess) e = wide_set_lds_limit_modes<8, RB>();
+    if (e == hipSuccess) e = wide_set_lds_limit_modes<12, RB>();
     return e;
 }
 
@@ -305,18 +327,25 @@ hipError_t gemm_wide_prepare_device()
 // products (0.020 us per tile pair), the operand fetch (0.014 us per KiB and workgroup) and the weight stream (0.050 us
 // per KiB and workgroup with all 256 busy), plus 0.48 us per MB of partial sums.  Few row tiles per workgroup
 // and few slices suit narrow projections (1280 x 8192, 256 rows: 4 tiles 27.3 us, 8 tiles 33.6), many tiles wide ones
-// (22016 x 4096, 256 rows: 12 tiles 86 us, 8 tiles 98).  A projection that may not be cut at all has no scratch for
-// partial sums: it takes the 12-tile kernels, which exist with every epilogue.
-void plan_wide(int n_tiles, int KS, int B, int n_cu, GemmPlan &p)
+// (22016 x 4096, 256 rows: 12 tiles 86 us, 8 tiles 98).  A projection without scratch for partial sums takes the
+// 8- or 12-tile kernels, which exist with every epilogue.
+//
+// B > 256: NG groups of GB rows; part_bytes bounds the slices (B rows of partial sums each).
+void plan_wide(int n_tiles, int KS, int B, int n_cu, int64_t part_bytes, GemmPlan &p)
 {
-    const int RB = (B + 63) / 64, kb_max = max_slices(n_tiles, KS, n_cu);
+    p.NG = (B + 255) / 256;
+    p.GB = ((B + p.NG - 1) / p.NG + 15) / 16 * 16;
+    const int RB = (std::min(p.GB, B) + 63) / 64, kb_max = max_slices(n_tiles, KS, n_cu);
     double best = 0.0;
-    for (int RA = kb_max == 1 ? 12 : 4; RA <= 12; RA += 4)
+    for (int RA = 4; RA <= 12; RA += 4)
         for (int kb = 1; kb <= kb_max; ++kb) {
-            const int rg = (n_tiles + RA - 1) / RA, wgs = rg * kb, rounds = (wgs + n_cu - 1) / n_cu;
+            const int64_t bytes = (int64_t)kb * B * n_tiles * 64;
+            if (bytes > part_bytes && (kb > 1 || RA == 4)) continue;             // without scratch: one slice, kernels with every epilogue
+            const int rg = (n_tiles + RA - 1) / RA, wgs = rg * kb * p.NG, rounds = (wgs + n_cu - 1) / n_cu;
             const double busy = std::min(1.0, (double)wgs / n_cu);
             const double step = std::max({0.0203 * RA * RB, 0.0058 + 0.0142 * (RA + 8 * RB), 0.0502 * RA * busy});
-            const double cost = 7.5 + rounds * ((KS + kb - 1) / kb) * step + 0.476e-6 * 4.0 * kb * B * n_tiles * 16.0 + (kb > 1 ? 1.0 : 0.0);
+            const double parts = kb == 1 && RA != 4 ? 0.0 : 0.476e-6 * (double)bytes + 1.0;
+            const double cost = 7.5 + rounds * ((KS + kb - 1) / kb) * step + parts;
             if (best == 0.0 || cost < best) { best = cost; p.Kb = kb; p.Rg = rg; p.MT = RA; }
         }
     p.NB = 4 * RB;
@@ -332,7 +361,7 @@ int64_t gemm_wide_scratch_bytes(int n_tiles, int KS, int B, int n_cu)
 hipError_t launch_gemm_wide(const GemmArgs &a0, const GemmPlan &p, int mode, hipStream_t s)
 {
     GemmArgs a = a0;
-    const bool direct = p.Kb == 1 && (mode == kGemmStore || p.MT == 12);
+    const bool direct = p.Kb == 1 && (mode == kGemmStore || p.MT != 4);
     if (!direct && (a.part == nullptr || (int64_t)a.Kb * a.B * a.n_tiles * 64 > a.part_bytes)) return hipErrorInvalidValue;
     const int m = direct ? mode : kPartial;
     if (direct) a.ngains = nullptr;          // the epilogue's own hand-over is the small-batch one (x * gains and per-tile statistics)

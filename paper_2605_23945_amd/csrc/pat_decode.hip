@@ -179,7 +179,7 @@ void layouts(const pat_cfg *c, const Shard &s, WorkLayout *w, WeightLayout *wt, 
     w->nstats = take((int64_t)cdiv(s.H, 16) * 32 * 4);    // per-tile sums of squares of the residual rows, live batch <= 32
     w->stats1 = take((int64_t)cdiv(s.H, 16) * 16 * 4); w->stats2 = take((int64_t)cdiv(s.H, 16) * 16 * 4);
     w->sync = take((int64_t)kFusedSyncWords * 4);
-    w->max_chunks = c->kv_token_budget / kMinChunk + 2 * (int64_t)MB;
+    w->max_chunks = c->kv_token_budget / kMinChunk + 4 * (int64_t)MB;      // also a full prefill pass of rows of four chunks
     w->chunk_meta = take(w->max_chunks * 32);
     w->part_acc = take(w->max_chunks * s.hq * s.d * 4);
     w->part_ml = take(w->max_chunks * s.hq * 2 * 4);
@@ -260,31 +260,6 @@ GemmArgs gemm_args(const void *w, int n, int k, const uint4 *xhi, const uint4 *x
     return g;
 }
 
-// Batches beyond 256 rows run as groups of 256 (the weights are streamed once per group).
-hipError_t gemm_groups(GemmArgs g, int mode, hipStream_t st)
-{
-    const int B = g.B;
-    for (int b0 = 0; b0 < B; b0 += 256) {
-        GemmArgs h = g;
-        h.B = std::min(256, B - b0);
-        const int64_t t0 = b0 / 16;
-        h.xhi = g.xhi + t0 * g.KS * 64; h.xlo = g.xlo + t0 * g.KS * 64;
-        if (g.y) h.y = g.y + (int64_t)b0 * g.ldy;
-        if (g.yhi) { h.yhi = g.yhi + t0 * g.KS_out * 64; h.ylo = g.ylo + t0 * g.KS_out * 64; }
-        if (g.ngains) { h.npk_hi = g.npk_hi + t0 * (g.n_tiles / 2) * 64; h.npk_lo = g.npk_lo + t0 * (g.n_tiles / 2) * 64; }
-        const bool norm_after = g.ngains && B > 32 && h.B <= 32;         // a last small group has no finished norm: a launch of its own
-        if (norm_after) h.ngains = nullptr;
-        if (g.kv_len) {
-            h.kv_len = g.kv_len + b0;
-            if (g.row_slot) h.row_slot = g.row_slot + b0; else h.page_table = g.page_table + (int64_t)b0 * g.max_pages;
-        }
-        hipError_t e = launch_gemm(h, mode, st);
-        if (e == hipSuccess && norm_after) e = launch_rmsnorm_pack(h.y, g.ngains, h.B, g.s_h, g.s_eps, h.npk_hi, h.npk_lo, st);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-}
-
 int pick_chunk(const pat_ctx *c, int64_t *n_chunks)
 {
     auto count = [&](int C) { int64_t n = 0; for (int i = 0; i < c->live; ++i) n += (c->kv_len[i] + 1 + C - 1) / C; return n; };
@@ -312,6 +287,39 @@ int pick_chunk(const pat_ctx *c, int64_t *n_chunks)
         if (best_n * c->sh.hkv >= 2 * (int64_t)c->n_cu) break;
     }
     *n_chunks = best_n;
+    return best;
+}
+
+// Blocks of a prefill pass: n consecutive positions of one sequence, rows row0 .. of the pass.
+struct PfBlock { int row0, n, slot, pos0; };
+
+// Chunk length of a prefill pass's attention, and the chunks of all its rows (0: every row has one, so nothing is merged).
+// Two workgroups fit a compute unit; an item takes about 3 us and 1.2 us per tile of 64 keys (alone on its compute unit or
+// beside another), a merge another launch and the partial results' round trip.  Short contexts (or passes with items enough) are best left whole; a wide pass of
+// few items over a long context is cut until it fills the chip.
+int pick_prefill_chunk(const pat_ctx *c, const std::vector<PfBlock> &blocks, int64_t *row_chunks)
+{
+    const double slots = 2.0 * c->n_cu;
+    int longest = 0;
+    for (const PfBlock &b : blocks) longest = std::max(longest, b.pos0 + b.n);
+    int best = 0; double best_cost = 0.0;
+    for (int C = 256;; C *= 2) {
+        double tiles = 0.0; int64_t rec = 0, rc = 0;
+        for (const PfBlock &b : blocks) {
+            const int L = b.pos0 + b.n;
+            tiles += (L + 63) / 64;
+            rec += (L + C - 1) / C;
+            for (int i = 0; i < b.n; ++i) rc += (b.pos0 + i + 1 + C - 1) / C;
+        }
+        const bool whole = C >= longest;
+        if (whole || (rc <= c->wl.max_chunks && rec <= kPfRecords)) {
+            const double items = (double)rec * c->sh.hkv, one = 1.2 * ((std::min(C, longest) + 63) / 64);
+            double cost = std::max(1.2 * tiles * c->sh.hkv / slots, one) + 3.0 * std::ceil(items / slots);
+            if (!whole) cost += 5.0 + 2.0e-6 * (double)rc * c->sh.hq * c->sh.d * 4;
+            if (best == 0 || cost < best_cost) { best = C; best_cost = cost; *row_chunks = whole ? 0 : rc; }
+        }
+        if (whole) break;
+    }
     return best;
 }
 
@@ -605,7 +613,8 @@ int pat_step_algo_bytes(pat_ctx *c, double *weight_bytes, double *kv_bytes)
 // The transformer layers over B rows whose embeddings sit in x: row b is the token at position pos[b]
 // (= tokens cached before it) of slot row_slot[b] (NULL: slot b, the decode step).  The attention
 // chunk records of these rows must have been planned; n_blocks > 0: the records are the block records
-// of a prefill pass (the block kernel), n_chunks still counts the rows' own chunks.  Leaves the rows'
+// of a prefill pass (the block kernel), n_chunks still counts the rows' own chunks (0: one chunk per row, whose
+// output the block kernel writes itself).  Leaves the rows'
 // final hidden states in x.
 static int run_layers(pat_ctx *c, int B, int C, int64_t n_chunks, const int32_t *pos, const int32_t *row_slot, int64_t n_blocks)
 {
@@ -648,11 +657,11 @@ static int run_layers(pat_ctx *c, int B, int C, int64_t n_chunks, const int32_t 
             if (!c->cfg.qk_norm) {
                 g.kv = c->kv; g.layer = l; g.hq = s.hq; g.max_pages = s.max_pages; g.kv_len = pos; g.row_slot = row_slot;
                 g.page_table = c->st.page_table; g.rope_cs = at<float>(W, w.rope);
-                TimeScope t(c, 0); PAT_HIP(c, gemm_groups(g, kGemmQKV, st));
+                TimeScope t(c, 0); PAT_HIP(c, launch_gemm(g, kGemmQKV, st));
             } else {
                 // per-head q/k normalisation needs whole heads: plain projection, then one small kernel
                 // that normalises, rotates and appends
-                { TimeScope t(c, 0); PAT_HIP(c, gemm_groups(g, kGemmStore, st)); }
+                { TimeScope t(c, 0); PAT_HIP(c, launch_gemm(g, kGemmStore, st)); }
                 TimeScope t(c, 2);
                 PAT_HIP(c, launch_qknorm_rope_append(qkv, s.qkv_rows, s.hq, c->kv, l, pos, row_slot, c->st.page_table, s.max_pages,
                                                      at<float>(W, w.rope), (const uint16_t *)(L + c->wt.gq),
@@ -662,25 +671,25 @@ static int run_layers(pat_ctx *c, int B, int C, int64_t n_chunks, const int32_t 
         aa.layer = l;
         {
             TimeScope t(c, 1);
-            if (n_blocks > 0) { aa.n_items = (int)(n_blocks * s.hkv); PAT_HIP(c, launch_attn_prefill(aa, st)); }
+            if (n_blocks > 0) { aa.n_items = (int)(n_blocks * s.hkv); PAT_HIP(c, launch_attn_prefill(aa, n_chunks == 0, st)); }
             else PAT_HIP(c, launch_attn_partial(aa, st));
-            PAT_HIP(c, launch_attn_merge(aa, st));
+            if (n_blocks == 0 || n_chunks > 0) PAT_HIP(c, launch_attn_merge(aa, st));
         }
         {
             GemmArgs g = gemm_args(L + c->wt.wo, s.H, s.hq * s.d, b_hi, b_lo, B, x, s.H, gpart, w.gemm_part_bytes);
             produce(g, L + c->wt.g2);
-            TimeScope t(c, 0); PAT_HIP(c, gemm_groups(g, kGemmAccum, st));
+            TimeScope t(c, 0); PAT_HIP(c, launch_gemm(g, kGemmAccum, st));
         }
         {
             GemmArgs g = gemm_args(L + c->wt.wgu, 2 * s.F, s.H, a_hi, a_lo, B, nullptr, 0, gpart, w.gemm_part_bytes);
             g.yhi = b_hi; g.ylo = b_lo; g.KS_out = s.F / 32;
             consume(g, false);
-            TimeScope t(c, 3); PAT_HIP(c, gemm_groups(g, kGemmSwiGLU, st));
+            TimeScope t(c, 3); PAT_HIP(c, launch_gemm(g, kGemmSwiGLU, st));
         }
         {
             GemmArgs g = gemm_args(L + c->wt.wd, s.H, s.F, b_hi, b_lo, B, x, s.H, gpart, w.gemm_part_bytes);
             produce(g, l + 1 < s.NL ? Wb + c->wt.layer0 + c->wt.layer_stride * (l + 1) + c->wt.g1 : Wb + c->wt.gf);   // the next RMSNorm's gains
-            TimeScope t(c, 0); PAT_HIP(c, gemm_groups(g, kGemmAccum, st));
+            TimeScope t(c, 0); PAT_HIP(c, launch_gemm(g, kGemmAccum, st));
         }
     }
     return PAT_OK;
@@ -828,7 +837,7 @@ int pat_decode_step(pat_ctx *c, pat_step_report *report_host, int32_t *next_tok_
                 g.sstats = s.NL > 0 ? at<float>(W, w.nstats) : at<float>(W, w.stats_e);
                 g.s_parts = s.NL > 0 ? cdiv(s.H, 16) : 1; g.s_h = s.H; g.s_eps = c->cfg.rms_eps;
             }
-            TimeScope t(c, 0); PAT_HIP(c, gemm_groups(g, kGemmStore, st));
+            TimeScope t(c, 0); PAT_HIP(c, launch_gemm(g, kGemmStore, st));
         }
     }
     { TimeScope t(c, 2); PAT_HIP(c, launch_argmax(logits, B, s.Vs, s.vocab0, next_tok, at<float>(W, w.best_val), st)); }
@@ -880,14 +889,15 @@ int pat_prefill(pat_ctx *c, int32_t n, const int32_t *slots, const int32_t *toke
         if (tokens[t] < 0 || tokens[t] >= s.V) return fail(c, PAT_EINVAL, "prefill: token id %d outside the vocabulary", tokens[t]);
     if (n_tokens == 0) return PAT_OK;
 
-    const int MB = c->cfg.max_batch, R_max = MB, C = 256;
+    const int MB = c->cfg.max_batch, R_max = MB;
     void *W = c->bufs.work;
     int32_t *rows = at<int32_t>(W, c->wl.rows);
     char *Wb = at<char>(c->bufs.weights, 0);
     int si = 0, pos = 0;
     int64_t t = 0;
-    const int NP = 16 / (s.hq / s.hkv);            // positions per attention block (the kernel's 16 operand rows / heads per KV head)
+    const int NP = attn_prefill_block(s.hq / s.hkv);      // positions per attention block
     const size_t set_ints = (size_t)kPfRecords * 8 + (size_t)3 * MB;
+    std::vector<PfBlock> blocks;
     int pass = 0;
     while (t < n_tokens) {
         // Two pinned staging sets in turn: the host builds pass n + 1 while the GPU runs pass n, and waits only for
@@ -897,33 +907,28 @@ int pat_prefill(pat_ctx *c, int32_t n, const int32_t *slots, const int32_t *toke
         if (c->pf_used[set]) PAT_HIP(c, hipEventSynchronize(c->pf_done[set]));
         int32_t *rec = c->pf_stage + set * set_ints;
         int32_t *p = rec + (size_t)kPfRecords * 8;
-        // one pass: the next rows in (slot, position) order, as many as the work buffers and the
-        // attention workspace take; a row's keys are rows of this or an earlier pass.  Rows of one
-        // sequence whose positions share pos / NP form a block; a block has one record per chunk of
-        // C keys up to its last position (C is a multiple of NP: every row of a block has the same chunks).
+        // one pass: the next rows in (slot, position) order, as many as the work buffers take; a row's keys are rows of
+        // this or an earlier pass.  Up to NP consecutive positions of one sequence form a block.
         int R = 0;
-        int64_t chunks = 0, n_rec = 0;
+        blocks.clear();
         while (R < R_max && t < n_tokens) {
             while (pos >= c->kv_len[slots[si]]) { ++si; pos = 0; }
-            const int64_t need = (pos + 1 + C - 1) / C;
-            const bool new_block = R == 0 || p[MB + R - 1] != slots[si] || pos % NP == 0;
-            if (chunks + need > c->wl.max_chunks || (new_block && n_rec + need > kPfRecords)) break;
-            if (new_block) {
-                for (int64_t ch = 0; ch < need; ++ch) {
-                    int32_t *r8 = rec + (n_rec + ch) * 8;
-                    r8[0] = R; r8[1] = 0; r8[2] = slots[si]; r8[3] = pos; r8[4] = (int32_t)(ch * C); r8[5] = r8[6] = r8[7] = 0;
-                }
-                n_rec += need;
-            }
-            for (int64_t ch = 0; ch < need; ++ch) rec[(n_rec - need + ch) * 8 + 1] += 1;     // one more row in the current block
-            p[R] = tokens[t]; p[MB + R] = slots[si]; p[2 * MB + R] = pos;
-            chunks += need; ++R; ++t; ++pos;
+            const int len = std::min({NP, c->kv_len[slots[si]] - pos, R_max - R});
+            blocks.push_back(PfBlock{R, len, slots[si], pos});
+            for (int i = 0; i < len; ++i, ++R, ++t, ++pos) { p[R] = tokens[t]; p[MB + R] = slots[si]; p[2 * MB + R] = pos; }
         }
-        if (R == 0) return fail(c, PAT_ENOMEM, "prefill: one row needs more attention chunks than the workspace holds");
+        int64_t chunks = 0;
+        const int C = pick_prefill_chunk(c, blocks, &chunks);
+        int64_t n_rec = 0;
+        for (const PfBlock &b : blocks)
+            for (int k0 = 0; k0 < b.pos0 + b.n; k0 += C) {
+                int32_t *r8 = rec + (n_rec++) * 8;
+                r8[0] = b.row0; r8[1] = b.n; r8[2] = b.slot; r8[3] = b.pos0; r8[4] = k0; r8[5] = r8[6] = r8[7] = 0;
+            }
         for (int a = 0; a < 3; ++a)
             PAT_HIP(c, hipMemcpyAsync(rows + a * MB, p + a * MB, (size_t)R * 4, hipMemcpyHostToDevice, c->stream));
         PAT_HIP(c, hipMemcpyAsync(c->st.chunk_meta, rec, (size_t)n_rec * 32, hipMemcpyHostToDevice, c->stream));
-        PAT_HIP(c, launch_plan_rows(c->st, R, C, rows + MB, rows + 2 * MB, false, c->stream));
+        if (chunks > 0) PAT_HIP(c, launch_plan_rows(c->st, R, C, rows + MB, rows + 2 * MB, false, c->stream));
         if (norm_is_folded(R))
             PAT_HIP(c, launch_embed_stats((const uint16_t *)(Wb + c->wt.embed), s.H, rows, (const uint16_t *)(Wb + c->wt.layer0 + c->wt.g1), R, at<float>(W, c->wl.x),
                                           at<float>(W, c->wl.stats_e), at<uint4>(W, c->wl.a_hi), at<uint4>(W, c->wl.a_lo), c->stream));
@@ -1182,7 +1187,7 @@ int64_t pat_op_gemm_scratch_bytes(int32_t n, int32_t k, int32_t b)
 int pat_op_gemm_plan(int32_t n, int32_t k, int32_t b, int32_t plan[4])
 {
     if (!plan || n <= 0 || k <= 0 || k % 32 || b <= 0 || b > 256) return PAT_EINVAL;
-    const GemmPlan p = gemm_plan(cdiv(n, 16), k / 32, b);
+    const GemmPlan p = gemm_plan(cdiv(n, 16), k / 32, b, gemm_scratch_bytes(cdiv(n, 16), k / 32, b));
     plan[0] = p.algo; plan[1] = p.Kb; plan[2] = p.Rg; plan[3] = p.NB;
     return PAT_OK;
 }

@@ -46,6 +46,21 @@ __device__ __host__ __forceinline__ int64_t packed_elem_offset(int row, int k, i
     return ((((int64_t)tile * KS + ks) * 64 + g * 16 + r) << 3) + j;
 }
 
+// Asynchronous loads from memory to LDS: 64 lanes x 16 bytes from base + lane_off (base wave-uniform) to the LDS bytes
+// lds_off .. lds_off + 1023 in lane order; _stream marks the data as read once.  Inline assembly because the compiler,
+// told of such a load, waits for ALL outstanding loads before the next use of any register loaded from memory; unknown
+// to it, the load only makes its counted waits a little stricter.  The caller waits for the data by hand
+// (s_waitcnt vmcnt), and drains them before the workgroup ends.
+__device__ __forceinline__ uint32_t lds_offset(const void *p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p; }
+__device__ __forceinline__ void load_to_lds(const void *base, uint32_t lane_off, uint32_t lds_off)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_off), "v"(lane_off), "s"(base) : "memory");
+}
+__device__ __forceinline__ void load_to_lds_stream(const void *base, uint32_t lane_off, uint32_t lds_off)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_off), "v"(lane_off), "s"(base) : "memory");
+}
+
 // Agent-scope (write-through) stores and loads: data that another workgroup of the SAME launch reads after a
 // device-wide barrier is written with these, so that no cache-wide write-back is needed; the reader uses
 // plain loads provided the address was not read earlier in the launch (no stale line can exist then).

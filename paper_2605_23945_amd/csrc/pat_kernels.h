@@ -43,14 +43,14 @@ struct GemmArgs {
     const float *sstats; int s_parts, s_h; float s_eps;
     float *part;               // scratch for K-slice partials [Kb][B][n_tiles * 16], or NULL
     int64_t part_bytes;        // its size: a plan that needs more is refused
-    int Kb, Rg;                // set by launch_gemm from gemm_plan
+    int Kb, Rg, NG, GB;        // set by launch_gemm from gemm_plan
 };
 // How a [16 n_tiles, 32 KS] projection at live batch B is cut: K slices across workgroups and row groups.
 enum GemmAlgo { kAlgoXs = 0, kAlgoWide = 3 };
-struct GemmPlan { int Kb, Rg, NB, MT, algo; };      // MT: waves per workgroup (small-batch kernel) or row tiles per workgroup (gemm_wide)
-GemmPlan gemm_plan(int n_tiles, int KS, int B);
+struct GemmPlan { int Kb, Rg, NB, MT, algo, NG, GB; };      // MT: waves (small-batch kernel) or row tiles (gemm_wide) per workgroup; NG groups of GB batch rows
+GemmPlan gemm_plan(int n_tiles, int KS, int B, int64_t part_bytes);
 int64_t gemm_scratch_bytes(int n_tiles, int KS, int B);      // room for partial sums that launch_gemm may need
-void plan_wide(int n_tiles, int KS, int B, int n_cu, GemmPlan &p);
+void plan_wide(int n_tiles, int KS, int B, int n_cu, int64_t part_bytes, GemmPlan &p);
 int64_t gemm_wide_scratch_bytes(int n_tiles, int KS, int B, int n_cu);
 hipError_t gemm_wide_prepare_device();
 hipError_t launch_gemm_wide(const GemmArgs &a, const GemmPlan &p, int mode, hipStream_t s);
@@ -89,7 +89,8 @@ struct AttnArgs {
     int n_items;               // n_chunks_total * hkv (host mirror)
 };
 hipError_t launch_attn_partial(const AttnArgs &a, hipStream_t s);
-hipError_t launch_attn_prefill(const AttnArgs &a, hipStream_t s);
+int attn_prefill_block(int G);            // positions per block record
+hipError_t launch_attn_prefill(const AttnArgs &a, bool direct, hipStream_t s);      // direct: one chunk per row, no merge
 hipError_t launch_attn_merge(const AttnArgs &a, hipStream_t s);
 
 // ---- fused layer kernel for live batches <= 16 (layer_fused.hip) ------------------

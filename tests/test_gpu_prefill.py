@@ -207,3 +207,14 @@ def test_prefill_is_bitwise_repeatable_and_stable_across_pass_widths():
         for t in range(2):
             same, close = bf16_close(outs[0][j][0][t], outs[2][j][0][t])
             assert close and same > 0.999
+
+
+# the block attention kernel: every head grouping and head dimension, blocks of 64 / G positions and 64-key tiles cut by
+# the sequence ends, pages shorter and longer than a tile; the last case's rows are few and its context long, so that its
+# keys are cut into chunks and merged
+@pytest.mark.parametrize("hq,hkv,d,page,lens,width", [(2, 2, 128, 16, (65, 1, 130), 256), (4, 2, 128, 128, (63, 64, 129), 96),
+                                                      (8, 2, 64, 32, (15, 200, 17), 232), (8, 1, 128, 64, (8, 9, 191), 64),
+                                                      (8, 1, 64, 64, (1300,), 256)])
+def test_block_attention_edges(hq, hkv, d, page, lens, width):
+    shard = pi.ShardShape(pi.ModelShape(2, 256, hq, hkv, d, 256, 256), 1, 0)
+    _prefill_parity(shard, list(lens), list(range(len(lens))), max_batch=width, page_tokens=page)
