@@ -15,7 +15,7 @@
 //
 // What bounds it: at long contexts the matrix cores and the vector ALU about equally (per wave and tile 80 products of
 // 16 clocks against 16 exponentials and splits per lane); at short ones the latency of an item's first loads.
-#include "pat_dev.h"
+#include "attn_mfma_dev.h"
 #include "pat_kernels.h"
 
 namespace pat {
@@ -24,23 +24,6 @@ namespace {
 
 constexpr int kRows = 64;       // operand rows per item
 constexpr int kTile = 64;       // keys per tile
-typedef short shortx4_t __attribute__((ext_vector_type(4)));
-
-// four 16-bit elements per lane, transposed among the 16 lanes of a group: element j of lane i is element i % 4 of the
-// 8 bytes that lane i / 4 + 4 j addresses
-__device__ __forceinline__ uint2 lds_read_tr(const char *p)
-{
-    typedef __attribute__((address_space(3))) shortx4_t *ptr_t;
-    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((ptr_t)p));
-}
-
-// the upper 16 bits of x and of y: two truncated bf16 values, x in the lower half
-__device__ __forceinline__ uint32_t upper_halves(float x, float y) { return __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u); }
-
-__device__ __forceinline__ floatx4_t mfma(u32x4_t a, u32x4_t b, floatx4_t c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
-}
 
 // DIRECT: every row has one chunk; the finished output goes to the packed operand of the O projection instead of the
 // partial (m, l, acc) of the row's chunk list.
@@ -102,12 +85,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a)
 #pragma unroll
         for (int ks = 0; ks < KST; ++ks) {
             const float4 q0 = *reinterpret_cast<const float4 *>(qp + ks * 32), q1 = *reinterpret_cast<const float4 *>(qp + ks * 32 + 4);
-            const float qv[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
-            uint16_t hh[8], ll[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) split_bf16(qv[j] * scale, hh[j], ll[j]);
-            qh[ks] = u32x4_t{(uint32_t)hh[0] | ((uint32_t)hh[1] << 16), (uint32_t)hh[2] | ((uint32_t)hh[3] << 16), (uint32_t)hh[4] | ((uint32_t)hh[5] << 16), (uint32_t)hh[6] | ((uint32_t)hh[7] << 16)};
-            ql[ks] = u32x4_t{(uint32_t)ll[0] | ((uint32_t)ll[1] << 16), (uint32_t)ll[2] | ((uint32_t)ll[3] << 16), (uint32_t)ll[4] | ((uint32_t)ll[5] << 16), (uint32_t)ll[6] | ((uint32_t)ll[7] << 16)};
+            split_fragment(q0, q1, scale, qh[ks], ql[ks]);
         }
     }
     look_up(t0 + kTile);
@@ -135,9 +113,9 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a)
                 kf[j] = *reinterpret_cast<const u32x4_t *>(kt + (key * PC + ((ks * 4 + g4) ^ (key & (PC - 1)))) * 16);
             }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) s[j] = mfma(kf[j], qh[ks], s[j]);
+            for (int j = 0; j < 4; ++j) s[j] = mfma_16x16x32(kf[j], qh[ks], s[j]);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) s[j] = mfma(kf[j], ql[ks], s[j]);
+            for (int j = 0; j < 4; ++j) s[j] = mfma_16x16x32(kf[j], ql[ks], s[j]);
         }
         float p[16];
 #pragma unroll
@@ -165,15 +143,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a)
         for (int j = 0; j < 16; ++j) { p[j] = __builtin_amdgcn_exp2f(p[j] - m0_); den += p[j]; }
 #pragma unroll
         for (int u = 0; u < 2; ++u) {                                    // 32 keys: the 16-key tiles 2 u and 2 u + 1
-            // p = h + m + l exactly: truncated to the upper 8 significant bits, the remainder likewise, and what is left
             u32x4_t ph, pm, pl;
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                const float x = p[u * 8 + 2 * w], y = p[u * 8 + 2 * w + 1];
-                const float xr = x - __uint_as_float(__float_as_uint(x) & 0xFFFF0000u), yr = y - __uint_as_float(__float_as_uint(y) & 0xFFFF0000u);
-                const float xl = xr - __uint_as_float(__float_as_uint(xr) & 0xFFFF0000u), yl = yr - __uint_as_float(__float_as_uint(yr) & 0xFFFF0000u);
-                ph[w] = upper_halves(x, y); pm[w] = upper_halves(xr, yr); pl[w] = upper_halves(xl, yl);
-            }
+            split3_bf16(p + u * 8, ph, pm, pl);
             const int ka = u * 32 + g4 * 4 + (col >> 2), kb = ka + 16;   // keys whose pieces this lane addresses
 #pragma unroll
             for (int f = 0; f < FT; ++f) {
@@ -181,9 +152,9 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a)
                 const uint2 va = lds_read_tr(vt + (ka * PC + (piece ^ (ka & (PC - 1)))) * 16 + half);
                 const uint2 vb = lds_read_tr(vt + (kb * PC + (piece ^ (kb & (PC - 1)))) * 16 + half);
                 const u32x4_t vf = {va.x, va.y, vb.x, vb.y};
-                o[f] = mfma(vf, ph, o[f]);
-                o[f] = mfma(vf, pm, o[f]);
-                o[f] = mfma(vf, pl, o[f]);
+                o[f] = mfma_16x16x32(vf, ph, o[f]);
+                o[f] = mfma_16x16x32(vf, pm, o[f]);
+                o[f] = mfma_16x16x32(vf, pl, o[f]);
             }
         }
     }

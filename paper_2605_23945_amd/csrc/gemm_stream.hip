@@ -333,6 +333,7 @@ hipError_t gemm_prepare_device()
     e = xs_set_lds_limit<1, 8, 8, 16>();
     if (e == hipSuccess) e = xs_set_lds_limit<2, 8, 8, 8>();
     if (e == hipSuccess) e = gemm_wide_prepare_device();
+    if (e == hipSuccess) e = attn_gqa_prepare_device();
     if (e == hipSuccess && dev >= 0 && dev < 64) done |= 1ull << dev;
     return e;
 }

@@ -264,15 +264,21 @@ int pick_chunk(const pat_ctx *c, int64_t *n_chunks)
 {
     auto count = [&](int C) { int64_t n = 0; for (int i = 0; i < c->live; ++i) n += (c->kv_len[i] + 1 + C - 1) / C; return n; };
     if (c->sh.hq / c->sh.hkv >= 4) {
-        // The matrix-score kernel holds three workgroups per compute unit; an item alone takes about
-        // 7 us (a chain of dependent loads) + 2.3 us per round of 64 tokens (measured at chunk lengths
-        // 64 .. 1024): take the chunk length that minimises (waves of items over the chip) x (time of
-        // one item).  This rule picks the measured best length at live batches 1 .. 256.
-        const int64_t slots = 3 * (int64_t)c->n_cu;
+        // One workgroup of attn_gqa_kernel fits a compute unit.  An item takes about 4.1 us before and after its stream and
+        // 0.625 us per 64 tokens (32 KiB) when memory keeps up; when it does not, the stream runs at 6.2 TB/s and three
+        // quarters of the 4.1 us show in every round of items over the chip.  Measured (128 features, 8 heads, one KV
+        // head): 11 sequences of about 6000 tokens 22.6 / 15.9 / 15.1 / 16.3 / 11.0 / 11.6 / 16.6 us at 64 / 128 / 192 /
+        // 256 / 320 / 512 / 1024 tokens, 180 of about 2100 101.7 / 62.4 / 59.3 / 55.1 / 49.5 / 44.6 / 37.6 us; the merge
+        // adds 0.05 us per chunk of the longest sequence.  The rule takes the best length in both.
+        const int64_t tile_bytes = 64 * 2 * 2 * (int64_t)c->sh.d;
+        int longest = 0; int64_t tiles = 0;
+        for (int i = 0; i < c->live; ++i) { longest = std::max(longest, c->kv_len[i] + 1); tiles += (c->kv_len[i] + 64) / 64; }
         int best = kMinChunk; int64_t best_n = 0; double best_cost = 0.0;
-        for (int C : {1024, 512, 256, 128, 64}) {
-            const int64_t n = count(C), items = n * c->sh.hkv;
-            const double cost = (double)((items + slots - 1) / slots) * (7.0 + 2.3 * (C / 64));
+        for (int C : {1024, 896, 768, 640, 512, 448, 384, 320, 256, 192, 128, 64}) {
+            const int64_t n = count(C);
+            const double rounds = (double)((n * c->sh.hkv + c->n_cu - 1) / c->n_cu), scale = (double)tile_bytes / 32768.0;
+            const double cost = std::max(rounds * (4.1 + 0.625 * scale * (C / 64)), (double)(tiles * c->sh.hkv * tile_bytes) / 6.2e6 + 3.1 * rounds) +
+                                0.05 * ((longest + C - 1) / C);
             if (best_n == 0 || cost < best_cost) { best = C; best_n = n; best_cost = cost; }
         }
         *n_chunks = best_n;

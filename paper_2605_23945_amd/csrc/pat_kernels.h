@@ -65,8 +65,9 @@ hipError_t launch_pack_act(const float *x, int b, int k, uint4 *hi, uint4 *lo, h
 hipError_t launch_rmsnorm_pack(const float *x, const uint16_t *g, int b, int h, float eps, uint4 *hi, uint4 *lo,
                                hipStream_t s);
 hipError_t launch_gemm(const GemmArgs &a, int mode, hipStream_t s);
-// sets the dynamic-LDS limit of the small-batch kernels on the current device (once per context)
+// sets the dynamic-LDS limits of the kernels on the current device (once per device)
 hipError_t gemm_prepare_device();
+hipError_t attn_gqa_prepare_device();
 
 // ---- attention over the paged cache (attention.hip) ----------------------------
 
@@ -89,6 +90,7 @@ struct AttnArgs {
     int n_items;               // n_chunks_total * hkv (host mirror)
 };
 hipError_t launch_attn_partial(const AttnArgs &a, hipStream_t s);
+hipError_t launch_attn_gqa(const AttnArgs &a, hipStream_t s);        // the case of 4 or 8 query heads per KV head
 int attn_prefill_block(int G);            // positions per block record
 hipError_t launch_attn_prefill(const AttnArgs &a, bool direct, hipStream_t s);      // direct: one chunk per row, no merge
 hipError_t launch_attn_merge(const AttnArgs &a, hipStream_t s);
