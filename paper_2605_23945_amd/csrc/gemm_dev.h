@@ -41,6 +41,16 @@ __device__ __forceinline__ float4 mfma_sum_pinned(floatx4_t h, floatx4_t l)
     return make_float4(x, y, z, w);
 }
 
+// The tile whose operand holds the high terms in columns 0 .. 7 and the low terms in columns 8 .. 15: column c plus column
+// c ^ 8 (a rotation by 8 inside the 16 lanes of a row), pinned in the same way.
+__device__ __forceinline__ float4 mfma_halves_pinned(floatx4_t v)
+{
+    auto other = [](float f) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(f), 0x128, 0xF, 0xF, false)); };   // row_ror:8
+    float x = v[0] + other(v[0]), y = v[1] + other(v[1]), z = v[2] + other(v[2]), w = v[3] + other(v[3]);
+    asm volatile("" : "+v"(x), "+v"(y), "+v"(z), "+v"(w));
+    return make_float4(x, y, z, w);
+}
+
 __device__ __forceinline__ float silu(float z) { return z / (1.0f + expf(-z)); }
 
 // What the epilogue of (row tile rt, quad, batch row b) reads besides the tile's sums: the position, page and

@@ -82,7 +82,52 @@ __device__ __forceinline__ void xs_pass(const GemmArgs &a, int lane, int wave, i
     }
 }
 
-template <int NB, int UK, int TB, int kXsWaves, int MODE>
+// The same for a live batch of at most 8 rows, whose high and low terms share one operand: columns 0 .. 7 hold the rows'
+// high terms, columns 8 .. 15 their low terms, and a tile's sum is column c plus column c ^ 8: bit by bit the sums of
+// xs_pass.  Half the matrix instructions, and half the activation loads: a 1 KiB load instruction costs a compute unit
+// about 14 ns wherever its data is, and with two per k-step the activations took 2/3 of the loads of a workgroup with one row
+// tile (7B down projection, 4096 x 11008: 1032 loads, 14 of the launch's 19 us).  7B shard, 2 rows: step 3.78 -> 3.64 ms;
+// its TP = 4 shard, 1 row: 1.57 -> 1.53 ms.  The registers this frees are better left free: a second tile's weights in
+// flight gave nothing (1.53 ms), passes of 11 k-steps lost 1 %.
+template <int U, int WAVES>
+__device__ __forceinline__ void xs_pass8(const GemmArgs &a, int lane, int wave, int kw0, int tb0, int nt, bool first, float4 *red)
+{
+    const int KS = a.KS;
+    u32x4_t x[U];
+    const uint4 *px = ((lane & 8) ? a.xlo : a.xhi) + kw0 * 64 + (lane >> 4) * 16 + min(lane & 7, a.B - 1);
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = ld16(px + u * 64);
+    auto fetch = [&](u32x4_t (&w)[U], int i) {
+        const uint4 *wp = a.w + ((int64_t)(tb0 + i) * KS + kw0) * 64 + lane;
+#pragma unroll
+        for (int u = 0; u < U; ++u) w[u] = ld16(wp + u * 64);
+        __builtin_amdgcn_sched_barrier(0);                  // all U loads in flight, ahead of the matrix instructions
+    };
+    auto tile = [&](const u32x4_t (&w)[U], int i) {
+        floatx4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc = mfma16(w[u], x[u], acc);
+        float4 v = mfma_halves_pinned(acc);
+        float4 *slot = &red[(i * WAVES + wave) * 64 + lane];
+        if (!first) { const float4 o = *slot; v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w; }
+        *slot = v;
+    };
+    for (int i = 0; i < nt; ++i) {
+        u32x4_t w[U];
+        fetch(w, i);
+        tile(w, i);
+    }
+}
+
+// one pass of either kind
+template <int NB, int U, int WAVES, bool HL>
+__device__ __forceinline__ void xs_run(const GemmArgs &a, int lane, int wave, int kw0, int tb0, int nt, bool first, float4 *red)
+{
+    if constexpr (HL) xs_pass8<U, WAVES>(a, lane, wave, kw0, tb0, nt, first, red);
+    else xs_pass<NB, U, WAVES>(a, lane, wave, kw0, tb0, nt, first, red);
+}
+
+template <int NB, int UK, int TB, int kXsWaves, bool HL, int MODE>
 __global__ __launch_bounds__(kXsWaves * 64) void gemm_xs_kernel(GemmArgs a)
 {
     extern __shared__ float4 red[];   // [TB][kXsWaves][NB][64]
@@ -112,15 +157,15 @@ __global__ __launch_bounds__(kXsWaves * 64) void gemm_xs_kernel(GemmArgs a)
         for (int k = kown0; k < kown1;) {
             const int rem = kown1 - k;
             const bool first = k == kown0;
-            if (rem >= 8) { xs_pass<NB, 8, kXsWaves>(a, lane, wave, k, tb0, nt, first, red); k += 8; continue; }
+            if (rem >= 8) { xs_run<NB, 8, kXsWaves, HL>(a, lane, wave, k, tb0, nt, first, red); k += 8; continue; }
             switch (rem) {
-            case 7: xs_pass<NB, 7, kXsWaves>(a, lane, wave, k, tb0, nt, first, red); break;
-            case 6: xs_pass<NB, 6, kXsWaves>(a, lane, wave, k, tb0, nt, first, red); break;
-            case 5: xs_pass<NB, 5, kXsWaves>(a, lane, wave, k, tb0, nt, first, red); break;
-            case 4: xs_pass<NB, 4, kXsWaves>(a, lane, wave, k, tb0, nt, first, red); break;
-            case 3: xs_pass<NB, 3, kXsWaves>(a, lane, wave, k, tb0, nt, first, red); break;
-            case 2: xs_pass<NB, 2, kXsWaves>(a, lane, wave, k, tb0, nt, first, red); break;
-            default: xs_pass<NB, 1, kXsWaves>(a, lane, wave, k, tb0, nt, first, red); break;
+            case 7: xs_run<NB, 7, kXsWaves, HL>(a, lane, wave, k, tb0, nt, first, red); break;
+            case 6: xs_run<NB, 6, kXsWaves, HL>(a, lane, wave, k, tb0, nt, first, red); break;
+            case 5: xs_run<NB, 5, kXsWaves, HL>(a, lane, wave, k, tb0, nt, first, red); break;
+            case 4: xs_run<NB, 4, kXsWaves, HL>(a, lane, wave, k, tb0, nt, first, red); break;
+            case 3: xs_run<NB, 3, kXsWaves, HL>(a, lane, wave, k, tb0, nt, first, red); break;
+            case 2: xs_run<NB, 2, kXsWaves, HL>(a, lane, wave, k, tb0, nt, first, red); break;
+            default: xs_run<NB, 1, kXsWaves, HL>(a, lane, wave, k, tb0, nt, first, red); break;
             }
             k = kown1;
         }
@@ -293,27 +338,27 @@ __global__ __launch_bounds__(kPackThreads) void rmsnorm_pack_kernel(const float 
 }
 
 // the kernels' dynamic LDS exceeds the default limit: raised per device by gemm_prepare_device()
-template <int NB, int UK, int TB, int kXsWaves>
+template <int NB, int UK, int TB, int kXsWaves, bool HL>
 hipError_t xs_set_lds_limit()
 {
     constexpr size_t lds = (size_t)TB * kXsWaves * NB * 64 * sizeof(float4);
-    hipError_t e = hipFuncSetAttribute((const void *)gemm_xs_kernel<NB, UK, TB, kXsWaves, kGemmStore>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)gemm_xs_kernel<NB, UK, TB, kXsWaves, kGemmAccum>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)gemm_xs_kernel<NB, UK, TB, kXsWaves, kGemmSwiGLU>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)gemm_xs_kernel<NB, UK, TB, kXsWaves, kGemmQKV>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipError_t e = hipFuncSetAttribute((const void *)gemm_xs_kernel<NB, UK, TB, kXsWaves, HL, kGemmStore>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)gemm_xs_kernel<NB, UK, TB, kXsWaves, HL, kGemmAccum>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)gemm_xs_kernel<NB, UK, TB, kXsWaves, HL, kGemmSwiGLU>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)gemm_xs_kernel<NB, UK, TB, kXsWaves, HL, kGemmQKV>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     return e;
 }
 
-template <int NB, int UK, int TB, int kXsWaves>
+template <int NB, int UK, int TB, int kXsWaves, bool HL>
 hipError_t launch_xs(const GemmArgs &a, int mode, hipStream_t s)
 {
     const unsigned grid = (unsigned)a.Rg;
     constexpr size_t lds = (size_t)TB * kXsWaves * NB * 64 * sizeof(float4);
     switch (mode) {
-    case kGemmStore: gemm_xs_kernel<NB, UK, TB, kXsWaves, kGemmStore><<<grid, kXsWaves * 64, lds, s>>>(a); break;
-    case kGemmAccum: gemm_xs_kernel<NB, UK, TB, kXsWaves, kGemmAccum><<<grid, kXsWaves * 64, lds, s>>>(a); break;
-    case kGemmQKV: gemm_xs_kernel<NB, UK, TB, kXsWaves, kGemmQKV><<<grid, kXsWaves * 64, lds, s>>>(a); break;
-    default: gemm_xs_kernel<NB, UK, TB, kXsWaves, kGemmSwiGLU><<<grid, kXsWaves * 64, lds, s>>>(a); break;
+    case kGemmStore: gemm_xs_kernel<NB, UK, TB, kXsWaves, HL, kGemmStore><<<grid, kXsWaves * 64, lds, s>>>(a); break;
+    case kGemmAccum: gemm_xs_kernel<NB, UK, TB, kXsWaves, HL, kGemmAccum><<<grid, kXsWaves * 64, lds, s>>>(a); break;
+    case kGemmQKV: gemm_xs_kernel<NB, UK, TB, kXsWaves, HL, kGemmQKV><<<grid, kXsWaves * 64, lds, s>>>(a); break;
+    default: gemm_xs_kernel<NB, UK, TB, kXsWaves, HL, kGemmSwiGLU><<<grid, kXsWaves * 64, lds, s>>>(a); break;
     }
     return hipGetLastError();
 }
@@ -330,8 +375,9 @@ hipError_t gemm_prepare_device()
     if (e != hipSuccess) return e;
     std::lock_guard<std::mutex> lock(mu);
     if (dev >= 0 && dev < 64 && (done >> dev & 1)) return hipSuccess;
-    e = xs_set_lds_limit<1, 8, 8, 16>();
-    if (e == hipSuccess) e = xs_set_lds_limit<2, 8, 8, 8>();
+    e = xs_set_lds_limit<1, 8, 8, 16, true>();
+    if (e == hipSuccess) e = xs_set_lds_limit<1, 8, 8, 16, false>();
+    if (e == hipSuccess) e = xs_set_lds_limit<2, 8, 8, 8, false>();
     if (e == hipSuccess) e = gemm_wide_prepare_device();
     if (e == hipSuccess) e = attn_gqa_prepare_device();
     if (e == hipSuccess && dev >= 0 && dev < 64) done |= 1ull << dev;
@@ -367,9 +413,11 @@ hipError_t launch_gemm(const GemmArgs &a0, int mode, hipStream_t s)
     if (a.sstats != nullptr && a.B > 32) return hipErrorInvalidValue;      // the consumer side of a folded RMSNorm: small-batch kernels only
     if (a.ngains != nullptr && (a.n_valid % 32 != 0 || !a.npk_hi || !a.npk_lo || (a.B <= 32 && !a.nstats))) return hipErrorInvalidValue;
     { const hipError_t e = gemm_prepare_device(); if (e != hipSuccess) return e; }
-    // measured on MI355X: 16 waves x 8 resident k-steps is best for one batch tile, 8 x 8 for two
-    if (a.B <= 16) return launch_xs<1, 8, 8, 16>(a, mode, s);
-    if (a.B <= 32) return launch_xs<2, 8, 8, 8>(a, mode, s);
+    // measured on MI355X: 16 waves x 8 resident k-steps is best for one batch tile, 8 x 8 for two; up to 8 rows both halves of
+    // the split share the tile (xs_pass8)
+    if (a.B <= 8) return launch_xs<1, 8, 8, 16, true>(a, mode, s);
+    if (a.B <= 16) return launch_xs<1, 8, 8, 16, false>(a, mode, s);
+    if (a.B <= 32) return launch_xs<2, 8, 8, 8, false>(a, mode, s);
     return launch_gemm_wide(a, p, mode, s);
 }
 
