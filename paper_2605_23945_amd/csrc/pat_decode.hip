@@ -434,10 +434,12 @@ int pat_load_layer(pat_ctx *c, int32_t layer, const pat_layer_weights *w)
         PAT_HIP(c, hipMemcpyAsync(L + c->wt.gq, w->gq, (size_t)s.d * 2, hipMemcpyDeviceToDevice, c->stream));
         PAT_HIP(c, hipMemcpyAsync(L + c->wt.gk, w->gk, (size_t)s.d * 2, hipMemcpyDeviceToDevice, c->stream));
     }
-    PAT_HIP(c, launch_pack_weight_qkv((const uint16_t *)w->wqkv, s.qkv_rows, s.H, s.H, (s.hq + s.hkv) * s.d, s.d, (uint4 *)(L + c->wt.wqkv), c->stream));
-    PAT_HIP(c, launch_pack_weight((const uint16_t *)w->wo, nullptr, s.H, s.hq * s.d, s.hq * s.d, (uint4 *)(L + c->wt.wo), c->stream));
-    PAT_HIP(c, launch_pack_weight((const uint16_t *)w->wg, (const uint16_t *)w->wu, s.F, s.H, s.H, (uint4 *)(L + c->wt.wgu), c->stream));
-    PAT_HIP(c, launch_pack_weight((const uint16_t *)w->wd, nullptr, s.H, s.F, s.F, (uint4 *)(L + c->wt.wd), c->stream));
+    const PackJob jobs[] = {
+        pack_job((const uint16_t *)w->wqkv, nullptr, s.qkv_rows, s.H, s.H, (uint4 *)(L + c->wt.wqkv), (s.hq + s.hkv) * s.d, s.d),
+        pack_job((const uint16_t *)w->wo, nullptr, s.H, s.hq * s.d, s.hq * s.d, (uint4 *)(L + c->wt.wo)),
+        pack_job((const uint16_t *)w->wg, (const uint16_t *)w->wu, s.F, s.H, s.H, (uint4 *)(L + c->wt.wgu)),
+        pack_job((const uint16_t *)w->wd, nullptr, s.H, s.F, s.F, (uint4 *)(L + c->wt.wd))};
+    PAT_HIP(c, launch_pack_weights(jobs, 4, c->stream));
     c->layer_loaded[layer] = 1;
     return PAT_OK;
 }
@@ -467,13 +469,15 @@ int pat_load_layer_from_full(pat_ctx *c, int32_t layer, const pat_layer_weights 
     uint4 *pq = (uint4 *)(L + c->wt.wqkv);
     const int64_t KS = s.H / 32;
     uint4 *pk = pq + (int64_t)(s.hq * d / 16) * KS * 64, *pv = pk + (int64_t)(s.hkv * d / 16) * KS * 64;
-    PAT_HIP(c, launch_pack_weight_qkv(wqkv + (int64_t)q0 * d * s.H, s.hq * d, s.H, s.H, s.hq * d, d, pq, c->stream));
-    PAT_HIP(c, launch_pack_weight_qkv(wqkv + ((int64_t)Hq + kv0) * d * s.H, s.hkv * d, s.H, s.H, s.hkv * d, d, pk, c->stream));
-    PAT_HIP(c, launch_pack_weight_qkv(wqkv + ((int64_t)Hq + Hkv + kv0) * d * s.H, s.hkv * d, s.H, s.H, 0, d, pv, c->stream));
     // O and down take a column range (strided rows), gate and up a row range
-    PAT_HIP(c, launch_pack_weight(wo + (int64_t)q0 * d, nullptr, s.H, s.hq * d, (int64_t)Hq * d, (uint4 *)(L + c->wt.wo), c->stream));
-    PAT_HIP(c, launch_pack_weight(wg + (int64_t)f0 * s.H, wu + (int64_t)f0 * s.H, s.F, s.H, s.H, (uint4 *)(L + c->wt.wgu), c->stream));
-    PAT_HIP(c, launch_pack_weight(wd + f0, nullptr, s.H, s.F, Ff, (uint4 *)(L + c->wt.wd), c->stream));
+    const PackJob jobs[] = {
+        pack_job(wqkv + (int64_t)q0 * d * s.H, nullptr, s.hq * d, s.H, s.H, pq, s.hq * d, d),
+        pack_job(wqkv + ((int64_t)Hq + kv0) * d * s.H, nullptr, s.hkv * d, s.H, s.H, pk, s.hkv * d, d),
+        pack_job(wqkv + ((int64_t)Hq + Hkv + kv0) * d * s.H, nullptr, s.hkv * d, s.H, s.H, pv, 0, d),
+        pack_job(wo + (int64_t)q0 * d, nullptr, s.H, s.hq * d, (int64_t)Hq * d, (uint4 *)(L + c->wt.wo)),
+        pack_job(wg + (int64_t)f0 * s.H, wu + (int64_t)f0 * s.H, s.F, s.H, s.H, (uint4 *)(L + c->wt.wgu)),
+        pack_job(wd + f0, nullptr, s.H, s.F, Ff, (uint4 *)(L + c->wt.wd))};
+    PAT_HIP(c, launch_pack_weights(jobs, 6, c->stream));
     c->layer_loaded[layer] = 1;
     return PAT_OK;
 }

@@ -56,11 +56,21 @@ hipError_t gemm_wide_prepare_device();
 hipError_t launch_gemm_wide(const GemmArgs &a, const GemmPlan &p, int mode, hipStream_t s);
 void gemm_set_compute_units(int n);
 
-// [n, k] (or gate/up pair w, w2) row-major with `ld` elements between rows -> streaming layout
+// [n, k] (or gate/up pair w, w2) row-major with `ld` elements between rows -> streaming layout.  Within each of the first
+// rope_rows / d heads of a QKV matrix, row p holds natural row p/2 (p even) or p/2 + d/2 (p odd), so the two elements a
+// rotation mixes are neighbours.
+struct PackJob {
+    const uint16_t *w, *w2;
+    uint4 *packed;
+    int64_t ld;
+    int n, KS, n_tiles, rope_rows, d;
+    int block0;                // set by launch_pack_weights
+};
+constexpr int kPackJobs = 6;
+struct PackJobs { PackJob job[kPackJobs]; int n; };
+PackJob pack_job(const uint16_t *w, const uint16_t *w2, int n, int k, int64_t ld, uint4 *packed, int rope_rows = 0, int d = 1);
+hipError_t launch_pack_weights(const PackJob *jobs, int n, hipStream_t s);
 hipError_t launch_pack_weight(const uint16_t *w, const uint16_t *w2, int n, int k, int64_t ld, uint4 *packed, hipStream_t s);
-// as above for rows of a QKV matrix: within each of the first rope_rows / d heads, row p holds natural row
-// p/2 (p even) or p/2 + d/2 (p odd), so the two elements a rotation mixes are neighbours
-hipError_t launch_pack_weight_qkv(const uint16_t *w, int n, int k, int64_t ld, int rope_rows, int d, uint4 *packed, hipStream_t s);
 hipError_t launch_pack_act(const float *x, int b, int k, uint4 *hi, uint4 *lo, hipStream_t s);
 hipError_t launch_rmsnorm_pack(const float *x, const uint16_t *g, int b, int h, float eps, uint4 *hi, uint4 *lo,
                                hipStream_t s);
