@@ -49,6 +49,9 @@ __global__ __launch_bounds__(kAttnThreads) void attn_stream_kernel(AttnArgs a)
         const bool rec_pages = C <= 4 * P;
         const int32_t *pt = a.page_table + (int64_t)(a.row_slot ? a.row_slot[b] : b) * a.max_pages;
         const int pfirst = t0 / P;
+        // chunks of more pages than their record holds (at most kMaxChunk / 16): lane i keeps the chunk's i-th page, so that no
+        // page look-up stands between a round's requests and the previous round's
+        const int pages = rec_pages ? 0 : pt[min(pfirst + lane, (t0 + cnt - 1) / P)];
         const int64_t head_off = (int64_t)h * P * D + seg * 8;
 
         // K and V rows of one round: addresses first (unconditional, clamped to the chunk's last
@@ -57,14 +60,8 @@ __global__ __launch_bounds__(kAttnThreads) void attn_stream_kernel(AttnArgs a)
             int64_t off[UR];
 #pragma unroll
             for (int u = 0; u < UR; ++u) {
-                const int tc = t0 + min(r0 + u * TPR + ts, cnt - 1);
-                int page;
-                if (rec_pages) {
-                    const int j = tc / P - pfirst;
-                    page = j == 0 ? m1.x : j == 1 ? m1.y : j == 2 ? m1.z : m1.w;
-                } else {
-                    page = pt[tc / P];
-                }
+                const int tc = t0 + min(r0 + u * TPR + ts, cnt - 1), j = tc / P - pfirst;
+                const int page = !rec_pages ? __shfl(pages, j, 64) : j == 0 ? m1.x : j == 1 ? m1.y : j == 2 ? m1.z : m1.w;
                 off[u] = page * page_elems + head_off + (int64_t)(tc % P) * D;
             }
 #pragma unroll
@@ -180,6 +177,31 @@ __global__ __launch_bounds__(kAttnThreads) void attn_stream_kernel(AttnArgs a)
         }
         __syncthreads();
         // the four waves' states in wave order; wave 0 always holds the chunk's first token
+        if (a.direct) {
+            // The row's only chunk (no merge: 8 sequences of the tiny configuration, two layers, step 82 -> 72 us together with
+            // the plan's and the embedding's common launch): the operand of the O
+            // projection, as the merge of one chunk would write it
+            for (int e = tid; e < G * D / 8; e += kAttnThreads) {
+                const int g = e / (D / 8), d0 = (e - g * (D / 8)) * 8;
+                float mw[4], sw[4], Mc = -INFINITY;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) { mw[w] = wml[(w * G + g) * 2]; Mc = fmaxf(Mc, mw[w]); }
+#pragma unroll
+                for (int w = 0; w < 4; ++w) sw[w] = mw[w] == -INFINITY ? 0.f : expf(mw[w] - Mc);
+                const float inv = 1.0f / ((wml[(0 * G + g) * 2 + 1] * sw[0] + wml[(1 * G + g) * 2 + 1] * sw[1]) +
+                                          (wml[(2 * G + g) * 2 + 1] * sw[2] + wml[(3 * G + g) * 2 + 1] * sw[3]));
+                float o[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int dd = d0 + j;
+                    o[j] = ((red[(0 * G + g) * D + dd] * sw[0] + red[(1 * G + g) * D + dd] * sw[1]) +
+                            (red[(2 * G + g) * D + dd] * sw[2] + red[(3 * G + g) * D + dd] * sw[3])) * inv;
+                }
+                attn_write_operand<false>(a, b, (h * G + g) * D + d0, o);
+            }
+            __syncthreads();
+            continue;
+        }
         for (int e = tid; e < G * D + G; e += kAttnThreads) {
             const int g = e < G * D ? e / D : e - G * D;
             float mw[4], Mc = -INFINITY;
@@ -211,6 +233,46 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(AttnArgs a)
     attn_merge_row_head<D, false>(a, blockIdx.y, blockIdx.x, threadIdx.x);
 }
 
+// Four waves per (sequence, query head), their states combined in wave order: what a merge of a long context takes is its
+// rounds of dependent loads (16 chunks a round for one wave of 128 features, 64 for four).  One sequence
+// of 33 chunks on 8 heads: the launch 4.86 -> 3.92 us, two of 23 on 32 heads 4.87 -> 4.78.
+constexpr int kMergeWaves = 4;
+template <int D>
+__global__ __launch_bounds__(kMergeWaves * 64) void attn_merge_wide_kernel(AttnArgs a)
+{
+    constexpr int LPT = D / 8;
+    __shared__ float st[kMergeWaves][LPT][10];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, b = blockIdx.y, head = blockIdx.x;
+    const int ce0 = a.chunk_start[b], nch = a.chunk_start[b + 1] - ce0;
+    float M, den, o[8];
+    attn_merge_fold<D>(a, ce0, nch, head, lane, wave, kMergeWaves, M, den, o);
+    if (lane < LPT) {
+        st[wave][lane][8] = M; st[wave][lane][9] = den;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) st[wave][lane][j] = o[j];
+    }
+    __syncthreads();
+    if (threadIdx.x >= LPT) return;
+    float Mc = M;                                           // wave 0 holds the first chunk: finite
+#pragma unroll
+    for (int w = 1; w < kMergeWaves; ++w) Mc = fmaxf(Mc, st[w][lane][8]);
+    const float s0 = expf(M - Mc);
+    den *= s0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) o[j] *= s0;
+#pragma unroll
+    for (int w = 1; w < kMergeWaves; ++w) {
+        const float sw = st[w][lane][8] == -INFINITY ? 0.f : expf(st[w][lane][8] - Mc);
+        den += st[w][lane][9] * sw;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o[j] += st[w][lane][j] * sw;
+    }
+    const float inv = 1.0f / den;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) o[j] *= inv;
+    attn_write_operand<false>(a, b, head * D + lane * 8, o);
+}
+
 template <int D>
 hipError_t launch_partial_d(const AttnArgs &a, int grid, hipStream_t s)
 {
@@ -240,9 +302,13 @@ hipError_t launch_attn_merge(const AttnArgs &a, hipStream_t s)
 {
     if (a.B <= 0) return hipSuccess;
     const dim3 grid(a.hq, a.B);
-    if (a.kv.d == 128) attn_merge_kernel<128><<<grid, 64, 0, s>>>(a);
-    else if (a.kv.d == 64) attn_merge_kernel<64><<<grid, 64, 0, s>>>(a);
-    else return hipErrorInvalidValue;
+    if (a.kv.d != 128 && a.kv.d != 64) return hipErrorInvalidValue;
+    // four waves where one would take a second round of loads and the chip has room for the others beside it
+    if (a.longest_chunks > 4 * (512 / a.kv.d) && (int64_t)a.hq * a.B <= 1024) {
+        if (a.kv.d == 128) attn_merge_wide_kernel<128><<<grid, kMergeWaves * 64, 0, s>>>(a);
+        else attn_merge_wide_kernel<64><<<grid, kMergeWaves * 64, 0, s>>>(a);
+    } else if (a.kv.d == 128) attn_merge_kernel<128><<<grid, 64, 0, s>>>(a);
+    else attn_merge_kernel<64><<<grid, 64, 0, s>>>(a);
     return hipGetLastError();
 }
 

@@ -191,6 +191,17 @@ __global__ __launch_bounds__(W * 64) void attn_gqa_kernel(AttnArgs a)
             v.x = fmaf(t.x, sw, v.x); v.y = fmaf(t.y, sw, v.y); v.z = fmaf(t.z, sw, v.z); v.w = fmaf(t.w, sw, v.w);
             l = fmaf(wml[w][g][1], sw, l);
         }
+        if (a.direct) {
+            // the row's only chunk: four features of the O projection's operand, as the merge of one chunk would write them
+            const float inv = 1.0f / l;
+            uint16_t hh[4], ll[4];
+            split_bf16(v.x * inv, hh[0], ll[0]); split_bf16(v.y * inv, hh[1], ll[1]);
+            split_bf16(v.z * inv, hh[2], ll[2]); split_bf16(v.w * inv, hh[3], ll[3]);
+            const int64_t off = packed_elem_offset(b, (h * G + g) * D + e % (D / 4) * 4, a.hq * D / 32);
+            *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(a.ohi) + off) = make_uint2(hh[0] | (uint32_t)hh[1] << 16, hh[2] | (uint32_t)hh[3] << 16);
+            *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(a.olo) + off) = make_uint2(ll[0] | (uint32_t)ll[1] << 16, ll[2] | (uint32_t)ll[3] << 16);
+            continue;
+        }
         const int64_t row = (int64_t)ce * a.hq + h * G + g;
         reinterpret_cast<float4 *>(a.part_acc + row * D)[e % (D / 4)] = v;
         if (e % (D / 4) == 0) *reinterpret_cast<float2 *>(a.part_ml + row * 2) = make_float2(Mc * 0.69314718f, l);     // the merge works in natural units

@@ -25,6 +25,7 @@
 // Before each barrier a wave requests the first weight blocks of its next phase, so that HBM keeps streaming
 // while the workgroups wait for each other.  Results do not depend on timing: every sum has a fixed order.
 #include "attn_merge_dev.h"
+#include "embed_dev.h"
 #include "gemm_dev.h"
 
 namespace pat {
@@ -371,38 +372,11 @@ __global__ __launch_bounds__(kFT) void layer_fused_kernel(FusedArgs fa)
 #undef PAT_FUSED_STAMP
 }
 
-// Embedding rows as fp32, each row's sum of squares (one part per row), and the rows times the first layer's
-// RMSNorm gains as the packed split-bf16 operand of its QKV projection.  One workgroup of 256 threads per row;
-// the sum has a fixed order (per thread, per wave by shuffles, the four waves in order).
-__global__ __launch_bounds__(256) void embed_stats_kernel(const uint16_t *table, int H, const int32_t *tok, const uint16_t *gains, float *x,
-                                                          float *stats, uint4 *pk_hi, uint4 *pk_lo)
+__global__ __launch_bounds__(kEmbedThreads) void embed_stats_kernel(const uint16_t *table, int H, const int32_t *tok, const uint16_t *gains, float *x,
+                                                                    float *stats, uint4 *pk_hi, uint4 *pk_lo)
 {
-    __shared__ float part[4];
-    const int b = blockIdx.x;
-    const uint16_t *row = table + (int64_t)tok[b] * H;
-    float ss = 0.f;
-    for (int k0 = threadIdx.x * 8; k0 < H; k0 += 256 * 8) {
-        const uint4 v = *reinterpret_cast<const uint4 *>(row + k0);
-        const uint4 gv = *reinterpret_cast<const uint4 *>(gains + k0);
-        const float4 p = make_float4(bf16lo(v.x), bf16hi(v.x), bf16lo(v.y), bf16hi(v.y));
-        const float4 q = make_float4(bf16lo(v.z), bf16hi(v.z), bf16lo(v.w), bf16hi(v.w));
-        float *o = x + (int64_t)b * H + k0;
-        *reinterpret_cast<float4 *>(o) = p;
-        *reinterpret_cast<float4 *>(o + 4) = q;
-        ss += (p.x * p.x + p.y * p.y) + (p.z * p.z + p.w * p.w) + (q.x * q.x + q.y * q.y) + (q.z * q.z + q.w * q.w);
-        const float xg[8] = {p.x * bf16lo(gv.x), p.y * bf16hi(gv.x), p.z * bf16lo(gv.y), p.w * bf16hi(gv.y),
-                             q.x * bf16lo(gv.z), q.y * bf16hi(gv.z), q.z * bf16lo(gv.w), q.w * bf16hi(gv.w)};
-        uint16_t hh[8], ll[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) split_bf16(xg[j], hh[j], ll[j]);
-        const int64_t vi = packed_elem_offset(b, k0, H >> 5) >> 3;
-        pk_hi[vi] = make_uint4(hh[0] | (uint32_t)hh[1] << 16, hh[2] | (uint32_t)hh[3] << 16, hh[4] | (uint32_t)hh[5] << 16, hh[6] | (uint32_t)hh[7] << 16);
-        pk_lo[vi] = make_uint4(ll[0] | (uint32_t)ll[1] << 16, ll[2] | (uint32_t)ll[3] << 16, ll[4] | (uint32_t)ll[5] << 16, ll[6] | (uint32_t)ll[7] << 16);
-    }
-    ss = wave_sum(ss);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
-    __syncthreads();
-    if (threadIdx.x == 0) stats[b] = (part[0] + part[1]) + (part[2] + part[3]);
+    __shared__ float part[kEmbedThreads / 64];
+    embed_stats_row(table, H, tok, gains, blockIdx.x, x, stats, pk_hi, pk_lo, part);
 }
 
 // x [b, k] fp32 times gains [k] -> packed split-bf16 (the operand of a projection with a folded RMSNorm); one thread per (row, 8 k)
@@ -456,7 +430,7 @@ hipError_t launch_embed_stats(const uint16_t *table, int H, const int32_t *tok, 
                               uint4 *pk_hi, uint4 *pk_lo, hipStream_t s)
 {
     if (B <= 0) return hipErrorInvalidValue;
-    embed_stats_kernel<<<B, 256, 0, s>>>(table, H, tok, gains, x, stats, pk_hi, pk_lo);
+    embed_stats_kernel<<<B, kEmbedThreads, 0, s>>>(table, H, tok, gains, x, stats, pk_hi, pk_lo);
     return hipGetLastError();
 }
 

@@ -263,28 +263,39 @@ GemmArgs gemm_args(const void *w, int n, int k, const uint4 *xhi, const uint4 *x
 int pick_chunk(const pat_ctx *c, int64_t *n_chunks)
 {
     auto count = [&](int C) { int64_t n = 0; for (int i = 0; i < c->live; ++i) n += (c->kv_len[i] + 1 + C - 1) / C; return n; };
+    int longest = 0;
+    for (int i = 0; i < c->live; ++i) longest = std::max(longest, c->kv_len[i] + 1);
+    // One chunk per sequence needs no merge: the attention kernel writes the O projection's operand itself.
     if (c->sh.hq / c->sh.hkv >= 4) {
         // One workgroup of attn_gqa_kernel fits a compute unit.  An item takes about 4.1 us before and after its stream and
         // 0.625 us per 64 tokens (32 KiB) when memory keeps up; when it does not, the stream runs at 6.2 TB/s and three
         // quarters of the 4.1 us show in every round of items over the chip.  Measured (128 features, 8 heads, one KV
         // head): 11 sequences of about 6000 tokens 22.6 / 15.9 / 15.1 / 16.3 / 11.0 / 11.6 / 16.6 us at 64 / 128 / 192 /
         // 256 / 320 / 512 / 1024 tokens, 180 of about 2100 101.7 / 62.4 / 59.3 / 55.1 / 49.5 / 44.6 / 37.6 us; the merge
-        // adds 0.05 us per chunk of the longest sequence.  The rule takes the best length in both.
+        // adds 5 us and 0.05 us per chunk of the longest sequence, unless every sequence is one chunk (8 sequences of up to 173
+        // tokens 2.1 us faster per layer whole, of up to 691 2.5 us slower; 128 of up to 1018 4.2 us faster).  The rule takes
+        // the best length in each.
         const int64_t tile_bytes = 64 * 2 * 2 * (int64_t)c->sh.d;
-        int longest = 0; int64_t tiles = 0;
-        for (int i = 0; i < c->live; ++i) { longest = std::max(longest, c->kv_len[i] + 1); tiles += (c->kv_len[i] + 64) / 64; }
+        int64_t tiles = 0;
+        for (int i = 0; i < c->live; ++i) tiles += (c->kv_len[i] + 64) / 64;
         int best = kMinChunk; int64_t best_n = 0; double best_cost = 0.0;
-        for (int C : {1024, 896, 768, 640, 512, 448, 384, 320, 256, 192, 128, 64}) {
+        for (int C : {longest, 1024, 896, 768, 640, 512, 448, 384, 320, 256, 192, 128, 64}) {
+            if (C > 1024) continue;                             // the kernel's longest chunk
             const int64_t n = count(C);
             const double rounds = (double)((n * c->sh.hkv + c->n_cu - 1) / c->n_cu), scale = (double)tile_bytes / 32768.0;
-            const double cost = std::max(rounds * (4.1 + 0.625 * scale * (C / 64)), (double)(tiles * c->sh.hkv * tile_bytes) / 6.2e6 + 3.1 * rounds) +
-                                0.05 * ((longest + C - 1) / C);
+            const double cost = std::max(rounds * (4.1 + 0.625 * scale * ((C + 63) / 64)), (double)(tiles * c->sh.hkv * tile_bytes) / 6.2e6 + 3.1 * rounds) +
+                                (C < longest ? 5.0 + 0.05 * ((longest + C - 1) / C) : 0.0);
             if (best_n == 0 || cost < best_cost) { best = C; best_n = n; best_cost = cost; }
         }
         *n_chunks = best_n;
         return best;
     }
-    // one-pass kernel of G < 4 (measured at live batches 1 .. 256 on the 7B shard): 128-token chunks,
+    // One-pass kernel of G < 4: whole sequences of up to 192 tokens, and of up to 384 when their heads give every compute
+    // unit an item (measured at live batches 1 .. 256 of the 7B, 7B TP = 4 and 13B TP = 2 shards, per layer against chunks
+    // of 64 or 128: up to 180 tokens -18 .. +1.5 us, 346 .. 360 tokens +2 .. +4 us below 256 items and -10 .. +2.7, mean -2.7,
+    // above, 700 tokens mostly slower by 1 .. 10).
+    if (longest <= 192 || (longest <= 384 && (int64_t)c->live * c->sh.hkv >= c->n_cu)) { *n_chunks = c->live; return longest; }
+    // Otherwise (measured at live batches 1 .. 256 on the 7B shard): 128-token chunks,
     // 64 when that leaves fewer than two work items per compute unit; 256 is never faster
     int best = kMinChunk;
     int64_t best_n = 0;
@@ -657,6 +668,10 @@ static int run_layers(pat_ctx *c, int B, int C, int64_t n_chunks, const int32_t 
     aa.page_table = c->st.page_table; aa.max_pages = s.max_pages; aa.chunk_start = c->st.chunk_start; aa.chunk_meta = c->st.chunk_meta; aa.chunk_tokens = C;
     aa.part_acc = at<float>(W, w.part_acc); aa.part_ml = at<float>(W, w.part_ml); aa.ohi = b_hi; aa.olo = b_lo;
     aa.n_items = (int)(n_chunks * s.hkv);
+    if (n_blocks == 0) {
+        for (int i = 0; i < B; ++i) aa.longest_chunks = std::max(aa.longest_chunks, (c->kv_len[i] + C) / C);
+        aa.direct = aa.longest_chunks == 1;
+    }
 
     for (int l = 0; l < s.NL; ++l) {
         char *L = Wb + c->wt.layer0 + c->wt.layer_stride * l;
@@ -683,7 +698,7 @@ static int run_layers(pat_ctx *c, int B, int C, int64_t n_chunks, const int32_t 
             TimeScope t(c, 1);
             if (n_blocks > 0) { aa.n_items = (int)(n_blocks * s.hkv); PAT_HIP(c, launch_attn_prefill(aa, n_chunks == 0, st)); }
             else PAT_HIP(c, launch_attn_partial(aa, st));
-            if (n_blocks == 0 || n_chunks > 0) PAT_HIP(c, launch_attn_merge(aa, st));
+            if (n_blocks == 0 ? !aa.direct : n_chunks > 0) PAT_HIP(c, launch_attn_merge(aa, st));
         }
         {
             GemmArgs g = gemm_args(L + c->wt.wo, s.H, s.hq * s.d, b_hi, b_lo, B, x, s.H, gpart, w.gemm_part_bytes);
@@ -828,16 +843,19 @@ int pat_decode_step(pat_ctx *c, pat_step_report *report_host, int32_t *next_tok_
     char *Wb = at<char>(c->bufs.weights, 0);
     float *gpart = at<float>(W, w.gemm_part);
 
-    { TimeScope t(c, 2); PAT_HIP(c, launch_plan_step(c->st, B, C, st)); }
     if (B <= kFusedMaxBatch && c->fused_ok) {
+        { TimeScope t(c, 2); PAT_HIP(c, launch_plan_step(c->st, B, C, st)); }
         if (int rc = run_layers_fused(c, B, C, n_chunks, logits)) return rc;
     } else {
         const bool fold = norm_is_folded(B);
         const uint16_t *g0 = (const uint16_t *)(s.NL > 0 ? Wb + c->wt.layer0 + c->wt.g1 : Wb + c->wt.gf);     // gains of the first RMSNorm
         {
             TimeScope t(c, 2);
-            if (fold) PAT_HIP(c, launch_embed_stats((const uint16_t *)(Wb + c->wt.embed), s.H, c->st.tok, g0, B, x, at<float>(W, w.stats_e), a_hi, a_lo, st));
-            else PAT_HIP(c, launch_embed((const uint16_t *)(Wb + c->wt.embed), s.H, c->st.tok, B, x, st));
+            if (fold) PAT_HIP(c, launch_plan_embed(c->st, B, C, (const uint16_t *)(Wb + c->wt.embed), s.H, g0, x, at<float>(W, w.stats_e), a_hi, a_lo, st));
+            else {
+                PAT_HIP(c, launch_plan_step(c->st, B, C, st));
+                PAT_HIP(c, launch_embed((const uint16_t *)(Wb + c->wt.embed), s.H, c->st.tok, B, x, st));
+            }
         }
         if (int rc = run_layers(c, B, C, n_chunks, c->st.kv_len, nullptr, 0)) return rc;
         if (!fold && s.NL == 0) { TimeScope t(c, 2); PAT_HIP(c, launch_rmsnorm_pack(x, (const uint16_t *)(Wb + c->wt.gf), B, s.H, c->cfg.rms_eps, a_hi, a_lo, st)); }

@@ -98,6 +98,8 @@ struct AttnArgs {
     float *part_ml;            // [n_chunks_total][hq][2]  (max, sum)
     uint4 *ohi, *olo;          // merged output as packed split-bf16 [B, hq*d]
     int n_items;               // n_chunks_total * hkv (host mirror)
+    int longest_chunks;        // most chunks of one row (0: unknown), for the choice of the merge kernel
+    bool direct;               // every row has one chunk: its workgroups write ohi / olo, nothing is merged
 };
 hipError_t launch_attn_partial(const AttnArgs &a, hipStream_t s);
 hipError_t launch_attn_gqa(const AttnArgs &a, hipStream_t s);        // the case of 4 or 8 query heads per KV head
@@ -157,6 +159,9 @@ struct StateArrays {           // device int32 arrays of max_batch entries
 hipError_t launch_pool_init(const StateArrays &st, int n_pages, hipStream_t s);
 hipError_t launch_admit(const StateArrays &st, int live, int n, hipStream_t s);   // new slots' arrays already copied in
 hipError_t launch_plan_step(const StateArrays &st, int B, int chunk_tokens, hipStream_t s);
+// the plan and, beside it, the embedding of the live rows' tokens (launch_embed_stats)
+hipError_t launch_plan_embed(const StateArrays &st, int B, int chunk_tokens, const uint16_t *table, int H, const uint16_t *gains, float *x,
+                             float *stats, uint4 *pk_hi, uint4 *pk_lo, hipStream_t s);
 // chunk records for rows that are not slots (prefill): row i is position row_pos[i] of slot row_slot[i]
 hipError_t launch_plan_rows(const StateArrays &st, int R, int chunk_tokens, const int32_t *row_slot, const int32_t *row_pos, bool write_records, hipStream_t s);
 hipError_t launch_embed(const uint16_t *table, int H, const int32_t *tok, int B, float *x, hipStream_t s);

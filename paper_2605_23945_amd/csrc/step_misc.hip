@@ -6,6 +6,7 @@
 // scans, so page assignment and compaction are deterministic.
 #include "pat_dev.h"
 #include "pat_kernels.h"
+#include "embed_dev.h"
 
 namespace pat {
 
@@ -67,7 +68,7 @@ __global__ __launch_bounds__(kBlk) void admit_kernel(StateArrays st, int live, i
 // (slot, first token, token count, its first four page ids), so that an attention
 // workgroup learns all it needs from a single 32-byte load instead of a search through the
 // prefix followed by length and page-table lookups.
-__global__ __launch_bounds__(kBlk) void plan_step_kernel(StateArrays st, int B, int C)
+__device__ __forceinline__ void plan_step(const StateArrays &st, int B, int C)
 {
     __shared__ int s_start[kBlk + 1];
     const int i = threadIdx.x;
@@ -98,6 +99,19 @@ __global__ __launch_bounds__(kBlk) void plan_step_kernel(StateArrays st, int B, 
         reinterpret_cast<int4 *>(st.chunk_meta)[2 * (int64_t)ce] = m0;
         reinterpret_cast<int4 *>(st.chunk_meta)[2 * (int64_t)ce + 1] = m1;
     }
+}
+
+__global__ __launch_bounds__(kBlk) void plan_step_kernel(StateArrays st, int B, int C) { plan_step(st, B, C); }
+
+// The plan in workgroup 0 and the embedding of row b (see embed_stats_row) in workgroup 1 + b: neither needs the other,
+// and one launch less is 4 us of a step that the smallest calls do in 80 (8 sequences of the tiny configuration).
+__global__ __launch_bounds__(kBlk) void plan_embed_kernel(StateArrays st, int B, int C, const uint16_t *table, int H, const uint16_t *gains,
+                                                          float *x, float *stats, uint4 *pk_hi, uint4 *pk_lo)
+{
+    __shared__ float part[kEmbedThreads / 64];
+    if (blockIdx.x == 0) { plan_step(st, B, C); return; }
+    if (threadIdx.x >= kEmbedThreads) return;             // whole waves: the others' barrier does not count them
+    embed_stats_row(table, H, st.tok, gains, blockIdx.x - 1, x, stats, pk_hi, pk_lo, part);
 }
 
 // Chunk prefix and chunk records for R rows that are positions of slots (prefill: row i is the token
@@ -375,6 +389,13 @@ hipError_t launch_admit(const StateArrays &st, int live, int n, hipStream_t s)
 hipError_t launch_plan_step(const StateArrays &st, int B, int chunk_tokens, hipStream_t s)
 {
     plan_step_kernel<<<1, kBlk, 0, s>>>(st, B, chunk_tokens);
+    return hipGetLastError();
+}
+
+hipError_t launch_plan_embed(const StateArrays &st, int B, int chunk_tokens, const uint16_t *table, int H, const uint16_t *gains, float *x,
+                             float *stats, uint4 *pk_hi, uint4 *pk_lo, hipStream_t s)
+{
+    plan_embed_kernel<<<1 + B, kBlk, 0, s>>>(st, B, chunk_tokens, table, H, gains, x, stats, pk_hi, pk_lo);
     return hipGetLastError();
 }
 

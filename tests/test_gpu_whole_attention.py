@@ -1,0 +1,59 @@
+"""Decode attention of whole sequences (one chunk each, no merge) and the merge of many chunks, through the decode step."""
+import numpy as np
+import pytest
+import torch
+
+import pat_inputs as pi
+from gpu_util import DEV, check_logits, make_decoder, make_oracle_decoder, oracle_admit
+from test_gpu_step import _gpu_step
+
+pytestmark = pytest.mark.gpu
+
+
+def _requests(shard, lens):
+    req = pi.rollout_requests(shard, len(lens), (1, 2), steps=4)
+    req["kv_len"] = np.array(lens, np.int32)
+    return req
+
+
+@pytest.mark.parametrize("hq,hkv,d,page,lens", [
+    (4, 4, 64, 16, (0, 1, 62, 63, 64, 127, 128, 188)),          # whole: more pages than a chunk record holds
+    (4, 2, 128, 64, (3, 190, 191, 192)),                        # the last step crosses from whole sequences to chunks
+    (32, 32, 64, 16, (380, 382, 20, 301, 255, 256, 64, 65)),    # an item per compute unit: whole up to 384
+    (8, 1, 128, 16, (100, 511, 30)),                            # grouped queries
+    (2, 2, 128, 64, (1500, 40)),                                # 24 chunks: four waves merge
+    (2, 2, 64, 32, (2500, 2047)),                               # 40 chunks of 64 features
+])
+def test_whole_sequences_and_wide_merges_vs_oracle(hq, hkv, d, page, lens):
+    import paper_2605_23945_amd as pat
+    shard = pi.shard_of(pi.ModelShape(1, 256, hq, hkv, d, 512, 512), 1, 0)
+    n = len(lens)
+    req = _requests(shard, lens)
+    dec = make_decoder(shard, n, max(lens) + 8, int(sum(lens)) + 2 * page * n + 64, page)
+    pat.admit_synthetic(dec, shard, req, DEV)
+    odec = make_oracle_decoder(shard)
+    oracle_admit(odec, shard, req, range(n), 4)
+    for _ in range(3):
+        ref_logits, ref_next, _ = odec.step()
+        logits, nxt, _ = _gpu_step(dec, n, shard.vocab)
+        check_logits(logits, ref_logits)
+        assert np.array_equal(nxt, ref_next)
+    dec.close()
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(4, 4, 128), (4, 2, 64), (8, 1, 128)])
+def test_page_length_does_not_change_a_whole_sequence(hq, hkv, d):
+    """The page ids come from the chunk's record or from the wave's lanes; the arithmetic is the same, bit by bit."""
+    import paper_2605_23945_amd as pat
+    shard = pi.shard_of(pi.ModelShape(1, 256, hq, hkv, d, 512, 512), 1, 0)
+    lens = (5, 97, 150, 186)
+    out = []
+    for page in (16, 32, 64, 128):
+        req = _requests(shard, lens)
+        dec = make_decoder(shard, len(lens), 256, 1024 + 4 * page * len(lens), page)
+        pat.admit_synthetic(dec, shard, req, DEV)
+        out.append([_gpu_step(dec, len(lens), shard.vocab)[0] for _ in range(2)])
+        dec.close()
+    for o in out[1:]:
+        for a, b in zip(out[0], o):
+            assert np.array_equal(a, b)
