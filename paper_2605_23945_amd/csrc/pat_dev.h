@@ -50,16 +50,21 @@ __device__ __host__ __forceinline__ int64_t packed_elem_offset(int row, int k, i
 // lds_off .. lds_off + 1023 in lane order; _stream marks the data as read once.  Inline assembly because the compiler,
 // told of such a load, waits for ALL outstanding loads before the next use of any register loaded from memory; unknown
 // to it, the load only makes its counted waits a little stricter.  The caller waits for the data by hand
-// (s_waitcnt vmcnt), and drains them before the workgroup ends.
+// (s_waitcnt vmcnt), and drains them before the workgroup ends.  m0 (the LDS base of such a load) is named as overwritten:
+// the compiler keeps its own values there, for loads to LDS that it issues itself and for indexed register access (its
+// remark that the register is a reserved one is what is meant here).
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ uint32_t lds_offset(const void *p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p; }
 __device__ __forceinline__ void load_to_lds(const void *base, uint32_t lane_off, uint32_t lds_off)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_off), "v"(lane_off), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_off), "v"(lane_off), "s"(base) : "memory", "m0");
 }
 __device__ __forceinline__ void load_to_lds_stream(const void *base, uint32_t lane_off, uint32_t lds_off)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_off), "v"(lane_off), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_off), "v"(lane_off), "s"(base) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 // Agent-scope (write-through) stores and loads: data that another workgroup of the SAME launch reads after a
 // device-wide barrier is written with these, so that no cache-wide write-back is needed; the reader uses
