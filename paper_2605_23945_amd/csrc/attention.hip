@@ -253,10 +253,10 @@ __global__ __launch_bounds__(kMergeWaves * 64) void attn_merge_wide_kernel(AttnA
     }
     __syncthreads();
     if (threadIdx.x >= LPT) return;
-    float Mc = M;                                           // wave 0 holds the first chunk: finite
+    float Mc = M;
 #pragma unroll
     for (int w = 1; w < kMergeWaves; ++w) Mc = fmaxf(Mc, st[w][lane][8]);
-    const float s0 = expf(M - Mc);
+    const float s0 = M == -INFINITY ? 0.f : expf(M - Mc);
     den *= s0;
 #pragma unroll
     for (int j = 0; j < 8; ++j) o[j] *= s0;

@@ -134,16 +134,17 @@ __global__ __launch_bounds__(W * 64) void attn_gqa_kernel(AttnArgs a)
         for (int j = 1; j < 8; ++j) mt = fmaxf(mt, p[j]);
         mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
         mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
-        const float Mn = fmaxf(M, mt);                         // finite: every tile holds at least one key of the chunk
+        const float Mn = fmaxf(M, mt);
         if (__any(Mn > M)) {                                   // some head of the wave has a new maximum
-            const float corr = __builtin_amdgcn_exp2f(M - Mn); // exp2(-inf) = 0 on the wave's first keys
+            const float corr = M == Mn ? 1.f : __builtin_amdgcn_exp2f(M - Mn);     // exp2(-inf) = 0 on the wave's first keys
             M = Mn;
             den *= corr;
 #pragma unroll
             for (int f = 0; f < FT; ++f) { o[f][0] *= corr; o[f][1] *= corr; o[f][2] *= corr; o[f][3] *= corr; }
         }
+        const float m0_ = M == -INFINITY ? 0.f : M;            // a head whose scores so far all overflowed to -inf: p = 0
 #pragma unroll
-        for (int j = 0; j < 8; ++j) { p[j] = __builtin_amdgcn_exp2f(p[j] - M); den += p[j]; }
+        for (int j = 0; j < 8; ++j) { p[j] = __builtin_amdgcn_exp2f(p[j] - m0_); den += p[j]; }
         u32x4_t ph, pm, pl;
         split3_bf16(p, ph, pm, pl);
         // newer than this tile's V: the next tile, and the K half requested above
@@ -186,7 +187,7 @@ __global__ __launch_bounds__(W * 64) void attn_gqa_kernel(AttnArgs a)
         float l = 0.f;
 #pragma unroll
         for (int w = 0; w < W; ++w) {
-            const float sw = __builtin_amdgcn_exp2f(mw[w] - Mc);        // a wave without tiles: exp2(-inf) = 0
+            const float sw = mw[w] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw[w] - Mc);     // a wave without tiles, or whose scores all are -inf
             const float4 t = reinterpret_cast<const float4 *>(lds + w * 4 * kHalf)[e];
             v.x = fmaf(t.x, sw, v.x); v.y = fmaf(t.y, sw, v.y); v.z = fmaf(t.z, sw, v.z); v.w = fmaf(t.w, sw, v.w);
             l = fmaf(wml[w][g][1], sw, l);

@@ -49,6 +49,7 @@ __device__ __forceinline__ void attn_merge_fold(const AttnArgs &a, int ce0, int 
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if (c0 + i * step >= nch) break;
+            if (m[i] == -INFINITY) continue;                           // all scores of the chunk are -inf: no weight (l = 0)
             const float Mn = fmaxf(M, m[i]);
             const float so = expf(M - Mn), sn = expf(m[i] - Mn);       // M = -inf on the first chunk: so = 0
             den = den * so + l[i] * sn;
