@@ -97,7 +97,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a)
     const int tiles = (last - t0) / kTile + 1;
     for (int t = 0; t < tiles; ++t) {
         const int buf = t & 1, key0 = t0 + t * kTile;
-        asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");    // tile t is in LDS, every wave is done with tile t - 1
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");    // tile t is in LDS, every wave has read tile t - 1
         if (t + 1 < tiles) { request(key0 + kTile, buf ^ 1); look_up(key0 + 2 * kTile); }
         if (key0 > wave_last) continue;                                  // nothing for this wave's rows (it keeps loading its share)
         const char *kt = reinterpret_cast<const char *>(kv[buf][0]), *vt = reinterpret_cast<const char *>(kv[buf][1]);
@@ -160,6 +160,37 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a)
     }
     den += __shfl_xor(den, 16, 64);
     den += __shfl_xor(den, 32, 64);
+
+    // A row's products with the keys it does not see (and the zero terms of p) are products with zero: not a number where
+    // such a V is infinite or not a number itself.  Rows that met one are summed again, one key after the other and only
+    // those of some weight, so that a position never depends on a later one.
+    bool bad = false;
+#pragma unroll
+    for (int f = 0; f < FT; ++f) bad |= o[f][0] != o[f][0] || o[f][1] != o[f][1] || o[f][2] != o[f][2] || o[f][3] != o[f][3];
+    if (__any(bad && live)) {
+        const float scale = rsqrtf((float)D) * 1.44269504f, top = M == -INFINITY ? 0.f : M;
+        const float *qp = a.qkv + (int64_t)(row0 + min(pi, n - 1)) * a.ldq + head * D;
+        const int end = min(wave_last, last);
+        den = 0.f;
+#pragma unroll
+        for (int f = 0; f < FT; ++f) o[f] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int key = t0; key <= end; ++key) {
+            const int64_t at = pt[key >> lgP] * page_bytes + (int64_t)(key & (P - 1)) * (D * 2);
+            const uint16_t *kr = reinterpret_cast<const uint16_t *>(pool[0] + at), *vr = reinterpret_cast<const uint16_t *>(pool[1] + at);
+            float dot = 0.f;
+#pragma unroll 1
+            for (int e = 0; e < D; ++e) dot = fmaf(qp[e] * scale, bf16_to_f32(kr[e]), dot);
+            const float w = key <= pos ? __builtin_amdgcn_exp2f(dot - top) : 0.f;
+            den += w;
+            if (w != 0.f) {
+#pragma unroll
+                for (int f = 0; f < FT; ++f)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) o[f][j] = fmaf(w, bf16_to_f32(vr[f * 16 + g4 * 4 + j]), o[f][j]);
+            }
+        }
+    }
     if (!live || pos < t0) return;                                       // the row takes no part in this chunk (no barrier follows)
     if (DIRECT) {
         const float inv = 1.0f / den;

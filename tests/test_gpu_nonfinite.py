@@ -1,10 +1,10 @@
-"""Cached values at and beyond the range of fp32 arithmetic: scores that overflow."""
+"""Cached values at and beyond the range of fp32 arithmetic: scores that overflow, positions whose K/V are not numbers."""
 import numpy as np
 import pytest
 import torch
 
 import pat_inputs as pi
-from gpu_util import DEV, check_logits
+from gpu_util import DEV, bf16_close, check_logits
 from oracle import Oracle, OracleDecoder, bits
 
 pytestmark = pytest.mark.gpu
@@ -52,4 +52,37 @@ def test_keys_whose_scores_overflow_have_no_weight(hq, hkv, d, lens, first, n_ba
     dec.pat_decode_step(True, nxt, logits)
     check_logits(logits.cpu().numpy(), ref)
     assert np.array_equal(nxt.cpu().numpy(), ref_next)
+    dec.close()
+
+
+@pytest.mark.parametrize("hq,hkv,d,length,at,width", [(2, 2, 128, 70, 20, 128), (8, 1, 64, 40, 6, 64), (4, 2, 64, 150, 140, 256),
+                                                      (8, 1, 64, 1300, 1293, 256)])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_a_position_that_is_not_a_number_leaves_the_earlier_ones_alone(hq, hkv, d, length, at, width, value):
+    """Prefill is causal: the states of the positions before `at` do not depend on its token, whose embedding is `value`."""
+    import paper_2605_23945_amd as pat
+    shard = pi.shard_of(pi.ModelShape(2, 256, hq, hkv, d, 256, 256), 1, 0)
+    dec = pat.Decoder(pat.make_cfg(shard, width, length + 4, length + 128, 64), DEV)
+    for l in range(2):
+        dec.pat_load_layer(l, pi.layer_weights(shard, l, device=DEV))
+    embed = pi.embedding_table(shard, device=DEV).clone()
+    embed[255] = value
+    dec.pat_load_final(dict(pi.final_weights(shard, device=DEV), embed=embed))
+    tokens = pi.prompt_tokens(shard, 0, length) % 255
+    out = []
+    for bad in (False, True):
+        t = np.array(tokens, np.int32)
+        if bad:
+            t[at] = 255
+        dec.pat_decode_reset()
+        dec.pat_decode_admit([0], [1], [length], [4])
+        dec.pat_prefill([0], t)
+        out.append([[bits(a.cpu()) for a in dec.pat_kv_read(0, l, length)] for l in range(2)])
+    for l in range(2):
+        for kv in range(2):
+            good, got = out[0][l][kv], out[1][l][kv]
+            assert np.all((got[at:].view(np.uint16) & 0x7F80) == 0x7F80) or l == 0     # from `at` on nothing is a number
+            # two orders of fp32 sums: the elements near a rounding boundary differ by a bf16 step
+            same, close = bf16_close(got[:at], good[:at])
+            assert close and same > 0.97, (l, kv, same)
     dec.close()
