@@ -256,13 +256,13 @@ __global__ __launch_bounds__(kMergeWaves * 64) void attn_merge_wide_kernel(AttnA
     float Mc = M;
 #pragma unroll
     for (int w = 1; w < kMergeWaves; ++w) Mc = fmaxf(Mc, st[w][lane][8]);
-    const float s0 = M == -INFINITY ? 0.f : expf(M - Mc);
+    const float s0 = M == -INFINITY ? 0.f : expf((M - Mc) * a.ml_unit);
     den *= s0;
 #pragma unroll
     for (int j = 0; j < 8; ++j) o[j] *= s0;
 #pragma unroll
     for (int w = 1; w < kMergeWaves; ++w) {
-        const float sw = st[w][lane][8] == -INFINITY ? 0.f : expf(st[w][lane][8] - Mc);
+        const float sw = st[w][lane][8] == -INFINITY ? 0.f : expf((st[w][lane][8] - Mc) * a.ml_unit);
         den += st[w][lane][9] * sw;
 #pragma unroll
         for (int j = 0; j < 8; ++j) o[j] += st[w][lane][j] * sw;

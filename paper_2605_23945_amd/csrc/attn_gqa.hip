@@ -205,7 +205,7 @@ __global__ __launch_bounds__(W * 64) void attn_gqa_kernel(AttnArgs a)
         }
         const int64_t row = (int64_t)ce * a.hq + h * G + g;
         reinterpret_cast<float4 *>(a.part_acc + row * D)[e % (D / 4)] = v;
-        if (e % (D / 4) == 0) *reinterpret_cast<float2 *>(a.part_ml + row * 2) = make_float2(Mc * 0.69314718f, l);     // the merge works in natural units
+        if (e % (D / 4) == 0) *reinterpret_cast<float2 *>(a.part_ml + row * 2) = make_float2(Mc, l);
     }
 }
 

@@ -23,7 +23,8 @@ __device__ __forceinline__ void attn_write_operand(const AttnArgs &a, int b, int
 // The partials of (row, query head) folded by wave w of W: lanes = D/8 feature segments x 64/(D/8) chunk lanes.  Chunk
 // lane cl of wave w folds the chunks c = w CL + cl, + W CL, ... in increasing order, then the chunk lanes are combined
 // pairwise in a fixed tree (online-softmax identity), so the result is run-to-run identical.  Lanes with cl = 0 hold it
-// (M = -inf, den = 0 where the wave has no chunk).
+// (M = -inf, den = 0 where the wave has no chunk).  The maxima stay in the unit that the chunk's weights were formed in:
+// converted one by one they would be rounded, and a chunk's weight would be off by 2^-24 of its maximum.
 template <int D>
 __device__ __forceinline__ void attn_merge_fold(const AttnArgs &a, int ce0, int nch, int head, int lane, int w, int W, float &M, float &den, float (&o)[8])
 {
@@ -51,7 +52,7 @@ __device__ __forceinline__ void attn_merge_fold(const AttnArgs &a, int ce0, int 
             if (c0 + i * step >= nch) break;
             if (m[i] == -INFINITY) continue;                           // all scores of the chunk are -inf: no weight (l = 0)
             const float Mn = fmaxf(M, m[i]);
-            const float so = expf(M - Mn), sn = expf(m[i] - Mn);       // M = -inf on the first chunk: so = 0
+            const float so = expf((M - Mn) * a.ml_unit), sn = expf((m[i] - Mn) * a.ml_unit);       // M = -inf on the first chunk: so = 0
             den = den * so + l[i] * sn;
             o[0] = o[0] * so + p0[i].x * sn; o[1] = o[1] * so + p0[i].y * sn; o[2] = o[2] * so + p0[i].z * sn; o[3] = o[3] * so + p0[i].w * sn;
             o[4] = o[4] * so + p1[i].x * sn; o[5] = o[5] * so + p1[i].y * sn; o[6] = o[6] * so + p1[i].z * sn; o[7] = o[7] * so + p1[i].w * sn;
@@ -63,7 +64,7 @@ __device__ __forceinline__ void attn_merge_fold(const AttnArgs &a, int ce0, int 
         const float M2 = __shfl_xor(M, off, 64), den2 = __shfl_xor(den, off, 64);
         const float Mn = fmaxf(M, M2);
         // a chunk lane that saw no chunk carries M = -inf, den = 0: its weight is exp(-inf) = 0
-        const float s1 = (M == -INFINITY) ? 0.f : expf(M - Mn), s2 = (M2 == -INFINITY) ? 0.f : expf(M2 - Mn);
+        const float s1 = (M == -INFINITY) ? 0.f : expf((M - Mn) * a.ml_unit), s2 = (M2 == -INFINITY) ? 0.f : expf((M2 - Mn) * a.ml_unit);
         // the lower lane's term is added first on both sides, so both lanes of a pair hold identical sums
         const bool low = (lane & off) == 0;
         den = low ? den * s1 + den2 * s2 : den2 * s2 + den * s1;

@@ -209,7 +209,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a)
         float *acc = a.part_acc + (ci * a.hq + head) * D + g4 * 4;
 #pragma unroll
         for (int f = 0; f < FT; ++f) *reinterpret_cast<float4 *>(acc + f * 16) = make_float4(o[f][0], o[f][1], o[f][2], o[f][3]);
-        if (g4 == 0) *reinterpret_cast<float2 *>(a.part_ml + (ci * a.hq + head) * 2) = make_float2(M * 0.69314718f, den);      // the merge works in natural units
+        if (g4 == 0) *reinterpret_cast<float2 *>(a.part_ml + (ci * a.hq + head) * 2) = make_float2(M, den);
     }
 }
 

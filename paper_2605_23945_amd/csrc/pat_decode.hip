@@ -667,6 +667,7 @@ static int run_layers(pat_ctx *c, int B, int C, int64_t n_chunks, const int32_t 
     aa.kv = c->kv; aa.qkv = qkv; aa.ldq = s.qkv_rows; aa.hq = s.hq; aa.B = B; aa.kv_len = pos; aa.row_slot = row_slot;
     aa.page_table = c->st.page_table; aa.max_pages = s.max_pages; aa.chunk_start = c->st.chunk_start; aa.chunk_meta = c->st.chunk_meta; aa.chunk_tokens = C;
     aa.part_acc = at<float>(W, w.part_acc); aa.part_ml = at<float>(W, w.part_ml); aa.ohi = b_hi; aa.olo = b_lo;
+    aa.ml_unit = n_blocks > 0 ? kLn2 : attn_decode_unit(s.hq / s.hkv);
     aa.n_items = (int)(n_chunks * s.hkv);
     if (n_blocks == 0) {
         for (int i = 0; i < B; ++i) aa.longest_chunks = std::max(aa.longest_chunks, (c->kv_len[i] + C) / C);
@@ -738,6 +739,7 @@ static int run_layers_fused(pat_ctx *c, int B, int C, int64_t n_chunks, float *l
     aa.kv = c->kv; aa.qkv = qkv; aa.ldq = s.qkv_rows; aa.hq = s.hq; aa.B = B; aa.kv_len = c->st.kv_len; aa.row_slot = nullptr;
     aa.page_table = c->st.page_table; aa.max_pages = s.max_pages; aa.chunk_start = c->st.chunk_start; aa.chunk_meta = c->st.chunk_meta; aa.chunk_tokens = C;
     aa.part_acc = at<float>(W, w.part_acc); aa.part_ml = at<float>(W, w.part_ml);
+    aa.ml_unit = attn_decode_unit(s.hq / s.hkv);
     aa.ohi = at<uint4>(W, w.o_hi); aa.olo = at<uint4>(W, w.o_lo);
     aa.n_items = (int)(n_chunks * s.hkv);
 

@@ -96,11 +96,14 @@ struct AttnArgs {
     int chunk_tokens;
     float *part_acc;           // [n_chunks_total][hq][d]
     float *part_ml;            // [n_chunks_total][hq][2]  (max, sum)
+    float ml_unit;             // what one unit of that max is in the exponent: 1, or ln 2 where the scores are in units of log2
     uint4 *ohi, *olo;          // merged output as packed split-bf16 [B, hq*d]
     int n_items;               // n_chunks_total * hkv (host mirror)
     int longest_chunks;        // most chunks of one row (0: unknown), for the choice of the merge kernel
     bool direct;               // every row has one chunk: its workgroups write ohi / olo, nothing is merged
 };
+constexpr float kLn2 = 0.69314718f;
+inline float attn_decode_unit(int G) { return G >= 4 ? kLn2 : 1.f; }      // ml_unit of launch_attn_partial, by query heads per KV head; launch_attn_prefill: kLn2
 hipError_t launch_attn_partial(const AttnArgs &a, hipStream_t s);
 hipError_t launch_attn_gqa(const AttnArgs &a, hipStream_t s);        // the case of 4 or 8 query heads per KV head
 int attn_prefill_block(int G);            // positions per block record

@@ -57,3 +57,38 @@ def test_page_length_does_not_change_a_whole_sequence(hq, hkv, d):
     for o in out[1:]:
         for a, b in zip(out[0], o):
             assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(8, 1, 128), (4, 1, 64)])
+def test_chunks_of_large_scores_merge_as_one(hq, hkv, d):
+    """Scores of some thousands: a sequence that is one chunk beside a short one and several beside a long one gives the
+    same logits.  The two ways share every score and weight; what differs is the rounding of a few sums and factors near 1
+    (2^-24 each) and, through it, of the operand's low terms (2^-17 of an element, a few of them: below 2^-17 of the scale)."""
+    import paper_2605_23945_amd as pat
+    H = 256
+    shard = pi.shard_of(pi.ModelShape(1, H, hq, hkv, d, 256, 512), 1, 0)
+    tok = 7
+    slow = slice(d // 2 - d // 16, d // 2)
+    w = pi.layer_weights(shard, 0, device=DEV)
+    embed = pi.embedding_table(shard, device=DEV)
+    q = w["wqkv"][: hq * d].view(hq, d, H).clone()
+    q[:, slow] = (torch.sign(embed[tok].float() * w["g1"].float()) * 0.5).to(torch.bfloat16)
+    w["wqkv"][: hq * d] = q.view(hq * d, H)
+    out = []
+    for other in (100, 3000):
+        lens = (400, other)
+        dec = pat.Decoder(pat.make_cfg(shard, 2, 3010, 3600, 64), DEV)
+        dec.pat_load_layer(0, w)
+        dec.pat_load_final(dict(pi.final_weights(shard, device=DEV), embed=embed))
+        dec.pat_decode_admit([0, 1], [tok, tok], lens, [4, 4])
+        for i, L in enumerate(lens):
+            k, v = (t.to(DEV).clone() for t in pi.kv_prefix(shard, i, 0, L))
+            k[:, :, slow] = 20.0
+            dec.pat_kv_write(i, 0, k, v)
+        logits = torch.empty(2, shard.vocab, device=DEV)
+        dec.pat_decode_step(True, torch.empty(2, dtype=torch.int32, device=DEV), logits)
+        out.append(logits[0].double().cpu().numpy())
+        dec.close()
+    err = float(np.max(np.abs(out[0] - out[1])) / out[0].std())
+    print("merge against one chunk:", err, flush=True)
+    assert err <= 2.0 ** -17
