@@ -1,30 +1,38 @@
-// Projections of a live batch of 33..256 rows, where the batch is a real dense dimension: the weights are streamed
-// ONCE for the whole batch, by a kernel that keeps both operand streams several k-steps ahead of the matrix cores.
+// Projections of more than 32 rows, where the batch is a real dense dimension: a kernel that streams the weights past up
+// to 128 rows at once and keeps both operand streams several k-steps ahead of the matrix cores.
 //
-// A workgroup of four waves (one per SIMD) owns RA row tiles x ALL batch tiles (4 RB) x a K slice; wave w holds the
-// accumulators of all RA row tiles against its own RB batch tiles.  So a batch fragment is needed by one wave only and
+// A workgroup of four waves (one per SIMD) owns RA row tiles x ALL 4 RB batch tiles of a row group x a K slice; wave w holds
+// the accumulators of all RA row tiles against its own RB batch tiles.  So a batch fragment is needed by one wave only and
 // goes straight from memory to its registers (a ring of XD + 1 k-steps), while the weight fragments, needed by all four
 // waves, go straight from memory to LDS (`global_load_lds`, 1 KiB per instruction, a ring of WS k-steps) without
-// touching a register.  One workgroup barrier per k-step; every row tile's step is one LDS read, up to one request and
-// 2 RB matrix instructions (high and low halves), so requests, LDS reads and products interleave evenly.
+// touching a register.  One workgroup barrier per k-step; every row tile's step is one LDS read, its share of the k-step's
+// requests and 2 RB matrix instructions (high and low halves), so requests, LDS reads and products interleave evenly.
+//
+// Sums: every XD + 1 k-steps the accumulators are added to a second set and start again from zero.  One chain over all of K
+// rounds 2 K / 32 times at the size of the result; against float64 sums of the same operands that gave 5.7e-7 (2-norm,
+// K = 4096), 8.1e-7 (K = 8192); in blocks it is 1.4e-7 .. 1.9e-7 at every K up to 11008, no more than the K slices of the
+// kernel it replaces gave (1.4e-7 .. 4.0e-7).  The second set is why a wave takes at most two batch tiles: 12 x 3, 8 x 4 and
+// 12 x 4 tiles have no registers for it.  The additions cost 1-3 % of a launch.
+//
+// More than 128 rows are cut into NG equal groups in ONE launch: the groups of a row range are neighbours on one XCD and
+// share its weight stream in L2.  That is faster than one group of up to 256 rows with one set of sums (22016 x 4096 at 256
+// rows 85 us against 101, 8192 x 1024 16 against 31) but for wide projections of 129..192 rows (22016 x 4096 at 130 rows 81
+// against 72) and of passes of about 1000 (1024 rows: 325 against 310; 7168 x 8192 213 against 191).
 //
 // What bounds it: up to 128 rows the weight stream from HBM (the per-k-step requests of all workgroups in flight,
 // up to 130 KB per compute unit, are what hides its latency); at 256 rows the chip's power limit (random operands run
 // 25-40 % slower than all-zero ones at the same instruction stream).  Measured against the kernel it replaces (batch
 // fragments staged through registers into LDS, two k-steps ahead; same box, reduction included), microseconds:
-//     rows          60            101           180           256
-//     22016 x 4096  49.4 -> 42.0  69.9 -> 51.4  82.3 -> 69.0  107  -> 86
-//     5120 x 6912   26.3 -> 23.0  37.5 -> 30.4  44.1 -> 36.4  56.5 -> 42.0
-//     1280 x 8192   22.0 -> 14.0  30.8 -> 17.5  34.1 -> 23.1  38.3 -> 27.3
-//     4096 x 1024   13.7 -> 10.0  17.2 -> 12.5  20.4 -> 16.5  22.5 -> 21.1
-//
-// More than 256 rows (prefill passes, large live batches) are cut into NG equal groups of up to 256 rows in ONE launch:
-// the groups of a row range are neighbours on one XCD and share its weight stream in L2, and the grid they fill is one
-// that K need not be split for (8192 x 3584 at 1024 rows: four launches of 256 rows took 172 us, one takes 80).
+//     rows          60            101           180           256           1024
+//     22016 x 4096  52.1 -> 46.1  73.2 -> 57.4  88.4 -> 82.5  112  -> 84.6  449  -> 325
+//     5120 x 6912   28.9 -> 27.5  40.6 -> 37.0  47.7 -> 42.2  59.4 -> 47.3  230  -> 128
+//     1280 x 8192   21.9 -> 16.8  31.0 -> 19.6  33.5 -> 24.9  38.7 -> 28.2  147  -> 57.8
+//     4096 x 1024   13.4 -> 12.9  17.8 -> 12.9  21.0 -> 13.2  24.1 -> 13.6  88.4 -> 23.9
 //
 // K can be split across workgroups (`plan_wide`); the slices' partial sums go to a scratch tensor and a reduction
 // kernel adds them in slice order and runs the epilogue, so results never depend on timing.
 #include <algorithm>
+#include <type_traits>
 #include "gemm_dev.h"
 
 namespace pat {
@@ -32,7 +40,7 @@ namespace pat {
 namespace {
 
 // Depth of the two rings per tile shape: batch fragments XD k-steps ahead in registers (RA RB 4 accumulator registers
-// beside them), weights WS - 1 k-steps ahead in LDS.  Loads complete in order, so a wait for a batch fragment also waits
+// and as many of the second sums beside them), weights WS - 1 k-steps ahead in LDS.  Loads complete in order, so a wait for a batch fragment also waits
 // for the weights requested before it: XD bounds how much of the weight stream is in flight.
 template <int RA, int RB> struct WideRings;
 template <> struct WideRings<4, 1> { static constexpr int XD = 7, WS = 14; };
@@ -41,13 +49,6 @@ template <> struct WideRings<12, 1> { static constexpr int XD = 7, WS = 11; };
 template <> struct WideRings<4, 2> { static constexpr int XD = 7, WS = 12; };
 template <> struct WideRings<8, 2> { static constexpr int XD = 7, WS = 11; };
 template <> struct WideRings<12, 2> { static constexpr int XD = 5, WS = 9; };
-template <> struct WideRings<4, 3> { static constexpr int XD = 5, WS = 10; };
-template <> struct WideRings<8, 3> { static constexpr int XD = 5, WS = 8; };
-template <> struct WideRings<12, 3> { static constexpr int XD = 5, WS = 8; };
-template <> struct WideRings<4, 4> { static constexpr int XD = 5, WS = 9; };
-template <> struct WideRings<8, 4> { static constexpr int XD = 5, WS = 8; };
-template <> struct WideRings<12, 4> { static constexpr int XD = 4, WS = 7; };
-
 template <int RA, int RB> constexpr int wide_lds_bytes() { return WideRings<RA, RB>::WS * RA * 1024; }
 
 // MODE kPartial: the tile's sums go to a.part[kb][b][n_tiles * 16] (kb = K slice); otherwise (one slice) the epilogue runs here.
@@ -86,11 +87,11 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(GemmArgs a)
     auto request_w = [&](int t, int i) { load_to_lds_stream(wsrc[i] + min(t, n - 1) * 64, lane * 16, lds0 + (s_req * RA + wave * CW + i) * 1024); };
     auto request_x = [&](int t, int i) -> u32x4_t { return *(xsrc[i] + min(t, n - 1) * 64 + lane); };
 
-    floatx4_t acc[RA][RB];
+    floatx4_t acc[RA][RB], sum[RA][RB];
 #pragma unroll
     for (int ra = 0; ra < RA; ++ra)
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) acc[ra][rb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+        for (int rb = 0; rb < RB; ++rb) acc[ra][rb] = sum[ra][rb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
     u32x4_t x[U][CX], w[PF];
     // the requests of the k-steps -DA .. -1, in the order the loop would have issued them
 #pragma unroll
@@ -111,7 +112,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(GemmArgs a)
 
     // One k-step.  The wait covers this wave's part of W(t + 1) (its requests are followed by those of DA - 2 whole
     // k-steps); after the barrier all parts are in LDS and every wave is done with the slot of W(t - 1), which takes W(t + DA).
-    auto step = [&](int t, const u32x4_t (&xc)[CX], u32x4_t (&xn)[CX]) {
+    auto step = [&](int t, const u32x4_t (&xc)[CX], u32x4_t (&xn)[CX], auto fold) {
         asm volatile("s_waitcnt vmcnt(%c0)\n\ts_barrier" ::"i"((DA - 2) * PER) : "memory");
         const int s_nxt = s_cur + 1 == WS ? 0 : s_cur + 1;
         const u32x4_t *cur = wring + s_cur * RA * 64 + lane, *nxt = wring + s_nxt * RA * 64 + lane;
@@ -120,6 +121,10 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(GemmArgs a)
 #pragma unroll
             for (int v = (r * PER) / RA; v < ((r + 1) * PER) / RA; ++v) { if (v < CW) request_w(t + DA, v); else xn[v - CW] = request_x(t + XD, v - CW); }
             w[(r + PF - 1) % PF] = r + PF - 1 < RA ? cur[(r + PF - 1) * 64] : nxt[(r + PF - 1 - RA) * 64];
+            if constexpr (decltype(fold)::value) {
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) { sum[r][rb] += acc[r][rb]; acc[r][rb] = floatx4_t{0.f, 0.f, 0.f, 0.f}; }
+            }
 #pragma unroll
             for (int i = 0; i < CX; ++i) acc[r][i % RB] = mfma16(w[r % PF], xc[i], acc[r][i % RB]);
             __builtin_amdgcn_sched_barrier(0);                  // keeps the interleaving, and every LDS read of a k-step before the next barrier
@@ -128,12 +133,14 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(GemmArgs a)
     };
     int t = 0;
     for (; t + U <= n; t += U) {
+        step(t, x[0], x[XD % U], std::true_type{});
 #pragma unroll
-        for (int u = 0; u < U; ++u) step(t + u, x[u], x[(u + XD) % U]);
+        for (int u = 1; u < U; ++u) step(t + u, x[u], x[(u + XD) % U], std::false_type{});
     }
+    if (t < n) step(t, x[0], x[XD % U], std::true_type{});
 #pragma unroll
-    for (int u = 0; u < U - 1; ++u)
-        if (t + u < n) step(t + u, x[u], x[(u + XD) % U]);
+    for (int u = 1; u < U - 1; ++u)
+        if (t + u < n) step(t + u, x[u], x[(u + XD) % U], std::false_type{});
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // no write to LDS may be in flight when the workgroup ends
 
     // the epilogue's addresses are derived from a copy of the lane index that the compiler cannot see through:
@@ -146,7 +153,8 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(GemmArgs a)
         if (rt >= rt1) continue;
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            const float4 v = make_float4(acc[ra][rb][0], acc[ra][rb][1], acc[ra][rb][2], acc[ra][rb][3]);
+            const floatx4_t s = sum[ra][rb] + acc[ra][rb];
+            const float4 v = make_float4(s[0], s[1], s[2], s[3]);
             const int bl = (wave * RB + rb) * 16 + (lane_e & 15), b = bl < nb ? b0 + bl : a.B, quad = lane_e >> 4;     // b == a.B: not stored
             if (MODE == kPartial) {
                 if (b < a.B) *reinterpret_cast<float4 *>(a.part + ((int64_t)kb * a.B + b) * ((int64_t)a.n_tiles * 16) + rt * 16 + quad * 4) = v;
@@ -314,41 +322,39 @@ int max_slices(int n_tiles, int KS, int n_cu)
 
 hipError_t gemm_wide_prepare_device()
 {
-    hipError_t e = wide_set_lds_limits<1>();
-    if (e == hipSuccess) e = wide_set_lds_limits<2>();
-    if (e == hipSuccess) e = wide_set_lds_limits<3>();
-    if (e == hipSuccess) e = wide_set_lds_limits<4>();
-    return e;
+    const hipError_t e = wide_set_lds_limits<1>();
+    return e == hipSuccess ? wide_set_lds_limits<2>() : e;
 }
 
-// Row tiles per workgroup (4, 8, 12) and K slices, by a cost model fitted to 122 measured launches (40 shapes of
-// 1280..22016 features, K 1024..11008, 60..256 rows; rms error 8 %, and on all but three shapes the cut it picks was the
-// best or within 3 % of the best measured): a launch takes 7.5 us plus its k-steps, each the longest of the matrix
-// products (0.020 us per tile pair), the operand fetch (0.014 us per KiB and workgroup) and the weight stream (0.050 us
-// per KiB and workgroup with all 256 busy), plus 0.48 us per MB of partial sums.  Few row tiles per workgroup
-// and few slices suit narrow projections (1280 x 8192, 256 rows: 4 tiles 27.3 us, 8 tiles 33.6), many tiles wide ones
-// (22016 x 4096, 256 rows: 12 tiles 86 us, 8 tiles 98).  A projection without scratch for partial sums takes the
-// 8- or 12-tile kernels, which exist with every epilogue.
-//
-// B > 256: NG groups of GB rows; part_bytes bounds the slices (B rows of partial sums each).
+// Row tiles per workgroup (4, 8, 12), batch tiles per wave (1, 2: groups of up to 64 or 128 rows) and K slices, by a cost
+// model fitted to 6910 measured launches: every cut of 17 projections (1280..32000 features, K 1024..11008) at 16 live
+// batches of 33..1024 rows (rms error 7 %; the cut it picks is within 3 % of the best measured in 89 % of the 272 cases,
+// within 10 % in 95 %, 1.2 % off on average).  A launch takes 7.6 us plus its k-steps, each the longest of the matrix
+// products (0.0205 us per tile pair), the operand fetch (0.0198 us per KiB of weights and 0.0108 per KiB of batch fragments
+// of a workgroup) and the weight stream (0.038 us per KiB and workgroup with all 256 busy, less where groups share it), plus
+// 0.78 us per MB of partial sums and 3.1 us for their reduction.  Few row tiles per workgroup and few slices suit narrow
+// projections (1280 x 8192, 60 rows: 4 tiles 16.8 us, 8 tiles 20.1), many tiles wide ones (22016 x 4096, 256 rows: 12 tiles
+// 85 us, 8 tiles 114).  A projection without scratch for partial sums takes the 8- or 12-tile kernels, which exist with
+// every epilogue; part_bytes bounds the slices (B rows of partial sums each).
 void plan_wide(int n_tiles, int KS, int B, int n_cu, int64_t part_bytes, GemmPlan &p)
 {
-    p.NG = (B + 255) / 256;
-    p.GB = ((B + p.NG - 1) / p.NG + 15) / 16 * 16;
-    const int RB = (std::min(p.GB, B) + 63) / 64, kb_max = max_slices(n_tiles, KS, n_cu);
+    const int kb_max = max_slices(n_tiles, KS, n_cu);
     double best = 0.0;
-    for (int RA = 4; RA <= 12; RA += 4)
-        for (int kb = 1; kb <= kb_max; ++kb) {
-            const int64_t bytes = (int64_t)kb * B * n_tiles * 64;
-            if (bytes > part_bytes && (kb > 1 || RA == 4)) continue;             // without scratch: one slice, kernels with every epilogue
-            const int rg = (n_tiles + RA - 1) / RA, wgs = rg * kb * p.NG, rounds = (wgs + n_cu - 1) / n_cu;
-            const double busy = std::min(1.0, (double)wgs / n_cu);
-            const double step = std::max({0.0203 * RA * RB, 0.0058 + 0.0142 * (RA + 8 * RB), 0.0502 * RA * busy});
-            const double parts = kb == 1 && RA != 4 ? 0.0 : 0.476e-6 * (double)bytes + 1.0;
-            const double cost = 7.5 + rounds * ((KS + kb - 1) / kb) * step + parts;
-            if (best == 0.0 || cost < best) { best = cost; p.Kb = kb; p.Rg = rg; p.MT = RA; }
-        }
-    p.NB = 4 * RB;
+    for (int RB = 1; RB <= 2; ++RB) {
+        const int ng = (B + 64 * RB - 1) / (64 * RB), gb = ((B + ng - 1) / ng + 15) / 16 * 16;
+        if (RB == 2 && gb <= 64) continue;                                         // as with one tile per wave
+        for (int RA = 4; RA <= 12; RA += 4)
+            for (int kb = 1; kb <= kb_max; ++kb) {
+                const int64_t bytes = (int64_t)kb * B * n_tiles * 64;
+                if (bytes > part_bytes && (kb > 1 || RA == 4)) continue;             // without scratch: one slice, kernels with every epilogue
+                const int rg = (n_tiles + RA - 1) / RA, wgs = rg * kb * ng, rounds = (wgs + n_cu - 1) / n_cu;
+                const double busy = std::min(1.0, (double)wgs / n_cu);
+                const double step = std::max({0.0205 * RA * RB, 0.006 + 0.0198 * RA + 0.0864 * RB, 0.038 * RA * busy * (ng > 1 ? 0.6 : 1.0)});
+                const double parts = kb == 1 && RA != 4 ? 0.0 : 0.78e-6 * (double)bytes + 3.1;
+                const double cost = 7.6 + rounds * ((KS + kb - 1) / kb) * step + parts;
+                if (best == 0.0 || cost < best) { best = cost; p.Kb = kb; p.Rg = rg; p.MT = RA; p.NB = 4 * RB; p.NG = ng; p.GB = gb; }
+            }
+    }
 }
 
 // Bytes of partial sums a launch may need (an upper bound over the cuts plan_wide chooses from).
@@ -365,8 +371,7 @@ hipError_t launch_gemm_wide(const GemmArgs &a0, const GemmPlan &p, int mode, hip
     if (!direct && (a.part == nullptr || (int64_t)a.Kb * a.B * a.n_tiles * 64 > a.part_bytes)) return hipErrorInvalidValue;
     const int m = direct ? mode : kPartial;
     if (direct) a.ngains = nullptr;          // the epilogue's own hand-over is the small-batch one (x * gains and per-tile statistics)
-    const hipError_t e = p.NB == 4 ? launch_wide_rb<1>(a, p.MT, m, s) : p.NB == 8 ? launch_wide_rb<2>(a, p.MT, m, s)
-                       : p.NB == 12 ? launch_wide_rb<3>(a, p.MT, m, s) : launch_wide_rb<4>(a, p.MT, m, s);
+    const hipError_t e = p.NB == 4 ? launch_wide_rb<1>(a, p.MT, m, s) : launch_wide_rb<2>(a, p.MT, m, s);
     if (e != hipSuccess) return e;
     if (direct) {
         if (mode == kGemmAccum && a0.ngains != nullptr) return launch_rmsnorm_pack(a.y, a0.ngains, a.B, a.s_h, a.s_eps, a.npk_hi, a.npk_lo, s);

@@ -1,5 +1,5 @@
-"""The full-batch projection kernel (33..256 rows) at the edges of its tiles, rings and K slices, through the C ABI,
-against float64 products of the same operands."""
+"""The full-batch projection kernel (33 rows and more) at the edges of its tiles, rings, row groups and K slices, through the
+C ABI, against float64 products of the same operands."""
 import numpy as np
 import pytest
 import torch
@@ -43,3 +43,24 @@ def test_edges_of_tiles_rings_and_slices(n, k, b):
         g, u = ref[:, : n // 2], ref[:, n // 2:]
         want = g / (1.0 + np.exp(-g)) * u
         assert np.max(np.abs(pat.unpack_act(yh, yl, b, n // 2) - want)) <= 2e-4 * float(np.sqrt(np.mean(want * want))) + 2 * tol * float(np.max(np.abs(ref)))
+
+
+@pytest.mark.parametrize("n,k,b", [(22016, 4096, 40), (22016, 4096, 256), (32000, 4096, 200), (13824, 5120, 101), (7168, 8192, 60),
+                                   (7168, 8192, 256), (4096, 11008, 128)])
+def test_long_sums_are_taken_in_blocks(n, k, b):
+    """The fp32 sums against float64 sums of the same split operands.  A rounding of the running sum costs about 2.5e-8 of it
+    (2^-24 uniform, averaged over a binade); blocks of at most 15 k-steps and a second chain over the blocks stay below
+    2.2e-7, one chain of 2 k / 32 additions gives 4e-7 .. 8e-7 at these depths."""
+    import paper_2605_23945_amd as pat
+    g = torch.Generator(device=DEV).manual_seed(n + k + b)
+    w = torch.empty(n, k, dtype=torch.bfloat16, device=DEV).normal_(0.0, 0.02, generator=g)
+    x = torch.randn(b, k, device=DEV, generator=g)
+    hi, lo = pat.pat_op_pack_act(x)
+    y = torch.empty(b, n, device=DEV)
+    pat.pat_op_gemm(pat.pat_op_pack_weight(w), n, k, hi, lo, b, y, mode=0)
+    xh = x.bfloat16().float()
+    xl = (x - xh).bfloat16().float()
+    ref = (xh.double() + xl.double()) @ w.double().t().contiguous()
+    err = float((y.double() - ref).norm() / ref.norm())
+    print(f"{n} x {k}, {b} rows: {err:.3e}", flush=True)
+    assert err <= 2.2e-7
