@@ -234,6 +234,11 @@ int pat_decode_reset(pat_ctx *ctx);
  * K/V of every cached token once, appended K/V), host arithmetic. */
 int pat_step_algo_bytes(pat_ctx *ctx, double *weight_bytes, double *kv_bytes);
 
+/* How attention is cut over the keys.  step: tokens per chunk and chunks of all sequences (the live batch's size where every
+ * sequence is one chunk) in the step that the live batch would take now; prefill: tokens per chunk and chunks of all rows (0
+ * where every row has one) in the most finely cut pass of the last pat_prefill.  Host arithmetic; either may be NULL. */
+int pat_attention_cut(pat_ctx *ctx, int32_t step[2], int32_t prefill[2]);
+
 /* Kernel-class timing: when enabled, every launch of the class is bracketed by
  * HIP events on the step's stream; totals accumulate until read.
  * class: 0 weight-streaming projections other than gate/up (QKV, O, down, vocabulary head; the fused layer launches when

@@ -84,7 +84,7 @@ class pat_switch_decision(C.Structure):
 
 EXPORTS = ["pat_decode_query", "pat_decode_init", "pat_load_layer", "pat_load_layer_from_full", "pat_load_final", "pat_decode_admit",
            "pat_kv_write", "pat_kv_read", "pat_kv_extract", "pat_kv_inject", "pat_prefill", "pat_decode_step", "pat_kv_compact", "pat_get_state", "pat_get_pages",
-           "pat_profile_grid", "pat_profile_prefill", "pat_decode_reset", "pat_step_algo_bytes", "pat_timing_enable", "pat_timing_read", "pat_timing_fused_trace",
+           "pat_profile_grid", "pat_profile_prefill", "pat_decode_reset", "pat_step_algo_bytes", "pat_attention_cut", "pat_timing_enable", "pat_timing_read", "pat_timing_fused_trace",
            "pat_decode_destroy", "pat_last_error", "pat_op_packed_weight_bytes", "pat_op_pack_weight",
            "pat_op_packed_act_bytes", "pat_op_pack_act", "pat_op_gemm", "pat_op_gemm_static", "pat_op_gemm_scratch_bytes", "pat_op_gemm_plan", "pat_op_rmsnorm_pack", "pat_op_embed_stats", "pat_op_pack_act_gain", "pat_op_gemm_norm", "pat_decode_uses_fused_kernel", "pat_op_barrier_probe", "pat_op_argmax",
            "pat_predictor_fit", "pat_predictor_destroy", "pat_predictor_line", "pat_predictor_query", "pat_switch_decide",
@@ -121,6 +121,7 @@ def load_library() -> C.CDLL:
                                      C.c_uint64, C.POINTER(pat_grid_row), i32p]
     lib.pat_profile_prefill.argtypes = [vp, i32p, C.c_int32, i32p, C.c_int32, C.c_int64, C.c_int32, C.c_uint64, C.POINTER(pat_prefill_row)]
     lib.pat_decode_reset.argtypes = [vp]
+    lib.pat_attention_cut.argtypes = [vp, i32p, i32p]
     lib.pat_step_algo_bytes.argtypes = [vp, C.POINTER(C.c_double), C.POINTER(C.c_double)]
     lib.pat_timing_enable.argtypes = [vp, C.c_int32]
     lib.pat_timing_read.argtypes = [vp, C.c_int32, C.POINTER(C.c_double), C.POINTER(C.c_int64), C.c_int32]
@@ -331,6 +332,11 @@ class Decoder:
         w, k = C.c_double(), C.c_double()
         self._chk(self.lib.pat_step_algo_bytes(self.ctx, C.byref(w), C.byref(k)))
         return w.value, k.value
+
+    def pat_attention_cut(self) -> dict:
+        a, b = (C.c_int32 * 2)(), (C.c_int32 * 2)()
+        self._chk(self.lib.pat_attention_cut(self.ctx, a, b))
+        return {"step": tuple(a), "prefill": tuple(b)}
 
     def pat_timing_enable(self, on: bool):
         self._chk(self.lib.pat_timing_enable(self.ctx, int(on)))

@@ -52,6 +52,9 @@ int64_t packed_x_bytes(int b, int k) { return (int64_t)cdiv(b, 16) * (k / 32) * 
 const int kMinChunk = 64;
 const int kPfRecords = 32768;   // (block of positions, key chunk) records of one prefill pass
 
+// Blocks of a prefill pass: n consecutive positions of one sequence, rows row0 .. of the pass.
+struct PfBlock { int row0, n, slot, pos0; };
+
 }  // namespace
 
 struct pat_ctx {
@@ -81,6 +84,8 @@ struct pat_ctx {
                                     // records, then 3 * max_batch ints (token, slot, position of the pass's rows)
     hipEvent_t pf_done[2] = {nullptr, nullptr};   // recorded after the copies that read a set were enqueued
     bool pf_used[2] = {false, false};
+    std::vector<PfBlock> pf_blocks; // of the pass being built; reserved once (max_batch: a block holds a row)
+    int32_t pf_cut[2] = {0, 0};     // chunk length and row chunks of the last prefill's most finely cut pass
     // timing
     bool timing = false;
     struct Ev { int klass; hipEvent_t a, b; };
@@ -307,9 +312,6 @@ int pick_chunk(const pat_ctx *c, int64_t *n_chunks)
     return best;
 }
 
-// Blocks of a prefill pass: n consecutive positions of one sequence, rows row0 .. of the pass.
-struct PfBlock { int row0, n, slot, pos0; };
-
 // Chunk length of a prefill pass's attention, and the chunks of all its rows (0: every row has one, so nothing is merged).
 // Two workgroups fit a compute unit; an item takes about 3 us and 1.2 us per tile of 64 keys (alone on its compute unit or
 // beside another), a merge another launch and the partial results' round trip.  Short contexts (or passes with items enough) are best left whole; a wide pass of
@@ -382,6 +384,7 @@ int pat_decode_init(const pat_cfg *cfg, const pat_buffers *bufs, void *hip_strea
                         at<int32_t>(W, w.tmp), s.max_pages, cfg->page_tokens};
     c->layer_loaded.assign(s.NL, 0);
     const int MB = cfg->max_batch;
+    c->pf_blocks.reserve(MB);
     c->seq_id.resize(MB); c->kv_len.resize(MB); c->gen.resize(MB); c->target.resize(MB); c->fin.assign(MB, 0);
     c->n_free = s.n_pages;
     auto die = [&](const char *what, hipError_t e) { fprintf(stderr, "pat_decode_init: %s: %s\n", what, hipGetErrorString(e)); if (c->pinned) (void)hipHostFree(c->pinned); if (c->pf_stage) (void)hipHostFree(c->pf_stage); for (auto ev : c->pf_done) if (ev) (void)hipEventDestroy(ev); delete c; return PAT_EHIP; };
@@ -628,6 +631,17 @@ int pat_step_algo_bytes(pat_ctx *c, double *weight_bytes, double *kv_bytes)
     for (int i = 0; i < c->live; ++i) ctx += c->kv_len[i] + 1;
     if (weight_bytes) *weight_bytes = s.NL * per_layer + 2.0 * s.Vs * s.H;
     if (kv_bytes) *kv_bytes = (double)s.NL * 2 * s.hkv * s.d * 2 * (ctx + c->live);
+    return PAT_OK;
+}
+
+int pat_attention_cut(pat_ctx *c, int32_t step[2], int32_t prefill[2])
+{
+    if (!c) return PAT_EINVAL;
+    if (step) {
+        step[0] = step[1] = 0;
+        if (c->live > 0) { int64_t n = 0; step[0] = pick_chunk(c, &n); step[1] = (int32_t)n; }
+    }
+    if (prefill) { prefill[0] = c->pf_cut[0]; prefill[1] = c->pf_cut[1]; }
     return PAT_OK;
 }
 
@@ -927,7 +941,8 @@ int pat_prefill(pat_ctx *c, int32_t n, const int32_t *slots, const int32_t *toke
     int64_t t = 0;
     const int NP = attn_prefill_block(s.hq / s.hkv);      // positions per attention block
     const size_t set_ints = (size_t)kPfRecords * 8 + (size_t)3 * MB;
-    std::vector<PfBlock> blocks;
+    std::vector<PfBlock> &blocks = c->pf_blocks;
+    c->pf_cut[0] = c->pf_cut[1] = 0;
     int pass = 0;
     while (t < n_tokens) {
         // Two pinned staging sets in turn: the host builds pass n + 1 while the GPU runs pass n, and waits only for
@@ -949,6 +964,7 @@ int pat_prefill(pat_ctx *c, int32_t n, const int32_t *slots, const int32_t *toke
         }
         int64_t chunks = 0;
         const int C = pick_prefill_chunk(c, blocks, &chunks);
+        if (c->pf_cut[0] == 0 || chunks > c->pf_cut[1]) { c->pf_cut[0] = C; c->pf_cut[1] = (int32_t)chunks; }
         int64_t n_rec = 0;
         for (const PfBlock &b : blocks)
             for (int k0 = 0; k0 < b.pos0 + b.n; k0 += C) {

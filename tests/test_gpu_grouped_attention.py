@@ -33,3 +33,27 @@ def test_decode_attention_of_grouped_queries(hq, hkv, d, page, lens):
         check_logits(logits, ref_logits)
         assert np.array_equal(nxt, ref_next)
     dec.close()
+
+
+@pytest.mark.parametrize("hq,hkv,d,n,longest,chunk", [(8, 1, 128, 24, 1500, 192), (8, 1, 128, 36, 1500, 320), (8, 1, 128, 36, 2000, 448),
+                                                      (4, 1, 128, 3, 700, 64)])
+def test_chunks_that_start_inside_a_page(hq, hkv, d, n, longest, chunk):
+    """Pages of 128 tokens and chunks that are no multiple of them: a chunk's first key lies in the middle of a page, and its
+    pages are one more than its length suggests."""
+    import paper_2605_23945_amd as pat
+    shard = pi.shard_of(pi.ModelShape(1, 256, hq, hkv, d, 512, 512), 1, 0)
+    lens = np.array([longest - 7 * i for i in range(n)], np.int32)
+    req = pi.rollout_requests(shard, n, (1, 2), steps=4)
+    req["kv_len"] = lens
+    dec = make_decoder(shard, n, longest + 8, int(lens.sum()) + 256 * n, 128)
+    pat.admit_synthetic(dec, shard, req, DEV)
+    rows = sorted({0, 1, n // 2, n - 1})
+    odec = make_oracle_decoder(shard)
+    oracle_admit(odec, shard, req, rows, 4)
+    for _ in range(2):
+        assert dec.pat_attention_cut()["step"][0] == chunk
+        ref_logits, ref_next, _ = odec.step()
+        logits, nxt, _ = _gpu_step(dec, n, shard.vocab)
+        check_logits(logits[rows], ref_logits)
+        assert np.array_equal(nxt[rows], ref_next)
+    dec.close()

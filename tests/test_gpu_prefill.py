@@ -28,7 +28,7 @@ def _kv_bits(dec, slot, n_layers, L):
     return out
 
 
-def _prefill_parity(shard, kv_lens, slots, max_batch, page_tokens=64, steps=2):
+def _prefill_parity(shard, kv_lens, slots, max_batch, page_tokens=64, steps=2, chunked=None):
     pat = _pat()
     n = len(kv_lens)
     req = pi.rollout_requests(shard, n, (1, 2), steps=steps + 1)
@@ -41,6 +41,8 @@ def _prefill_parity(shard, kv_lens, slots, max_batch, page_tokens=64, steps=2):
     toks = [pi.prompt_tokens(shard, int(req["seq_id"][j]), int(kv_lens[j])) for j in slots]
     print(f"prefill: slots {list(slots)}, lengths {[int(kv_lens[j]) for j in slots]}, pass width {max_batch}", flush=True)
     dec.pat_prefill(slots, np.concatenate(toks) if toks else np.zeros(0, np.int32))
+    if chunked is not None:
+        assert (dec.pat_attention_cut()["prefill"][1] > 0) == chunked
     for j, t in zip(slots, toks):
         prefill(odec, j, t)
     st = dec.pat_get_state()
@@ -77,8 +79,7 @@ def _prefill_parity(shard, kv_lens, slots, max_batch, page_tokens=64, steps=2):
 
 
 def test_tiny_ragged_sequences_in_one_pass():
-    """Lengths 0, 1, one short of / on / past a page boundary, several attention chunks; rows of
-    all sequences share one pass."""
+    """Lengths 0, 1, one short of / on / past a page boundary; rows of all sequences share one pass."""
     shard = pi.CONFIGS["tiny_tp1"]["shard"]
     _prefill_parity(shard, [0, 1, 15, 16, 17, 90], [0, 1, 2, 3, 4, 5], max_batch=256, page_tokens=16)
 
@@ -90,16 +91,17 @@ def test_tiny_many_passes_and_a_subset_of_slots_in_any_order():
     _prefill_parity(shard, [9, 30, 5, 21], [3, 1], max_batch=4, page_tokens=16)
 
 
-def test_tiny_long_sequence_spanning_passes_and_chunks():
-    """300 + 270 positions at pass width 256: three passes, up to two attention chunks per row."""
+def test_tiny_long_sequence_spanning_passes():
+    """300 + 270 positions at pass width 256: three passes."""
     shard = pi.CONFIGS["tiny_tp1"]["shard"]
     _prefill_parity(shard, [300, 270], [0, 1], max_batch=256)
 
 
-def test_pass_wider_than_one_projection_group():
-    """Pass width 320: a pass of 320 rows runs its projections as groups of 256 + 64 rows."""
+@pytest.mark.parametrize("lens,width", [((200, 150, 90), 320), ((300, 200, 30), 530), ((500, 400, 124), 1000)])
+def test_pass_wider_than_one_projection_group(lens, width):
+    """Passes of 320, 530 and 1000 rows: three to sixteen row groups in a projection's launch, the last one ragged."""
     shard = pi.CONFIGS["tiny_tp1"]["shard"]
-    _prefill_parity(shard, [200, 150, 90], [0, 1, 2], max_batch=320, page_tokens=16)
+    _prefill_parity(shard, list(lens), [0, 1, 2], max_batch=width, page_tokens=16)
 
 
 @pytest.mark.parametrize("tp,rank", [(2, 1)])
@@ -210,11 +212,19 @@ def test_prefill_is_bitwise_repeatable_and_stable_across_pass_widths():
 
 
 # the block attention kernel: every head grouping and head dimension, blocks of 64 / G positions and 64-key tiles cut by
-# the sequence ends, pages shorter and longer than a tile; the last case's rows are few and its context long, so that its
-# keys are cut into chunks and merged
+# the sequence ends, pages shorter and longer than a tile
 @pytest.mark.parametrize("hq,hkv,d,page,lens,width", [(2, 2, 128, 16, (65, 1, 130), 256), (4, 2, 128, 128, (63, 64, 129), 96),
-                                                      (8, 2, 64, 32, (15, 200, 17), 232), (8, 1, 128, 64, (8, 9, 191), 64),
-                                                      (8, 1, 64, 64, (1300,), 256)])
+                                                      (8, 2, 64, 32, (15, 200, 17), 232), (8, 1, 128, 64, (8, 9, 191), 64)])
 def test_block_attention_edges(hq, hkv, d, page, lens, width):
     shard = pi.ShardShape(pi.ModelShape(2, 256, hq, hkv, d, 256, 256), 1, 0)
-    _prefill_parity(shard, list(lens), list(range(len(lens))), max_batch=width, page_tokens=page)
+    _prefill_parity(shard, list(lens), list(range(len(lens))), max_batch=width, page_tokens=page, chunked=False)
+
+
+# few rows over a long context: their keys are cut into chunks and merged; the last pass holds the end of the long sequence
+# (several chunks per row) and whole short ones, whose rows take no part in the later chunks
+@pytest.mark.parametrize("hq,hkv,d,page,lens,width", [(8, 1, 64, 64, (1300,), 256), (8, 1, 128, 128, (1300, 9, 70), 256),
+                                                      (2, 2, 128, 64, (1290, 65), 256), (4, 2, 64, 16, (1400, 1, 130), 256),
+                                                      (8, 2, 128, 32, (1100, 33), 128), (2, 2, 64, 64, (900, 20), 128)])
+def test_block_attention_over_chunks(hq, hkv, d, page, lens, width):
+    shard = pi.ShardShape(pi.ModelShape(2, 256, hq, hkv, d, 256, 256), 1, 0)
+    _prefill_parity(shard, list(lens), list(range(len(lens))), max_batch=width, page_tokens=page, steps=1, chunked=True)

@@ -145,10 +145,10 @@ def test_grouped_query_shapes(hq, hkv, d):
 
 @pytest.mark.parametrize("page_tokens", [64, 16])
 def test_grouped_query_many_long_sequences_use_long_chunks(page_tokens):
-    """One KV head, 8 query heads, 72 sequences of about 3000 cached tokens: more 256-token chunks than
-    the chip holds at once, so the host picks 512-token chunks (8 rounds per item, 8 or 32 pages each)."""
+    """One KV head, 8 query heads, 72 sequences of about 3000 cached tokens: memory bounds their attention whatever the cut,
+    so the host picks the longest chunks (1024 tokens: 8 tiles per wave, 16 or 64 pages each)."""
     m = pi.ModelShape(1, 256, 8, 1, 128, 512, 512)
-    _sampled_rows_parity(pi.shard_of(m, 1, 0), 72, (2800, 3300), [0, 17, 71], steps=2, page_tokens=page_tokens)
+    _sampled_rows_parity(pi.shard_of(m, 1, 0), 72, (2800, 3300), [0, 17, 71], steps=2, page_tokens=page_tokens, chunk=1024)
 
 
 def test_long_context_many_chunks_and_ragged_batch():
@@ -289,11 +289,12 @@ def test_70b_gqa_tp8_shape_two_layers_sampled_rows():
     dec.close()
 
 
-def _sampled_rows_parity(shard, n, prompt_len, rows, steps=1, max_seq=None, page_tokens=64):
+def _sampled_rows_parity(shard, n, prompt_len, rows, steps=1, max_seq=None, page_tokens=64, chunk=None):
     pat = _pat()
     req = pi.rollout_requests(shard, n, prompt_len, steps=steps + 2)
     dec = make_decoder(shard, n, (max_seq or prompt_len[1]) + steps + 8, int(req["kv_len"].sum()) + 2 * page_tokens * n + 256, page_tokens)
     pat.admit_synthetic(dec, shard, req, DEV)
+    assert chunk is None or dec.pat_attention_cut()["step"][0] == chunk
     odec = make_oracle_decoder(shard, layer_cache=False)
     oracle_admit(odec, shard, req, rows, steps + 2)
     worst = 0.0
@@ -313,20 +314,34 @@ def test_7b_tp4_shard_shape_two_layers_sampled_rows():
 
 
 def test_7b_shape_two_layers_batch_200_full_batch_projections():
-    """Live batch 200 (13 batch tiles, the last one ragged): the projections that hold the whole batch."""
+    """Live batch 200 (13 batch tiles, the last one ragged): projections of several row groups."""
     shard = pi.CONFIGS["7b_tp1"]["shard"].with_layers(2)
     _sampled_rows_parity(shard, 200, (64, 300), [0, 63, 64, 127, 128, 191, 192, 199], steps=2)
 
 
-def test_live_batch_300_runs_as_two_projection_groups():
-    """More than 256 live sequences: the projections run as groups of 256 rows (256 + 44 here), every
-    other kernel over all rows at once; rows on both sides of the group boundary are checked."""
+@pytest.mark.parametrize("n,rows", [(300, [0, 63, 64, 111, 112, 127, 128, 223, 224, 255, 256, 257, 299]),
+                                    (530, [0, 63, 64, 111, 112, 447, 448, 511, 512, 529]),
+                                    (1000, [0, 127, 128, 511, 512, 895, 896, 959, 960, 999])])
+def test_large_live_batches_run_as_row_groups(n, rows):
+    """More than 128 live sequences: the projections run as equal groups of up to 64 or 128 rows with a ragged last one
+    (300 rows: 112, 112, 76 or four of 64 and 44; 530: four of 112 and 82 or eight of 64 and 18; 1000: seven of 128 and 104
+    or fifteen of 64 and 40), every other kernel over all rows at once; rows on both sides of those boundaries."""
     shard = pi.CONFIGS["tiny_tp1"]["shard"]
-    _sampled_rows_parity(shard, 300, (10, 120), [0, 255, 256, 257, 299], steps=2, page_tokens=16)
+    _sampled_rows_parity(shard, n, (10, 120), rows, steps=2, page_tokens=16)
+
+
+def test_hidden_size_past_what_the_norm_keeps_in_registers():
+    """8256 features: the reduction that adds the K slices and normalises the row reads its own sums again past 8192."""
+    import ctypes
+    shard = pi.shard_of(pi.ModelShape(2, 8256, 2, 2, 64, 2048, 512), 1, 0)
+    plan = (ctypes.c_int32 * 4)()
+    assert _pat().load_library().pat_op_gemm_plan(8256, 2048, 40, plan) == 0
+    assert plan[1] > 1                                       # K slices: their sums go through the reduction
+    _sampled_rows_parity(shard, 40, (5, 60), [0, 15, 16, 39], steps=2)
 
 
 def test_13b_tp2_shard_batch_130_full_batch_projections():
-    """Live batch 130 (nine batch tiles -> the 12-tile shape) on the hidden-5120 shard."""
+    """Live batch 130 (nine batch tiles, two or three row groups) on the hidden-5120 shard."""
     shard = pi.CONFIGS["13b_tp2"]["shard"].with_layers(2)
     _sampled_rows_parity(shard, 130, (64, 200), [0, 64, 128, 129], steps=1)
 
