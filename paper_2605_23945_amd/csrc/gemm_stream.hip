@@ -396,7 +396,7 @@ hipError_t gemm_prepare_device()
 static int g_target_wgs = 256;   // one resident workgroup per compute unit
 void gemm_set_compute_units(int n) { if (n > 0) g_target_wgs = n; }
 
-GemmPlan gemm_plan(int n_tiles, int KS, int B, int64_t part_bytes)
+GemmPlan gemm_plan(int n_tiles, int KS, int B, int64_t part_bytes, bool norm)
 {
     GemmPlan p{1, 1, 1, 16, kAlgoXs, 1, B};
     if (B <= 32) {
@@ -405,7 +405,7 @@ GemmPlan gemm_plan(int n_tiles, int KS, int B, int64_t part_bytes)
         p.NB = B <= 16 ? 1 : 2; p.MT = B <= 16 ? 16 : 8;
     } else {
         p.algo = kAlgoWide;
-        plan_wide(n_tiles, KS, B, g_target_wgs, part_bytes, p);
+        plan_wide(n_tiles, KS, B, g_target_wgs, part_bytes, norm, p);
     }
     return p;
 }
@@ -417,7 +417,7 @@ hipError_t launch_gemm(const GemmArgs &a0, int mode, hipStream_t s)
     if (a0.B <= 0 || a0.n_tiles <= 0) return hipSuccess;
     if (a0.KS < 1) return hipErrorInvalidValue;
     GemmArgs a = a0;
-    const GemmPlan p = gemm_plan(a.n_tiles, a.KS, a.B, a.part ? a.part_bytes : 0);
+    const GemmPlan p = gemm_plan(a.n_tiles, a.KS, a.B, a.part ? a.part_bytes : 0, mode == kGemmAccum && a.ngains != nullptr);
     a.Kb = p.Kb; a.Rg = p.Rg; a.NG = p.NG; a.GB = p.GB;
     if (a.sstats != nullptr && a.B > 32) return hipErrorInvalidValue;      // the consumer side of a folded RMSNorm: small-batch kernels only
     if (a.ngains != nullptr && (a.n_valid % 32 != 0 || !a.npk_hi || !a.npk_lo || (a.B <= 32 && !a.nstats))) return hipErrorInvalidValue;

@@ -328,15 +328,16 @@ hipError_t gemm_wide_prepare_device()
 
 // Row tiles per workgroup (4, 8, 12), batch tiles per wave (1, 2: groups of up to 64 or 128 rows) and K slices, by a cost
 // model fitted to 6910 measured launches: every cut of 17 projections (1280..32000 features, K 1024..11008) at 16 live
-// batches of 33..1024 rows (rms error 7 %; the cut it picks is within 3 % of the best measured in 89 % of the 272 cases,
-// within 10 % in 95 %, 1.2 % off on average).  A launch takes 7.6 us plus its k-steps, each the longest of the matrix
-// products (0.0205 us per tile pair), the operand fetch (0.0198 us per KiB of weights and 0.0108 per KiB of batch fragments
-// of a workgroup) and the weight stream (0.038 us per KiB and workgroup with all 256 busy, less where groups share it), plus
-// 0.78 us per MB of partial sums and 3.1 us for their reduction.  Few row tiles per workgroup and few slices suit narrow
-// projections (1280 x 8192, 60 rows: 4 tiles 16.8 us, 8 tiles 20.1), many tiles wide ones (22016 x 4096, 256 rows: 12 tiles
-// 85 us, 8 tiles 114).  A projection without scratch for partial sums takes the 8- or 12-tile kernels, which exist with
-// every epilogue; part_bytes bounds the slices (B rows of partial sums each).
-void plan_wide(int n_tiles, int KS, int B, int n_cu, int64_t part_bytes, GemmPlan &p)
+// batches of 33..1024 rows, the residual ones with the RMSNorm that follows (rms error 7 %; the cut it picks is within 3 % of
+// the best measured in 91 % of the 272 cases, within 10 % in 97 %, 0.8 % off on average).  A launch takes 9.1 us plus its
+// k-steps, each the longest of the matrix products (0.0215 us per tile pair), the operand fetch (0.0194 us per KiB of weights
+// and 0.0104 per KiB of batch fragments of a workgroup) and the weight stream (0.037 us per KiB and workgroup with all 256
+// busy, less where groups share it).  Partial sums cost 0.88 us per MB; a following norm 7.4 us and 0.87 us per MB of
+// results as a launch of its own, 2.4 us and 0.15 per MB of results within the reduction of the slices.  Few row
+// tiles per workgroup and few slices suit narrow projections (1280 x 8192, 64 rows: 4 tiles 16.9 us, 8 tiles 20.3), many
+// tiles wide ones (22016 x 4096, 256 rows: 12 tiles 86 us, 8 tiles 115).  A projection without scratch for partial sums takes
+// the 8- or 12-tile kernels, which exist with every epilogue; part_bytes bounds the slices (B rows of partial sums each).
+void plan_wide(int n_tiles, int KS, int B, int n_cu, int64_t part_bytes, bool norm, GemmPlan &p)
 {
     const int kb_max = max_slices(n_tiles, KS, n_cu);
     double best = 0.0;
@@ -349,9 +350,11 @@ void plan_wide(int n_tiles, int KS, int B, int n_cu, int64_t part_bytes, GemmPla
                 if (bytes > part_bytes && (kb > 1 || RA == 4)) continue;             // without scratch: one slice, kernels with every epilogue
                 const int rg = (n_tiles + RA - 1) / RA, wgs = rg * kb * ng, rounds = (wgs + n_cu - 1) / n_cu;
                 const double busy = std::min(1.0, (double)wgs / n_cu);
-                const double step = std::max({0.0205 * RA * RB, 0.006 + 0.0198 * RA + 0.0864 * RB, 0.038 * RA * busy * (ng > 1 ? 0.6 : 1.0)});
-                const double parts = kb == 1 && RA != 4 ? 0.0 : 0.78e-6 * (double)bytes + 3.1;
-                const double cost = 7.6 + rounds * ((KS + kb - 1) / kb) * step + parts;
+                const double step = std::max({0.0215 * RA * RB, 0.0065 + 0.0194 * RA + 0.0832 * RB, 0.037 * RA * busy * (ng > 1 ? 0.3 : 1.0)});
+                const bool direct = kb == 1 && RA != 4;
+                const double mb = 1e-6 * (double)bytes, y_mb = mb / kb;
+                const double tail = norm ? (direct ? 7.4 + 0.87 * y_mb : 2.4 + 0.8 * mb + 0.15 * y_mb) : direct ? 0.0 : 0.6 + 0.88 * mb;
+                const double cost = 9.1 + rounds * ((KS + kb - 1) / kb) * step + tail;
                 if (best == 0.0 || cost < best) { best = cost; p.Kb = kb; p.Rg = rg; p.MT = RA; p.NB = 4 * RB; p.NG = ng; p.GB = gb; }
             }
     }

@@ -48,9 +48,9 @@ struct GemmArgs {
 // How a [16 n_tiles, 32 KS] projection at live batch B is cut: K slices across workgroups and row groups.
 enum GemmAlgo { kAlgoXs = 0, kAlgoWide = 3 };
 struct GemmPlan { int Kb, Rg, NB, MT, algo, NG, GB; };      // MT: waves (small-batch kernel) or row tiles (gemm_wide) per workgroup; NG groups of GB batch rows
-GemmPlan gemm_plan(int n_tiles, int KS, int B, int64_t part_bytes);
+GemmPlan gemm_plan(int n_tiles, int KS, int B, int64_t part_bytes, bool norm = false);      // norm: an RMSNorm of the results follows (GemmArgs::ngains)
 int64_t gemm_scratch_bytes(int n_tiles, int KS, int B);      // room for partial sums that launch_gemm may need
-void plan_wide(int n_tiles, int KS, int B, int n_cu, int64_t part_bytes, GemmPlan &p);
+void plan_wide(int n_tiles, int KS, int B, int n_cu, int64_t part_bytes, bool norm, GemmPlan &p);
 int64_t gemm_wide_scratch_bytes(int n_tiles, int KS, int B, int n_cu);
 hipError_t gemm_wide_prepare_device();
 hipError_t launch_gemm_wide(const GemmArgs &a, const GemmPlan &p, int mode, hipStream_t s);
