@@ -272,14 +272,14 @@ int pick_chunk(const pat_ctx *c, int64_t *n_chunks)
     for (int i = 0; i < c->live; ++i) longest = std::max(longest, c->kv_len[i] + 1);
     // One chunk per sequence needs no merge: the attention kernel writes the O projection's operand itself.
     if (c->sh.hq / c->sh.hkv >= 4) {
-        // One workgroup of attn_gqa_kernel fits a compute unit.  An item takes about 4.1 us before and after its stream and
-        // 0.625 us per 64 tokens (32 KiB) when memory keeps up; when it does not, the stream runs at 6.2 TB/s and three
-        // quarters of the 4.1 us show in every round of items over the chip.  Measured (128 features, 8 heads, one KV
-        // head): 11 sequences of about 6000 tokens 22.6 / 15.9 / 15.1 / 16.3 / 11.0 / 11.6 / 16.6 us at 64 / 128 / 192 /
-        // 256 / 320 / 512 / 1024 tokens, 180 of about 2100 101.7 / 62.4 / 59.3 / 55.1 / 49.5 / 44.6 / 37.6 us; the merge
-        // adds 5 us and 0.05 us per chunk of the longest sequence, unless every sequence is one chunk (8 sequences of up to 173
-        // tokens 2.1 us faster per layer whole, of up to 691 2.5 us slower; 128 of up to 1018 4.2 us faster).  The rule takes
-        // the best length in each.
+        // One workgroup of attn_gqa_kernel fits a compute unit.  An item takes about 2.7 us before and after its stream and
+        // 0.89 us per 64 tokens of 128 features (32 KiB) when memory keeps up; when it does not, the stream runs at 7.1 TB/s and
+        // 2.3 us of every round of items over the chip show beside it; the merge adds 4.2 us, 0.024 us per chunk of the longest
+        // sequence and 0.001 us per row and head.  Fitted to every cut of 617 batches (8 or 4 heads on each of 1..8 KV heads, 64
+        // or 128 features, 1..200 sequences of 60..6000 tokens on average, K and V from memory): the cut it picks is 0.6 % off
+        // the best on average and within 3 % of it in 93 %.  The kernel alone, 11 sequences of about 6000 tokens (8 heads, one KV head, 128
+        // features): 22.6 / 15.9 / 15.1 / 16.3 / 11.0 / 11.6 / 16.6 us at 64 / 128 / 192 / 256 / 320 / 512 / 1024 tokens, 180 of
+        // about 2100 101.7 / 62.4 / 59.3 / 55.1 / 49.5 / 44.6 / 37.6 us.
         const int64_t tile_bytes = 64 * 2 * 2 * (int64_t)c->sh.d;
         int64_t tiles = 0;
         for (int i = 0; i < c->live; ++i) tiles += (c->kv_len[i] + 64) / 64;
@@ -288,8 +288,8 @@ int pick_chunk(const pat_ctx *c, int64_t *n_chunks)
             if (C > 1024) continue;                             // the kernel's longest chunk
             const int64_t n = count(C);
             const double rounds = (double)((n * c->sh.hkv + c->n_cu - 1) / c->n_cu), scale = (double)tile_bytes / 32768.0;
-            const double cost = std::max(rounds * (4.1 + 0.625 * scale * ((C + 63) / 64)), (double)(tiles * c->sh.hkv * tile_bytes) / 6.2e6 + 3.1 * rounds) +
-                                (C < longest ? 5.0 + 0.05 * ((longest + C - 1) / C) : 0.0);
+            const double cost = std::max(rounds * (2.7 + 0.89 * scale * ((C + 63) / 64)), (double)(tiles * c->sh.hkv * tile_bytes) / 7.1e6 + 2.3 * rounds) +
+                                (C < longest ? 4.2 + 0.024 * ((longest + C - 1) / C) + 0.001 * c->sh.hq * c->live : 0.0);
             if (best_n == 0 || cost < best_cost) { best = C; best_n = n; best_cost = cost; }
         }
         *n_chunks = best_n;

@@ -35,7 +35,7 @@ def test_decode_attention_of_grouped_queries(hq, hkv, d, page, lens):
     dec.close()
 
 
-@pytest.mark.parametrize("hq,hkv,d,n,longest,chunk", [(8, 1, 128, 24, 1500, 192), (8, 1, 128, 36, 1500, 320), (8, 1, 128, 36, 2000, 448),
+@pytest.mark.parametrize("hq,hkv,d,n,longest,chunk", [(8, 1, 128, 24, 1500, 192), (8, 1, 128, 36, 2000, 320), (8, 1, 128, 40, 2600, 448),
                                                       (4, 1, 128, 3, 700, 64)])
 def test_chunks_that_start_inside_a_page(hq, hkv, d, n, longest, chunk):
     """Pages of 128 tokens and chunks that are no multiple of them: a chunk's first key lies in the middle of a page, and its
