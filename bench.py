@@ -145,11 +145,11 @@ def roofline_objects(shard, prof_rows, classes, n_prof_steps, fused):
     if n0:
         rest = w_bytes - gu_bytes * classes[3][1]
         out["other_projections"] = {"kernel": ("layer_fused_kernel (O, gate/up, down, next QKV per launch)" if fused else
-                                               "gemm_xs_kernel / gemm_wide_kernel (QKV, O, down, vocabulary head)"),
+                                               "gemm_xs_kernel / gemm_wide_kernel (QKV, O and down, above 32 rows with the RMSNorm that follows, vocabulary head)"),
                                     "bound": "hbm", "achieved": round(rest / (ms0 * 1e-3) / 1e9, 1), "peak": 8000.0, "unit": "GB/s",
                                     "frac": round(rest / (ms0 * 1e-3) / HBM_PEAK, 4), "traffic": None, "launches": int(n0),
                                     "avg_launch_us": round(ms0 * 1e3 / n0, 2)}
-    out["everything_else"] = {"kernel": "embedding, argmax, bookkeeping (and rmsnorm_pack above 32 rows)", "total_ms": round(classes[2][0], 3),
+    out["everything_else"] = {"kernel": "plan, embedding, argmax, bookkeeping (and the first RMSNorm above 32 rows; the others are in other_projections)", "total_ms": round(classes[2][0], 3),
                               "launches": int(classes[2][1])}
     out["profiled_steps"] = int(n_prof_steps)
     return out

@@ -241,8 +241,8 @@ int pat_attention_cut(pat_ctx *ctx, int32_t step[2], int32_t prefill[2]);
 
 /* Kernel-class timing: when enabled, every launch of the class is bracketed by
  * HIP events on the step's stream; totals accumulate until read.
- * class: 0 weight-streaming projections other than gate/up (QKV, O, down, vocabulary head; the fused layer launches when
- * that kernel is in use), 1 attention (partial + merge), 2 everything else, 3 the gate/up projection. */
+ * class: 0 weight-streaming projections other than gate/up (QKV, O, down, vocabulary head; above 32 rows O and down with the
+ * RMSNorm that follows them; the fused layer launches when that kernel is in use), 1 attention (partial + merge), 2 everything else, 3 the gate/up projection. */
 int pat_timing_enable(pat_ctx *ctx, int32_t on);
 int pat_timing_read(pat_ctx *ctx, int32_t klass, double *total_ms, int64_t *launches, int32_t reset);
 
