@@ -90,8 +90,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a)
     }
     look_up(t0 + kTile);
     // Sums in blocks: `o` starts anew at every tile and is added to `sum`.  One chain over a whole context rounds so often at
-    // the size of the result that the output's distance from float64 (2.56e-6, 2-norm, of which all but a few percent is its
-    // split into two bf16 terms) grew by 1.2 % at 1756 keys; blocks of 4 tiles leave 0.08 % and take the same time (1024 rows
+    // the size of the result that the output's distance from float64 (2.56e-6, 2-norm; the two bf16 terms that it is stored in
+    // round it too) grew by 1.3 % at 1756 keys; blocks of 4 tiles leave 0.08 % and take the same time (1024 rows
     // over 4024 keys, 8 heads on one KV head: 133.7 us, every tile 133.0 us, two runs of one side differ by 0.9 us).
     floatx4_t o[FT], sum[FT];
 #pragma unroll
