@@ -159,6 +159,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, int rt, int qua
                 float ss = (o.x * o.x + o.y * o.y) + (o.z * o.z + o.w * o.w);
                 ss = ss + __shfl_xor(ss, 16, 64);
                 ss = ss + __shfl_xor(ss, 32, 64);
+                asm volatile("" : "+v"(ss));       // waited for here: pending past the branch, the next tile group's first loads would wait for it (and for the arguments' fetch)
                 if (quad == 0) a.nstats[(int64_t)rt * (((a.B + 15) >> 4) << 4) + b] = ss;
             }
         } else {

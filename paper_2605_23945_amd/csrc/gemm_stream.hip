@@ -127,26 +127,55 @@ __device__ __forceinline__ void xs_run(const GemmArgs &a, int lane, int wave, in
     else xs_pass<NB, U, WAVES>(a, lane, wave, kw0, tb0, nt, first, red);
 }
 
-template <int NB, int UK, int TB, int kXsWaves, bool HL, int MODE>
-__global__ __launch_bounds__(kXsWaves * 64) void gemm_xs_kernel(GemmArgs a)
+// The arguments that only the epilogue reads, as values that the compiler cannot see through at the place of the call: what
+// is derived from them (a null test, a layer's address) is derived there and not ahead of the stream, which would wait for
+// their fetch.  Whole groups of neighbours, also where a mode needs a part: the compiler fetches a group with one load, and
+// would put something else into the registers of an unused neighbour, after a wait for the load.
+template <class T> __device__ __forceinline__ void opaque(T &v) { asm volatile("" : "+s"(v)); }
+template <class T>
+__device__ __forceinline__ void opaque(T *&p)                   // stays a pointer to global memory for the compiler
 {
+    uint64_t v = (uint64_t)p;
+    asm volatile("" : "+s"(v));
+    p = (T *)(__attribute__((address_space(1))) T *)v;
+}
+template <class... T> __device__ __forceinline__ void opaque_all(T &...v) { (opaque(v), ...); }
+template <int MODE>
+__device__ __forceinline__ GemmArgs epilogue_args(GemmArgs a)
+{
+    opaque_all(a.y, a.ldy, a.n_valid);
+    if (MODE == kGemmQKV) opaque_all(a.kv.pool, a.kv.n_pages, a.kv.hkv, a.kv.P, a.kv.d, a.layer, a.hq, a.max_pages, a.KS_out, a.kv_len, a.page_table, a.row_slot, a.rope_cs);
+    if (MODE == kGemmSwiGLU) opaque_all(a.yhi, a.ylo, a.KS_out);
+    if (MODE == kGemmAccum) opaque_all(a.ngains, a.npk_hi, a.npk_lo, a.nstats, a.n_tiles);
+    else opaque_all(a.sstats, a.s_parts, a.s_h, a.s_eps, a.n_tiles);
+    return a;
+}
+
+// What the first loads depend on comes as leading scalar arguments, which the compiler's kernel-argument preload has in
+// registers when a wave starts; the rest of the arguments is fetched beside the stream.  The workgroup's row tiles follow
+// from a quotient and a remainder that the host divides.  Before, a launch began with a round trip to memory for its
+// arguments and two 64-bit divisions (150 scalar instructions each): eight steps of the 7B TP = 4 shard, one row, 11.95 ->
+// 11.13 ms, four of the TP = 1 shard, two rows, 14.51 -> 13.92 ms, 32 of the tiny configuration 2.29 -> 2.03 ms.
+template <int NB, int UK, int TB, int kXsWaves, bool HL, int MODE>
+__global__ __launch_bounds__(kXsWaves * 64) void gemm_xs_kernel(const uint4 *w, const uint4 *xhi, const uint4 *xlo, int KS, int B, int tiles_q, int tiles_r, GemmArgs a)
+{
+    a.w = w; a.xhi = xhi; a.xlo = xlo; a.KS = KS; a.B = B;
     extern __shared__ float4 red[];   // [TB][kXsWaves][NB][64]
     constexpr int R = 16 * NB, PQ = R / 4;          // batch rows of the tiles, 16-byte pieces per part of the row statistics
     __shared__ __align__(16) float s_part[kXsWaves][R];
     // the wave index as a scalar: what derives from it (k share, slots, tile) stays in scalar registers
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int KS = a.KS, Rg = a.Rg;
     const int rg = blockIdx.x;
     // the wave's contiguous share of the k-steps (shares differ by at most one step)
-    const int kown0 = (int)((int64_t)wave * KS / kXsWaves), kown1 = (int)((int64_t)(wave + 1) * KS / kXsWaves);
-    const int rt0 = (int)((int64_t)rg * a.n_tiles / Rg), rt1 = (int)((int64_t)(rg + 1) * a.n_tiles / Rg);
+    const int kown0 = (int)((unsigned)(wave * KS) / kXsWaves), kown1 = (int)((unsigned)((wave + 1) * KS) / kXsWaves);
+    // the workgroup's row tiles: the first tiles_r workgroups own one more than the others
+    const int rt0 = rg * tiles_q + min(rg, tiles_r), rt1 = rt0 + tiles_q + (rg < tiles_r ? 1 : 0);
 
     // Folded RMSNorm (a.sstats set): the operand rows are x * gains, the results are multiplied by 1 / rms of their
     // batch row.  The rows' sums of squares come as per-part sums sstats[part][R]; the workgroup adds them once, in
     // a fixed order: thread t takes the 16-byte pieces t, t + threads, ... (four rows of one part) in increasing
     // order, a wave folds its pieces per row group with a shuffle butterfly, and the wave sums meet in LDS at the
     // barrier the first tile group has anyway.
-    const bool scale = MODE != kGemmAccum && a.sstats != nullptr;     // the residual projections are never the consumer of a norm
     float inv[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) inv[nb] = 1.f;
@@ -172,18 +201,20 @@ __global__ __launch_bounds__(kXsWaves * 64) void gemm_xs_kernel(GemmArgs a)
         // The epilogue's own reads (see EpiPre) travel while the workgroup meets at the barrier.  What the epilogue
         // derives from the lane index is computed from this copy, which the compiler cannot see through: hoisted
         // above the stream those values would occupy registers the stream needs (spills inside the loop).
-        int lane_e = lane;
-        asm volatile("" : "+v"(lane_e));
+        int lane_e = lane, KS_e = KS;
+        asm volatile("" : "+v"(lane_e), "+s"(KS_e));
+        const GemmArgs e = epilogue_args<MODE>(a);
+        const bool scale = MODE != kGemmAccum && e.sstats != nullptr;     // the residual projections are never the consumer of a norm
         EpiPre pre[NB];
         if (wave < nt) {
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) pre[nb] = epilogue_prefetch<MODE>(a, tb0 + wave, lane_e >> 4, nb * 16 + (lane_e & 15));
+            for (int nb = 0; nb < NB; ++nb) pre[nb] = epilogue_prefetch<MODE>(e, tb0 + wave, lane_e >> 4, nb * 16 + (lane_e & 15));
         }
         if (scale && tb0 == rt0) {
             // read after the stream, like the epilogue's other operands: nothing of it occupies registers during the stream
             float4 ssq = make_float4(0.f, 0.f, 0.f, 0.f);
-            for (int i = (wave << 6) + lane_e; i < a.s_parts * PQ; i += kXsWaves * 64) {
-                const float4 t = reinterpret_cast<const float4 *>(a.sstats)[i];
+            for (int i = (wave << 6) + lane_e; i < e.s_parts * PQ; i += kXsWaves * 64) {
+                const float4 t = reinterpret_cast<const float4 *>(e.sstats)[i];
                 ssq.x += t.x; ssq.y += t.y; ssq.z += t.z; ssq.w += t.w;
             }
 #pragma unroll
@@ -201,7 +232,7 @@ __global__ __launch_bounds__(kXsWaves * 64) void gemm_xs_kernel(GemmArgs a)
                 float tot = 0.f;
 #pragma unroll
                 for (int w = 0; w < kXsWaves; ++w) tot += s_part[w][row];
-                inv[nb] = 1.0f / sqrtf(tot / (float)a.s_h + a.s_eps);
+                inv[nb] = 1.0f / sqrtf(tot / (float)e.s_h + e.s_eps);
             }
         }
         if (wave < nt) {
@@ -211,7 +242,7 @@ __global__ __launch_bounds__(kXsWaves * 64) void gemm_xs_kernel(GemmArgs a)
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
                 float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (KS >= kXsWaves) {                                      // every wave owns k-steps
+                if (KS_e >= kXsWaves) {                                    // every wave owns k-steps
                     v = red[(wave * kXsWaves * NB + nb) * 64 + lane];
 #pragma unroll
                     for (int ww = 1; ww < kXsWaves; ++ww) {
@@ -220,13 +251,13 @@ __global__ __launch_bounds__(kXsWaves * 64) void gemm_xs_kernel(GemmArgs a)
                     }
                 } else {
                     for (int ww = 0; ww < kXsWaves; ++ww) {
-                        if ((ww + 1) * KS / kXsWaves == ww * KS / kXsWaves) continue;   // empty share: no partial
+                        if ((ww + 1) * KS_e / kXsWaves == ww * KS_e / kXsWaves) continue;   // empty share: no partial
                         const float4 t = red[((wave * kXsWaves + ww) * NB + nb) * 64 + lane];
                         v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
                     }
                 }
                 if (scale) { v.x *= inv[nb]; v.y *= inv[nb]; v.z *= inv[nb]; v.w *= inv[nb]; }
-                gemm_epilogue<MODE>(a, rt, lane_e >> 4, nb * 16 + (lane_e & 15), v, pre[nb]);
+                gemm_epilogue<MODE>(e, rt, lane_e >> 4, nb * 16 + (lane_e & 15), v, pre[nb]);
             }
         }
         if (tb0 + TB < rt1) __syncthreads();
@@ -362,12 +393,13 @@ template <int NB, int UK, int TB, int kXsWaves, bool HL>
 hipError_t launch_xs(const GemmArgs &a, int mode, hipStream_t s)
 {
     const unsigned grid = (unsigned)a.Rg;
+    const int tq = a.n_tiles / a.Rg, tr = a.n_tiles % a.Rg;
     constexpr size_t lds = (size_t)TB * kXsWaves * NB * 64 * sizeof(float4);
     switch (mode) {
-    case kGemmStore: gemm_xs_kernel<NB, UK, TB, kXsWaves, HL, kGemmStore><<<grid, kXsWaves * 64, lds, s>>>(a); break;
-    case kGemmAccum: gemm_xs_kernel<NB, UK, TB, kXsWaves, HL, kGemmAccum><<<grid, kXsWaves * 64, lds, s>>>(a); break;
-    case kGemmQKV: gemm_xs_kernel<NB, UK, TB, kXsWaves, HL, kGemmQKV><<<grid, kXsWaves * 64, lds, s>>>(a); break;
-    default: gemm_xs_kernel<NB, UK, TB, kXsWaves, HL, kGemmSwiGLU><<<grid, kXsWaves * 64, lds, s>>>(a); break;
+    case kGemmStore: gemm_xs_kernel<NB, UK, TB, kXsWaves, HL, kGemmStore><<<grid, kXsWaves * 64, lds, s>>>(a.w, a.xhi, a.xlo, a.KS, a.B, tq, tr, a); break;
+    case kGemmAccum: gemm_xs_kernel<NB, UK, TB, kXsWaves, HL, kGemmAccum><<<grid, kXsWaves * 64, lds, s>>>(a.w, a.xhi, a.xlo, a.KS, a.B, tq, tr, a); break;
+    case kGemmQKV: gemm_xs_kernel<NB, UK, TB, kXsWaves, HL, kGemmQKV><<<grid, kXsWaves * 64, lds, s>>>(a.w, a.xhi, a.xlo, a.KS, a.B, tq, tr, a); break;
+    default: gemm_xs_kernel<NB, UK, TB, kXsWaves, HL, kGemmSwiGLU><<<grid, kXsWaves * 64, lds, s>>>(a.w, a.xhi, a.xlo, a.KS, a.B, tq, tr, a); break;
     }
     return hipGetLastError();
 }

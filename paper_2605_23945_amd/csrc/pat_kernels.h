@@ -16,20 +16,21 @@ struct KvLayout {
     __host__ __device__ int64_t base(int layer, int kv) const { return ((int64_t)layer * 2 + kv) * n_pages * page_elems(); }
 };
 
+// The order matters to the small-batch kernels: groups of fields that an epilogue reads together lie side by side without
+// padding (see epilogue_args in gemm_stream.hip).
 struct GemmArgs {
     const uint4 *w;            // packed weights: [n_tiles][KS][64] vectors
-    int n_tiles, KS;           // 16-row tiles, 32-wide k-steps
     const uint4 *xhi, *xlo;    // packed split-bf16 activations: [b_tiles][KS][64]
-    int B;                     // live rows
+    int KS, B;                 // 32-wide k-steps, live rows
     float *y;                  // [B, ldy] fp32 (store / accumulate)
     int ldy, n_valid;          // row stride of y, number of real output columns
     uint4 *yhi, *ylo;          // SwiGLU: packed split-bf16 output [b_tiles][KS_out][64]
-    int KS_out;
     // kGemmQKV (rows are this shard's q heads, k heads, v heads; q and k rows stored with rotary
     // partners adjacent): rotate q and k at position kv_len[b], write q fp32 into y (natural
     // order), append k and v as bf16 to the slot's page
     KvLayout kv;
     int layer, hq, max_pages;
+    int KS_out;                // SwiGLU: k-steps of the packed output
     const int32_t *kv_len, *page_table;
     const int32_t *row_slot;   // slot (page-table row) of batch row b, or NULL: slot b
     const float *rope_cs;      // [pos][d/2][cos, sin]
@@ -41,6 +42,7 @@ struct GemmArgs {
     //    batch row, from the per-part sums of squares sstats[part][16 * batch tiles] (fixed summation order).
     const uint16_t *ngains; uint4 *npk_hi, *npk_lo; float *nstats;
     const float *sstats; int s_parts, s_h; float s_eps;
+    int n_tiles;               // 16-row tiles of the weights
     float *part;               // scratch for K-slice partials [Kb][B][n_tiles * 16], or NULL
     int64_t part_bytes;        // its size: a plan that needs more is refused
     int Kb, Rg, NG, GB;        // set by launch_gemm from gemm_plan
