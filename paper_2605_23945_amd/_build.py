@@ -9,12 +9,11 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpat_decode.so")
 SOURCES = ["gemm_stream.hip", "gemm_wide.hip", "attention.hip", "attn_prefill.hip", "attn_gqa.hip", "layer_fused.hip", "step_misc.hip", "pat_decode.hip", "pat_switch.cpp"]
-# the last option: up to 16 words of leading scalar arguments are in a kernel's registers when its waves start
+# the last option: up to 14 words of leading scalar arguments are in a kernel's registers when its waves start
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-mllvm", "-amdgpu-kernarg-preload-count=16"]
-HOST_# the last option: up to 16 words of leading scalar arguments are in a kernel's registers when its waves start
-FLAGS = ["-O3", "-std=c++17", "-fPIC", "-Wall"]          # host-only sources (.cpp)
+HOST_FLAGS = ["-O3", "-std=c++17", "-fPIC", "-Wall"]          # host-only sources (.cpp)
 
 
 def build_library(verbose: bool = False) -> str:
