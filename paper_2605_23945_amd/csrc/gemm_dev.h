@@ -16,6 +16,7 @@ __device__ __forceinline__ floatx4_t mfma16(uint4 a, uint4 b, floatx4_t c)
 // used in a later one are held in this type: assignments of the runtime's uint4 class can be
 // lowered to memcpy between address spaces, which pins the variable in scratch memory.
 __device__ __forceinline__ u32x4_t ld16(const uint4 *p) { return *reinterpret_cast<const u32x4_t *>(p); }
+__device__ __forceinline__ u32x4_t ld16_stream(const uint4 *p) { return __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(p)); }     // data read once
 __device__ __forceinline__ void st16(uint4 *p, u32x4_t v) { *reinterpret_cast<u32x4_t *>(p) = v; }
 __device__ __forceinline__ floatx4_t mfma16(u32x4_t a, uint4 b, floatx4_t c)
 {

@@ -52,9 +52,9 @@ __device__ __forceinline__ void xs_pass(const GemmArgs &a, int lane, int wave, i
     }
     for (int i = 0; i < nt; ++i) {
         const uint4 *wp = a.w + ((int64_t)(tb0 + i) * KS + kw0) * 64 + lane;
-        uint4 w[U];
+        u32x4_t w[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) w[u] = wp[u * 64];
+        for (int u = 0; u < U; ++u) w[u] = ld16_stream(wp + u * 64);
         // keep all U loads in flight: without this the scheduler interleaves load / wait / multiply
         // through one register quad and the wave has a single KiB outstanding
         __builtin_amdgcn_sched_barrier(0);
@@ -100,7 +100,7 @@ __device__ __forceinline__ void xs_pass8(const GemmArgs &a, int lane, int wave, 
     auto fetch = [&](u32x4_t (&w)[U], int i) {
         const uint4 *wp = a.w + ((int64_t)(tb0 + i) * KS + kw0) * 64 + lane;
 #pragma unroll
-        for (int u = 0; u < U; ++u) w[u] = ld16(wp + u * 64);
+        for (int u = 0; u < U; ++u) w[u] = ld16_stream(wp + u * 64);
         __builtin_amdgcn_sched_barrier(0);                  // all U loads in flight, ahead of the matrix instructions
     };
     auto tile = [&](const u32x4_t (&w)[U], int i) {
