@@ -29,8 +29,10 @@ constexpr int kKeys = 32;       // keys per tile
 template <int N>
 __device__ __forceinline__ void wait_newer() { asm volatile("s_waitcnt vmcnt(%0)" ::"i"(N) : "memory"); }     // all but the N newest loads have arrived
 
+// Leading scalar arguments: what the first loads depend on (see gemm_xs_kernel).
 template <int D, int G, int W>
-__global__ __launch_bounds__(W * 64) void attn_gqa_kernel(AttnArgs a)
+__global__ __launch_bounds__(W * 64) void attn_gqa_kernel(const int32_t *meta, const uint16_t *kbase, const uint16_t *vbase, const float *qkv, uint32_t hkv, int ldq, int lgP,
+                                                          int C, AttnArgs a)
 {
     static_assert(G == 4 || G == 8, "heads per operand column");
     constexpr int KST = D / 32, FT = D / 16, PC = D / 8;       // k-steps of a score, 16-feature tiles, 16-byte pieces per row
@@ -41,10 +43,10 @@ __global__ __launch_bounds__(W * 64) void attn_gqa_kernel(AttnArgs a)
     __shared__ float wml[W][G][2];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 15, g4 = lane >> 4;
-    const int hkv = a.kv.hkv, P = a.kv.P, lgP = __builtin_ctz(P);
-    const int ce = blockIdx.x / hkv, h = blockIdx.x - ce * hkv;
-    int4 m0 = reinterpret_cast<const int4 *>(a.chunk_meta)[2 * (int64_t)ce];
-    int4 m1 = reinterpret_cast<const int4 *>(a.chunk_meta)[2 * (int64_t)ce + 1];
+    const int P = 1 << lgP;
+    const uint32_t ce = blockIdx.x / hkv, h = blockIdx.x - ce * hkv;
+    int4 m0 = reinterpret_cast<const int4 *>(meta)[2 * (int64_t)ce];
+    int4 m1 = reinterpret_cast<const int4 *>(meta)[2 * (int64_t)ce + 1];
     asm volatile("" : "+s"(m0.x), "+s"(m0.y), "+s"(m0.z), "+s"(m1.x), "+s"(m1.y), "+s"(m1.z), "+s"(m1.w));     // one load, not two in turn
     const int b = __builtin_amdgcn_readfirstlane(m0.x), t0 = __builtin_amdgcn_readfirstlane(m0.y),
               cnt = __builtin_amdgcn_readfirstlane(m0.z);
@@ -56,13 +58,12 @@ __global__ __launch_bounds__(W * 64) void attn_gqa_kernel(AttnArgs a)
     int page;
     {
         const int j = (min(t0 + ((lane >> 1) * W + wave) * kKeys + (lane & 1) * 16, last) >> lgP) - (t0 >> lgP);
-        if (a.chunk_tokens <= 4 * P) page = j == 0 ? m1.x : j == 1 ? m1.y : j == 2 ? m1.z : m1.w;
+        if (C <= 4 * P) page = j == 0 ? m1.x : j == 1 ? m1.y : j == 2 ? m1.z : m1.w;
         else page = a.page_table[(int64_t)(a.row_slot ? a.row_slot[b] : b) * a.max_pages + (t0 >> lgP) + j];
         asm volatile("" : "+v"(page));                         // here, or the compiler waits for all loads at every later use
     }
-    const int64_t page_bytes = a.kv.page_elems() * 2;
-    const char *kpool = reinterpret_cast<const char *>(a.kv.pool + a.kv.base(a.layer, 0)) + (int64_t)h * P * D * 2;
-    const char *vpool = reinterpret_cast<const char *>(a.kv.pool + a.kv.base(a.layer, 1)) + (int64_t)h * P * D * 2;
+    const int64_t page_bytes = (int64_t)(hkv << lgP) * D * 2, head_bytes = (int64_t)(h << lgP) * D * 2;
+    const char *kpool = reinterpret_cast<const char *>(kbase) + head_bytes, *vpool = reinterpret_cast<const char *>(vbase) + head_bytes;
     char *const ring = lds + wave * 4 * kHalf;
     const uint32_t ring0 = lds_offset(ring), q0 = lds_offset(lds + W * 4 * kHalf);
 
@@ -77,7 +78,7 @@ __global__ __launch_bounds__(W * 64) void attn_gqa_kernel(AttnArgs a)
         }
     };
     {
-        const char *qp = reinterpret_cast<const char *>(a.qkv + (int64_t)b * a.ldq + h * G * D);
+        const char *qp = reinterpret_cast<const char *>(qkv + (int64_t)b * ldq + h * G * D);
 #pragma unroll
         for (int i = 0; i < (NQ + W - 1) / W; ++i)
             if (i * W + wave < NQ) load_to_lds(qp, (uint32_t)((i * W + wave) * 1024 + lane * 16), q0 + (uint32_t)((i * W + wave) * 1024));
@@ -217,7 +218,8 @@ template <int D, int G> constexpr size_t gqa_lds() { return (size_t)kWaves * 4 *
 template <int D, int G>
 hipError_t launch_gqa(const AttnArgs &a, hipStream_t s)
 {
-    attn_gqa_kernel<D, G, kWaves><<<a.n_items, kWaves * 64, gqa_lds<D, G>(), s>>>(a);
+    attn_gqa_kernel<D, G, kWaves><<<a.n_items, kWaves * 64, gqa_lds<D, G>(), s>>>(a.chunk_meta, a.kv.pool + a.kv.base(a.layer, 0), a.kv.pool + a.kv.base(a.layer, 1), a.qkv,
+                                                                                  (uint32_t)a.kv.hkv, a.ldq, __builtin_ctz(a.kv.P), a.chunk_tokens, a);
     return hipGetLastError();
 }
 

@@ -28,7 +28,8 @@ constexpr int kTile = 64;       // keys per tile
 // DIRECT: every row has one chunk; the finished output goes to the packed operand of the O projection instead of the
 // partial (m, l, acc) of the row's chunk list.
 template <int D, int G, bool DIRECT>
-__global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a)
+__global__ __launch_bounds__(256, 2) void attn_prefill_kernel(const int32_t *meta, const uint16_t *kbase, const uint16_t *vbase, const float *qkv, const int32_t *page_table,
+                                                              uint32_t hkv, int ldq, int lgP, int C, int max_pages, AttnArgs a)
 {
     static_assert(G == 1 || G == 2 || G == 4 || G == 8, "the 64 operand rows are 64 / G positions x G heads");
     constexpr int KST = D / 32, FT = D / 16, PC = D / 8;       // k-steps of a score, 16-feature tiles, 16-byte pieces per row
@@ -36,18 +37,17 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a)
     __shared__ u32x4_t kv[2][2][kTile * PC];                   // [buffer][K | V][key][piece, permuted]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 15, g4 = lane >> 4;
-    const int hkv = a.kv.hkv, P = a.kv.P, lgP = __builtin_ctz(P);
-    const int ce = blockIdx.x / hkv, h = blockIdx.x - ce * hkv;
-    const int4 m0 = reinterpret_cast<const int4 *>(a.chunk_meta)[2 * (int64_t)ce];
-    const int4 m1 = reinterpret_cast<const int4 *>(a.chunk_meta)[2 * (int64_t)ce + 1];
+    const int P = 1 << lgP;
+    const uint32_t ce = blockIdx.x / hkv, h = blockIdx.x - ce * hkv;
+    const int4 m0 = reinterpret_cast<const int4 *>(meta)[2 * (int64_t)ce];
+    const int4 m1 = reinterpret_cast<const int4 *>(meta)[2 * (int64_t)ce + 1];
     const int row0 = __builtin_amdgcn_readfirstlane(m0.x), n = __builtin_amdgcn_readfirstlane(m0.y),
               slot = __builtin_amdgcn_readfirstlane(m0.z), pos0 = __builtin_amdgcn_readfirstlane(m0.w),
               t0 = __builtin_amdgcn_readfirstlane(m1.x);
-    const int last = min(t0 + a.chunk_tokens, pos0 + n) - 1;   // last key of the item
-    const int32_t *pt = a.page_table + (int64_t)slot * a.max_pages;
-    const int64_t page_bytes = a.kv.page_elems() * 2;
-    const char *pool[2] = {reinterpret_cast<const char *>(a.kv.pool + a.kv.base(a.layer, 0)) + (int64_t)h * P * D * 2,
-                           reinterpret_cast<const char *>(a.kv.pool + a.kv.base(a.layer, 1)) + (int64_t)h * P * D * 2};
+    const int last = min(t0 + C, pos0 + n) - 1;   // last key of the item
+    const int32_t *pt = page_table + (int64_t)slot * max_pages;
+    const int64_t page_bytes = (int64_t)(hkv << lgP) * D * 2, head_bytes = (int64_t)(h << lgP) * D * 2;
+    const char *pool[2] = {reinterpret_cast<const char *>(kbase) + head_bytes, reinterpret_cast<const char *>(vbase) + head_bytes};
     const uint32_t lds0 = lds_offset(kv);
 
     // Tile of 64 keys from `key0` into buffer `buf`: wave w loads keys 16 w .. 16 w + 15 of K and of V, KPI per instruction.
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a)
     u32x4_t qh[KST], ql[KST];
     {
         const float scale = rsqrtf((float)D) * 1.44269504f;              // scores in units of log2: p is one exp2 instruction
-        const float *qp = a.qkv + (int64_t)(row0 + min(pi, n - 1)) * a.ldq + head * D + g4 * 8;
+        const float *qp = qkv + (int64_t)(row0 + min(pi, n - 1)) * ldq + head * D + g4 * 8;
 #pragma unroll
         for (int ks = 0; ks < KST; ++ks) {
             const float4 q0 = *reinterpret_cast<const float4 *>(qp + ks * 32), q1 = *reinterpret_cast<const float4 *>(qp + ks * 32 + 4);
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a)
     for (int f = 0; f < FT; ++f) bad |= o[f][0] != o[f][0] || o[f][1] != o[f][1] || o[f][2] != o[f][2] || o[f][3] != o[f][3];
     if (__any(bad && live)) {
         const float scale = rsqrtf((float)D) * 1.44269504f, top = M == -INFINITY ? 0.f : M;
-        const float *qp = a.qkv + (int64_t)(row0 + min(pi, n - 1)) * a.ldq + head * D;
+        const float *qp = qkv + (int64_t)(row0 + min(pi, n - 1)) * ldq + head * D;
         const int end = min(wave_last, last);
         den = 0.f;
 #pragma unroll
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a)
             *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(a.olo) + off) = make_uint2((uint32_t)ll[0] | ((uint32_t)ll[1] << 16), (uint32_t)ll[2] | ((uint32_t)ll[3] << 16));
         }
     } else {
-        const int64_t ci = a.chunk_start[row0 + pi] + t0 / a.chunk_tokens;
+        const int64_t ci = a.chunk_start[row0 + pi] + t0 / C;
         float *acc = a.part_acc + (ci * a.hq + head) * D + g4 * 4;
 #pragma unroll
         for (int f = 0; f < FT; ++f) *reinterpret_cast<float4 *>(acc + f * 16) = make_float4(o[f][0], o[f][1], o[f][2], o[f][3]);
@@ -227,11 +227,13 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a)
 template <int D, bool DIRECT>
 hipError_t launch_prefill_d(const AttnArgs &a, hipStream_t s)
 {
+    const int lgP = __builtin_ctz(a.kv.P);
+    const uint16_t *kb = a.kv.pool + a.kv.base(a.layer, 0), *vb = a.kv.pool + a.kv.base(a.layer, 1);
     switch (a.hq / a.kv.hkv) {
-    case 1: attn_prefill_kernel<D, 1, DIRECT><<<a.n_items, 256, 0, s>>>(a); break;
-    case 2: attn_prefill_kernel<D, 2, DIRECT><<<a.n_items, 256, 0, s>>>(a); break;
-    case 4: attn_prefill_kernel<D, 4, DIRECT><<<a.n_items, 256, 0, s>>>(a); break;
-    case 8: attn_prefill_kernel<D, 8, DIRECT><<<a.n_items, 256, 0, s>>>(a); break;
+    case 1: attn_prefill_kernel<D, 1, DIRECT><<<a.n_items, 256, 0, s>>>(a.chunk_meta, kb, vb, a.qkv, a.page_table, (uint32_t)a.kv.hkv, a.ldq, lgP, a.chunk_tokens, a.max_pages, a); break;
+    case 2: attn_prefill_kernel<D, 2, DIRECT><<<a.n_items, 256, 0, s>>>(a.chunk_meta, kb, vb, a.qkv, a.page_table, (uint32_t)a.kv.hkv, a.ldq, lgP, a.chunk_tokens, a.max_pages, a); break;
+    case 4: attn_prefill_kernel<D, 4, DIRECT><<<a.n_items, 256, 0, s>>>(a.chunk_meta, kb, vb, a.qkv, a.page_table, (uint32_t)a.kv.hkv, a.ldq, lgP, a.chunk_tokens, a.max_pages, a); break;
+    case 8: attn_prefill_kernel<D, 8, DIRECT><<<a.n_items, 256, 0, s>>>(a.chunk_meta, kb, vb, a.qkv, a.page_table, (uint32_t)a.kv.hkv, a.ldq, lgP, a.chunk_tokens, a.max_pages, a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -265,6 +265,14 @@ GemmArgs gemm_args(const void *w, int n, int k, const uint4 *xhi, const uint4 *x
     return g;
 }
 
+// K and V that a layer of a decode step reads, the appended token included.
+int64_t live_kv_bytes(const pat_ctx *c)
+{
+    int64_t tokens = 0;
+    for (int i = 0; i < c->live; ++i) tokens += c->kv_len[i] + 1;
+    return tokens * c->sh.hkv * c->sh.d * 4;
+}
+
 int pick_chunk(const pat_ctx *c, int64_t *n_chunks)
 {
     auto count = [&](int C) { int64_t n = 0; for (int i = 0; i < c->live; ++i) n += (c->kv_len[i] + 1 + C - 1) / C; return n; };
@@ -285,7 +293,7 @@ int pick_chunk(const pat_ctx *c, int64_t *n_chunks)
         for (int i = 0; i < c->live; ++i) tiles += (c->kv_len[i] + 64) / 64;
         int best = kMinChunk; int64_t best_n = 0; double best_cost = 0.0;
         for (int C : {longest, 1024, 896, 768, 640, 512, 448, 384, 320, 256, 192, 128, 64}) {
-            if (C > 1024) continue;                             // the kernel's longest chunk
+            if (C > kAttnMaxChunk) continue;
             const int64_t n = count(C);
             const double rounds = (double)((n * c->sh.hkv + c->n_cu - 1) / c->n_cu), scale = (double)tile_bytes / 32768.0;
             const double cost = std::max(rounds * (2.7 + 0.89 * scale * ((C + 63) / 64)), (double)(tiles * c->sh.hkv * tile_bytes) / 7.1e6 + 2.3 * rounds) +
@@ -295,20 +303,24 @@ int pick_chunk(const pat_ctx *c, int64_t *n_chunks)
         *n_chunks = best_n;
         return best;
     }
-    // One-pass kernel of G < 4: whole sequences of up to 192 tokens, and of up to 384 when their heads give every compute
-    // unit an item (measured at live batches 1 .. 256 of the 7B, 7B TP = 4 and 13B TP = 2 shards, per layer against chunks
-    // of 64 or 128: up to 180 tokens -18 .. +1.5 us, 346 .. 360 tokens +2 .. +4 us below 256 items and -10 .. +2.7, mean -2.7,
-    // above, 700 tokens mostly slower by 1 .. 10).
-    if (longest <= 192 || (longest <= 384 && (int64_t)c->live * c->sh.hkv >= c->n_cu)) { *n_chunks = c->live; return longest; }
-    // Otherwise (measured at live batches 1 .. 256 on the 7B shard): 128-token chunks,
-    // 64 when that leaves fewer than two work items per compute unit; 256 is never faster
-    int best = kMinChunk;
-    int64_t best_n = 0;
-    for (int C : {128, 64}) {
-        best = C; best_n = count(C);
-        if (best_n * c->sh.hkv >= 2 * (int64_t)c->n_cu) break;
-    }
-    *n_chunks = best_n;
+    // One-pass kernel of G < 4, by the bytes of K and V that a launch reads (kernel and merge, measured at 28 batches of 1 .. 256
+    // sequences on 8, 16, 20 and 32 heads; all within 3 % of the best cut measured, microseconds):
+    //  * short launches want many items: a round of the kernel (64 tokens of 128 features, 128 of 64) is a chunk.  2 sequences of about
+    //    2900 tokens on 32 heads: 20.6 at 64 tokens, 21.6 at 128, 21.0 at 192; one of 2047 on 8: 8.0, 8.9, 9.6;
+    //  * from 300 MB on (one query head per KV head) 192 tokens: 16 of about 1500 on 32 heads 67.6, 68.2, 66.4;
+    //  * long streams want few and long ones, two workgroups per compute unit: 60 of about 1100 on 32 heads 182 at 128 tokens,
+    //    166 at 256, 165 at 384 and 512, 167 at 768.
+    // Whole sequences need no merge: up to 192 tokens, up to 384 when their heads give every compute unit an item, and in
+    // a long stream of 16 items per compute unit up to the longest chunk (256 of about 620: 397 against 403).
+    const int G = c->sh.hq / c->sh.hkv, d = c->sh.d, round = d == 128 ? 64 : 128;
+    const int64_t items = (int64_t)c->live * c->sh.hkv, bytes = live_kv_bytes(c);
+    const bool two = attn_stream_two_per_cu(G, d, bytes);
+    if (longest <= 192 || (longest <= 384 && items >= c->n_cu) || (two && longest <= kAttnMaxChunk && items >= 16 * (int64_t)c->n_cu)) { *n_chunks = c->live; return longest; }
+    int best = round;
+    if (two) best = 384;
+    else if (G == 1) best = bytes >= 300000000 && d == 128 ? 192 : round;
+    else best = bytes >= 300000000 ? 4 * round : count(128) * c->sh.hkv >= 2 * (int64_t)c->n_cu ? 128 : round;
+    *n_chunks = count(best);
     return best;
 }
 
@@ -686,6 +698,7 @@ static int run_layers(pat_ctx *c, int B, int C, int64_t n_chunks, const int32_t 
     if (n_blocks == 0) {
         for (int i = 0; i < B; ++i) aa.longest_chunks = std::max(aa.longest_chunks, (c->kv_len[i] + C) / C);
         aa.direct = aa.longest_chunks == 1;
+        aa.kv_bytes = live_kv_bytes(c);
     }
 
     for (int l = 0; l < s.NL; ++l) {

@@ -70,19 +70,19 @@ __global__ __launch_bounds__(kBlk) void admit_kernel(StateArrays st, int live, i
 // prefix followed by length and page-table lookups.
 __device__ __forceinline__ void plan_step(const StateArrays &st, int B, int C)
 {
-    __shared__ int s_start[kBlk + 1];
-    const int i = threadIdx.x;
+    __shared__ int s_start[kBlk + 1], s_len[kBlk];
+    const int i = threadIdx.x, lgP = __builtin_ctz(st.P);  // a power of two
+    const int n_free = st.scalars[S_NFREE];                // requested with the lengths, not after the scans
     const int L = (i < B) ? st.kv_len[i] : 0;
     const int chunks = (i < B) ? (L + 1 + C - 1) / C : 0;
-    const int need = (i < B && (L % st.P) == 0) ? 1 : 0;
+    const int need = (i < B && (L & (st.P - 1)) == 0) ? 1 : 0;
     int tot_c, tot_p;
     const int off_c = block_exclusive_scan(chunks, tot_c);
     const int off_p = block_exclusive_scan(need, tot_p);
-    if (i < B) { st.chunk_start[i] = off_c; s_start[i] = off_c; }
+    if (i < B) { st.chunk_start[i] = off_c; s_start[i] = off_c; s_len[i] = L; }
     if (i == 0) { st.chunk_start[B] = tot_c; st.scalars[S_CHUNKS] = tot_c; s_start[B] = tot_c; }
-    const int n_free = st.scalars[S_NFREE];
     if (tot_p > n_free) { if (i == 0) st.scalars[S_ERR] = 2; return; }
-    if (need) st.page_table[(int64_t)i * st.max_pages + L / st.P] = st.free_stack[n_free - 1 - off_p];
+    if (need) st.page_table[(int64_t)i * st.max_pages + (L >> lgP)] = st.free_stack[n_free - 1 - off_p];
     __syncthreads();                                   // page-table rows and s_start are complete
     if (i == 0) st.scalars[S_NFREE] = n_free - tot_p;
     const int n_rec = min(tot_c, st.max_chunks);       // the host checked the count against the workspace
@@ -90,10 +90,10 @@ __device__ __forceinline__ void plan_step(const StateArrays &st, int B, int C)
         int lo = 0, hi = B;                            // largest b with s_start[b] <= ce
         while (hi - lo > 1) { const int mid = (lo + hi) >> 1; if (s_start[mid] <= ce) lo = mid; else hi = mid; }
         const int b = lo, t0 = (ce - s_start[b]) * C;
-        const int n = st.kv_len[b] + 1;
+        const int n = s_len[b] + 1;
         const int cnt = min(n - t0, C);
         const int32_t *pt = st.page_table + (int64_t)b * st.max_pages;
-        const int p0 = t0 / st.P, plast = (t0 + cnt - 1) / st.P;
+        const int p0 = t0 >> lgP, plast = (t0 + cnt - 1) >> lgP;
         int4 m0 = make_int4(b, t0, cnt, 0), m1;
         m1.x = pt[p0]; m1.y = pt[min(p0 + 1, plast)]; m1.z = pt[min(p0 + 2, plast)]; m1.w = pt[min(p0 + 3, plast)];
         reinterpret_cast<int4 *>(st.chunk_meta)[2 * (int64_t)ce] = m0;
@@ -105,13 +105,14 @@ __global__ __launch_bounds__(kBlk) void plan_step_kernel(StateArrays st, int B, 
 
 // The plan in workgroup 0 and the embedding of row b (see embed_stats_row) in workgroup 1 + b: neither needs the other,
 // and one launch less is 4 us of a step that the smallest calls do in 80 (8 sequences of the tiny configuration).
-__global__ __launch_bounds__(kBlk) void plan_embed_kernel(StateArrays st, int B, int C, const uint16_t *table, int H, const uint16_t *gains,
-                                                          float *x, float *stats, uint4 *pk_hi, uint4 *pk_lo)
+// The embedding's arguments lead: they are in registers when a wave starts (see gemm_xs_kernel).
+__global__ __launch_bounds__(kBlk) void plan_embed_kernel(const uint16_t *table, const int32_t *tok, const uint16_t *gains, float *x, float *stats, uint4 *pk_hi, uint4 *pk_lo,
+                                                          int H, int B, int C, StateArrays st)
 {
     __shared__ float part[kEmbedThreads / 64];
     if (blockIdx.x == 0) { plan_step(st, B, C); return; }
     if (threadIdx.x >= kEmbedThreads) return;             // whole waves: the others' barrier does not count them
-    embed_stats_row(table, H, st.tok, gains, blockIdx.x - 1, x, stats, pk_hi, pk_lo, part);
+    embed_stats_row(table, H, tok, gains, blockIdx.x - 1, x, stats, pk_hi, pk_lo, part);
 }
 
 // Chunk prefix and chunk records for R rows that are positions of slots (prefill: row i is the token
@@ -195,29 +196,30 @@ __global__ __launch_bounds__(kBlk) void argmax_kernel(const float *logits, int n
 
 struct ReportDev { int32_t live, n_fin; int64_t sum_ctx; int32_t n_free, step; };
 
-__global__ __launch_bounds__(kBlk) void finish_kernel(StateArrays st, const int32_t *next_tok, int B, int eos,
-                                                      ReportDev *rep)
+// Sixteen words of leading arguments: what the rows need is in registers when the workgroup starts (see gemm_xs_kernel).
+__global__ __launch_bounds__(kBlk) void finish_kernel(const int32_t *next_tok, int32_t *gen, int32_t *kv_len, const int32_t *target, int32_t *tok, int32_t *fin, int B, int eos,
+                                                      int32_t *scalars, ReportDev *rep)
 {
     __shared__ int s_fin;
     __shared__ unsigned long long s_ctx;
-    if (threadIdx.x == 0) { s_fin = 0; s_ctx = 0; }
+    int step = 0, n_free = 0;
+    if (threadIdx.x == 0) { s_fin = 0; s_ctx = 0; step = scalars[S_STEP] + 1; n_free = scalars[S_NFREE]; }     // requested with the rows, not after them
     __syncthreads();
     const int i = threadIdx.x;
     if (i < B) {
         const int t = next_tok[i];
-        const int g = st.gen[i] + 1, L = st.kv_len[i] + 1;
-        const int f = (g >= st.target[i]) || (eos >= 0 && t == eos);
-        st.tok[i] = t; st.gen[i] = g; st.kv_len[i] = L; st.fin[i] = f;
+        const int g = gen[i] + 1, L = kv_len[i] + 1;
+        const int f = (g >= target[i]) || (eos >= 0 && t == eos);
+        tok[i] = t; gen[i] = g; kv_len[i] = L; fin[i] = f;
         if (f) atomicAdd(&s_fin, 1);                       // integer sums: order does not matter
         atomicAdd(&s_ctx, (unsigned long long)L);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        st.scalars[S_NFIN] = s_fin;
-        *reinterpret_cast<int64_t *>(st.scalars + S_SUMCTX) = (int64_t)s_ctx;
-        const int step = st.scalars[S_STEP] + 1;
-        st.scalars[S_STEP] = step;
-        if (rep) { rep->live = B; rep->n_fin = s_fin; rep->sum_ctx = (int64_t)s_ctx; rep->n_free = st.scalars[S_NFREE]; rep->step = step; }
+        scalars[S_NFIN] = s_fin;
+        *reinterpret_cast<int64_t *>(scalars + S_SUMCTX) = (int64_t)s_ctx;
+        scalars[S_STEP] = step;
+        if (rep) { rep->live = B; rep->n_fin = s_fin; rep->sum_ctx = (int64_t)s_ctx; rep->n_free = n_free; rep->step = step; }
     }
 }
 
@@ -403,7 +405,7 @@ hipError_t launch_plan_step(const StateArrays &st, int B, int chunk_tokens, hipS
 hipError_t launch_plan_embed(const StateArrays &st, int B, int chunk_tokens, const uint16_t *table, int H, const uint16_t *gains, float *x,
                              float *stats, uint4 *pk_hi, uint4 *pk_lo, hipStream_t s)
 {
-    plan_embed_kernel<<<1 + B, kBlk, 0, s>>>(st, B, chunk_tokens, table, H, gains, x, stats, pk_hi, pk_lo);
+    plan_embed_kernel<<<1 + B, kBlk, 0, s>>>(table, st.tok, gains, x, stats, pk_hi, pk_lo, H, B, chunk_tokens, st);
     return hipGetLastError();
 }
 
@@ -429,7 +431,7 @@ hipError_t launch_argmax(const float *logits, int B, int n, int base, int32_t *o
 
 hipError_t launch_finish(const StateArrays &st, const int32_t *next_tok, int B, int eos, void *report_dev, hipStream_t s)
 {
-    finish_kernel<<<1, kBlk, 0, s>>>(st, next_tok, B, eos, reinterpret_cast<ReportDev *>(report_dev));
+    finish_kernel<<<1, kBlk, 0, s>>>(next_tok, st.gen, st.kv_len, st.target, st.tok, st.fin, B, eos, st.scalars, reinterpret_cast<ReportDev *>(report_dev));
     return hipGetLastError();
 }
 

@@ -97,3 +97,47 @@ def test_chunks_of_large_scores_merge_as_one(hq, hkv, d):
     err = float(np.max(np.abs(out[0] - out[1])) / out[0].std())
     print("merge against one chunk:", err, flush=True)
     assert err <= 2.0 ** -15
+
+
+@pytest.mark.parametrize("heads,n,longest,chunk", [
+    (16, 40, 1290, 192),           # 300 MB of K and V: chunks of three rounds
+    (16, 61, 1420, 384),           # 500 MB: two workgroups per compute unit, chunks past a record's four pages
+    (32, 130, 700, 0),             # 16 items per compute unit: whole sequences
+])
+def test_long_streams_equal_the_same_sequences_in_a_short_batch(heads, n, longest, chunk):
+    """Rows of a batch whose K and V are hundreds of megabytes against the same sequences alone, which are cut into chunks of one
+    round.  The sums' order differs, and the projections' kernels (more than 32 rows, at most 32): both are within 1e-4 of the
+    logits' scale of float64 in their own tests."""
+    import paper_2605_23945_amd as pat
+    d, page = 128, 64
+    shard = pi.shard_of(pi.ModelShape(1, 256, heads, heads, d, 512, 512), 1, 0)
+    lens = np.array([longest - (i * longest) // (2 * n) for i in range(n)], np.int32)
+    lens[[0, n - 1]] = lens[[n - 1, 0]]
+    off = np.concatenate(([0], np.cumsum(lens)))
+    g = torch.Generator(device=DEV).manual_seed(n)
+    kv = torch.empty(1, 2, heads, int(off[-1]), d, dtype=torch.bfloat16, device=DEV).normal_(0, 1, generator=g)
+    weights, final = pi.layer_weights(shard, 0, device=DEV), pi.final_weights(shard, device=DEV)
+    final = dict(final, embed=pi.embedding_table(shard, device=DEV))
+
+    def step(slots):
+        m = len(slots)
+        ls = lens[slots]
+        dec = pat.Decoder(pat.make_cfg(shard, m, longest + 4, int(ls.sum()) + 2 * page * m, page), DEV)
+        dec.pat_load_layer(0, weights)
+        dec.pat_load_final(final)
+        dec.pat_decode_admit(list(range(m)), [int(3 + 7 * s) % 512 for s in slots], ls, [4] * m)
+        buf = kv if m == n else torch.cat([kv[:, :, :, off[s]: off[s + 1]] for s in slots], dim=3).contiguous()
+        dec.pat_kv_inject(list(range(m)), buf, layer0=0)
+        cut = tuple(int(c) for c in dec.pat_attention_cut()["step"])
+        logits = torch.empty(m, shard.vocab, device=DEV)
+        dec.pat_decode_step(False, torch.empty(m, dtype=torch.int32, device=DEV), logits)
+        out = logits.double().cpu().numpy()
+        dec.close()
+        return cut, out
+
+    cut, out = step(list(range(n)))
+    assert cut == ((longest + 1, n) if chunk == 0 else (chunk, int(sum((l + chunk) // chunk for l in lens))))
+    rows = [0, n // 2, n - 1]
+    short, ref = step(rows)
+    assert short[0] == 64
+    assert np.max(np.abs(out[rows] - ref)) <= 2e-4 * float(ref.std())
