@@ -8,11 +8,12 @@
 // touching a register.  One workgroup barrier per k-step; every row tile's step is one LDS read, its share of the k-step's
 // requests and 2 RB matrix instructions (high and low halves), so requests, LDS reads and products interleave evenly.
 //
-// Sums: every XD + 1 k-steps the accumulators are added to a second set and start again from zero.  One chain over all of K
-// rounds 2 K / 32 times at the size of the result; against float64 sums of the same operands that gave 5.7e-7 (2-norm,
-// K = 4096), 8.1e-7 (K = 8192); in blocks it is 1.4e-7 .. 1.9e-7 at every K up to 11008, no more than the K slices of the
-// kernel it replaces gave (1.4e-7 .. 4.0e-7).  The second set is why a wave takes at most two batch tiles: 12 x 3, 8 x 4 and
-// 12 x 4 tiles have no registers for it.  The additions cost 1-3 % of a launch.
+// Sums: every XD + 1 k-steps a row tile's accumulators are added to a second set and start again from zero.  One chain over all
+// of K rounds 2 K / 32 times at the size of the result; against float64 sums of the same operands that gave 5.7e-7 (2-norm,
+// K = 4096), 8.1e-7 (K = 8192); in blocks it is 1.4e-7 .. 1.9e-7 at every K up to 11008.  The second set is why a wave takes at
+// most two batch tiles.  The row tiles start their chains at different k-steps, and a tile's additions are spread between the
+// products of the others: all tiles at once, in one k-step of the ring, they held up the matrix cores for 90 (8 x 2 tiles) to
+// 180 (12 x 2) clocks per k-step.
 //
 // More than 128 rows are cut into NG equal groups in ONE launch: the groups of a row range are neighbours on one XCD and
 // share its weight stream in L2.  That is faster than one group of up to 256 rows with one set of sums (22016 x 4096 at 256
@@ -20,8 +21,15 @@
 // against 72) and of passes of about 1000 (1024 rows: 325 against 310; 7168 x 8192 213 against 191).
 //
 // What bounds it: up to 128 rows the weight stream from HBM (the per-k-step requests of all workgroups in flight,
-// up to 130 KB per compute unit, are what hides its latency); at 256 rows the chip's power limit (random operands run
-// 25-40 % slower than all-zero ones at the same instruction stream).  Measured against the kernel it replaces (batch
+// up to 130 KB per compute unit, are what hides its latency).  From 256 rows on the chip's power limit: with random operands
+// the clock falls to 1.8 .. 2.0 GHz (all-zero ones: 2.4), and what the operands' way from L2 and through LDS takes of
+// the power is missing at the matrix cores.  Between, the issue of the one wave that a SIMD has: a product of 16 clocks leaves
+// room for one other instruction, so the loop has 57 others to 32 products (8 x 2 tiles) where it had 75; with one batch tile
+// per wave LDS (4 waves read every weight: 125 bytes per clock at the products' rate).  Clocks per k-step with all-zero operands, of
+// products / alone without loads / in all: 8 x 2 tiles 512 / 599 / 791, 12 x 2 768 / 899 / 1109, 12 x 1 384 / 445 / 768.
+// Staging the weights through registers into LDS, with exact waits, took the same time (8 x 2) or 10 % more (12 x 2); other
+// cache policies of the weights' loads changed nothing.
+// Measured against the kernel it replaced (batch
 // fragments staged through registers into LDS, two k-steps ahead; same box, reduction included), microseconds:
 //     rows          60            101           180           256           1024
 //     22016 x 4096  52.1 -> 46.1  73.2 -> 57.4  88.4 -> 82.5  112  -> 84.6  449  -> 325
@@ -33,6 +41,7 @@
 // kernel adds them in slice order and runs the epilogue, so results never depend on timing.
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 #include "gemm_dev.h"
 
 namespace pat {
@@ -51,97 +60,117 @@ template <> struct WideRings<8, 2> { static constexpr int XD = 7, WS = 11; };
 template <> struct WideRings<12, 2> { static constexpr int XD = 5, WS = 9; };
 template <int RA, int RB> constexpr int wide_lds_bytes() { return WideRings<RA, RB>::WS * RA * 1024; }
 
+// elements of a wave's row tile that are added to the second sums after j of the RA - 1 other row tiles
+__host__ __device__ constexpr int wide_folded(int RA, int RB, int j) { return j * 4 * RB / (RA - 1); }
+template <int N, class F, int... I> __device__ __forceinline__ void static_for_i(F &&f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F> __device__ __forceinline__ void static_for(F &&f) { static_for_i<N>(f, std::make_integer_sequence<int, N>{}); }
+
 // MODE kPartial: the tile's sums go to a.part[kb][b][n_tiles * 16] (kb = K slice); otherwise (one slice) the epilogue runs here.
 constexpr int kPartial = -1;
+// The leading arguments are in registers when a wave starts (see gemm_xs_kernel): 14 words, the most that fit.  ng_gb: groups
+// and rows of a group (<< 16); ks_qr: k-steps of a slice and how many slices have one more (<< 24).
 template <int RA, int RB, int MODE>
-__global__ __launch_bounds__(256) void gemm_wide_kernel(GemmArgs a)
+__global__ __launch_bounds__(256) void gemm_wide_kernel(const uint4 *w, const uint4 *xhi, const uint4 *xlo, int KS, int B, uint32_t total, uint32_t ng_gb, uint32_t Rg, uint32_t ks_qr,
+                                                        int tiles_q, int tiles_r, GemmArgs a)
 {
+    const uint32_t NG = ng_gb & 0xFFFFu;
+    const int GB = ng_gb >> 16, ks_q = ks_qr & 0xFFFFFFu, ks_r = ks_qr >> 24;
+    a.B = B;
     constexpr int XD = WideRings<RA, RB>::XD, WS = WideRings<RA, RB>::WS;
     constexpr int CW = RA / 4, CX = 2 * RB, PER = CW + CX;      // requests per wave and k-step: weights, batch fragments
     constexpr int U = XD + 1, DA = WS - 1, PF = 4;              // DA: k-steps the weights are requested ahead; PF: LDS reads in flight
     static_assert(RA % 4 == 0 && DA >= XD + 1 && (DA - 2) * PER <= 63, "the hand-counted waits fit the counter");
     extern __shared__ u32x4_t wring[];                          // [WS][RA][64]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int KS = a.KS;
     // Workgroups are dealt round robin to the eight XCDs (blockIdx % 8); giving each XCD consecutive work items, slice
     // major, lets its workgroups share one K slice of the activations in their L2.
-    const int id = blockIdx.x, total = a.Kb * a.Rg * a.NG;
-    const int item = (id & 7) * (total >> 3) + min(id & 7, total & 7) + (id >> 3);
-    const int part = item / a.NG, grp = item - part * a.NG, kb = part / a.Rg, rg = part - kb * a.Rg;
-    const int b0 = grp * a.GB, nb = min(a.GB, a.B - b0);        // this workgroup's batch rows b0 .. b0 + nb - 1
-    const int ks0 = (int)((int64_t)kb * KS / a.Kb), n = (int)((int64_t)(kb + 1) * KS / a.Kb) - ks0;
-    const int rt0 = (int)((int64_t)rg * a.n_tiles / a.Rg), rt1 = (int)((int64_t)(rg + 1) * a.n_tiles / a.Rg);
+    const uint32_t id = blockIdx.x, item = (id & 7) * (total >> 3) + min(id & 7, total & 7) + (id >> 3);
+    const uint32_t part = item / NG, grp = item - part * NG, kb = part / Rg, rg = part - kb * Rg;
+    const int b0 = grp * GB, nb = min(GB, B - b0);              // this workgroup's batch rows b0 .. b0 + nb - 1
+    // its k-steps and row tiles: the first ks_r slices (tiles_r ranges) have one more than the others
+    const int ks0 = kb * ks_q + min((int)kb, ks_r), n = ks_q + ((int)kb < ks_r ? 1 : 0);
+    const int rt0 = rg * tiles_q + min((int)rg, tiles_r), rt1 = rt0 + tiles_q + ((int)rg < tiles_r ? 1 : 0);
     const int bt0 = b0 >> 4, bt_last = (nb - 1) >> 4;
     const uint32_t lds0 = lds_offset(wring);
 
     // All requests are unconditional, from clamped (always valid) addresses, so that every wave issues the same number
     // per k-step: row tiles past the range repeat its last one and batch tiles past the live batch the last live one
-    // (neither is stored), k-steps past the slice repeat its last one (never multiplied).
-    const u32x4_t *wsrc[CW], *xsrc[CX];
+    // (neither is stored), k-steps past the slice repeat its last one (never multiplied).  One wave per SIMD issues
+    // everything, so what stands between its matrix instructions is kept short: bases in scalar registers, one offset per
+    // operand and k-step (vw, vx) that stops at the slice's last k-step, ring slots as byte offsets.
+    const char *wsrc[CW], *xsrc[CX];
 #pragma unroll
-    for (int i = 0; i < CW; ++i) wsrc[i] = reinterpret_cast<const u32x4_t *>(a.w) + ((int64_t)min(rt0 + wave * CW + i, rt1 - 1) * KS + ks0) * 64;
+    for (int i = 0; i < CW; ++i) wsrc[i] = reinterpret_cast<const char *>(w) + (uint64_t)(uint32_t)(min(rt0 + wave * CW + i, rt1 - 1) * KS + ks0) * 1024;
 #pragma unroll
     for (int i = 0; i < CX; ++i)
-        xsrc[i] = reinterpret_cast<const u32x4_t *>(i / RB ? a.xlo : a.xhi) + ((int64_t)(bt0 + min(wave * RB + i % RB, bt_last)) * KS + ks0) * 64;
-    int s_req = 0, s_cur = 0;                                   // ring slots: of the next request, of the current k-step
-    auto request_w = [&](int t, int i) { load_to_lds_stream(wsrc[i] + min(t, n - 1) * 64, lane * 16, lds0 + (s_req * RA + wave * CW + i) * 1024); };
-    auto request_x = [&](int t, int i) -> u32x4_t { return *(xsrc[i] + min(t, n - 1) * 64 + lane); };
+        xsrc[i] = reinterpret_cast<const char *>(i / RB ? xlo : xhi) + (uint64_t)(uint32_t)((bt0 + min(wave * RB + i % RB, bt_last)) * KS + ks0) * 1024;
+    const uint32_t lane16 = lane * 16, k_last = (uint32_t)(n - 1) * 1024, ring = lds0 + (uint32_t)(wave * CW) * 1024;
+    uint32_t kw = 0, kx = 0;                                    // byte offsets of the next requests' k-steps inside the slice
+    uint32_t at_req = 0, at_cur = 0;                            // ring slots (bytes): of the next request, of the current k-step
+    constexpr uint32_t SLOT = RA * 1024, END = WS * SLOT;
+    auto request_w = [&](int i) { load_to_lds_stream(wsrc[i], lane16 + kw, ring + at_req + i * 1024); };
+    auto request_x = [&](int i) -> u32x4_t { return *reinterpret_cast<const u32x4_t *>(xsrc[i] + (lane16 + kx)); };
 
     floatx4_t acc[RA][RB], sum[RA][RB];
 #pragma unroll
     for (int ra = 0; ra < RA; ++ra)
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) acc[ra][rb] = sum[ra][rb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-    u32x4_t x[U][CX], w[PF];
+    u32x4_t x[U][CX], wf[PF];
     // the requests of the k-steps -DA .. -1, in the order the loop would have issued them
 #pragma unroll
     for (int s = -DA; s < 0; ++s) {
 #pragma unroll
-        for (int i = 0; i < CW; ++i) request_w(s + DA, i);
-        ++s_req;
+        for (int i = 0; i < CW; ++i) request_w(i);
+        at_req += SLOT; kw = min(kw + 1024, k_last);
         if (s + XD >= 0) {
 #pragma unroll
-            for (int i = 0; i < CX; ++i) x[s + XD][i] = request_x(s + XD, i);
+            for (int i = 0; i < CX; ++i) x[s + XD][i] = request_x(i);
+            kx = min(kx + 1024, k_last);
         }
         __builtin_amdgcn_sched_barrier(0);
     }
     // W(0), W(1): at least (DA - 2) CW younger requests are outstanding or done
     asm volatile("s_waitcnt vmcnt(%c0)\n\ts_barrier" ::"i"((DA - 2) * CW) : "memory");
 #pragma unroll
-    for (int p = 0; p < PF - 1; ++p) w[p] = wring[p * 64 + lane];
+    for (int p = 0; p < PF - 1; ++p) wf[p] = wring[p * 64 + lane];
 
     // One k-step.  The wait covers this wave's part of W(t + 1) (its requests are followed by those of DA - 2 whole
     // k-steps); after the barrier all parts are in LDS and every wave is done with the slot of W(t - 1), which takes W(t + DA).
-    auto step = [&](int t, const u32x4_t (&xc)[CX], u32x4_t (&xn)[CX], auto fold) {
+    // FR: rows r with r % U == u start a new chain in this k-step; their sums so far were added to `sum` since their last products.
+    auto step = [&](auto uu) {
+        constexpr int u = decltype(uu)::value;
+        const u32x4_t (&xc)[CX] = x[u];
+        u32x4_t (&xn)[CX] = x[(u + XD) % U];
         asm volatile("s_waitcnt vmcnt(%c0)\n\ts_barrier" ::"i"((DA - 2) * PER) : "memory");
-        const int s_nxt = s_cur + 1 == WS ? 0 : s_cur + 1;
-        const u32x4_t *cur = wring + s_cur * RA * 64 + lane, *nxt = wring + s_nxt * RA * 64 + lane;
+        const uint32_t at_nxt = at_cur + SLOT == END ? 0 : at_cur + SLOT;
+        const char *cur = reinterpret_cast<const char *>(wring) + (at_cur + lane16), *nxt = reinterpret_cast<const char *>(wring) + (at_nxt + lane16);
 #pragma unroll
         for (int r = 0; r < RA; ++r) {
 #pragma unroll
-            for (int v = (r * PER) / RA; v < ((r + 1) * PER) / RA; ++v) { if (v < CW) request_w(t + DA, v); else xn[v - CW] = request_x(t + XD, v - CW); }
-            w[(r + PF - 1) % PF] = r + PF - 1 < RA ? cur[(r + PF - 1) * 64] : nxt[(r + PF - 1 - RA) * 64];
-            if constexpr (decltype(fold)::value) {
+            for (int v = (r * PER) / RA; v < ((r + 1) * PER) / RA; ++v) { if (v < CW) request_w(v); else xn[v - CW] = request_x(v - CW); }
+            wf[(r + PF - 1) % PF] = *reinterpret_cast<const u32x4_t *>(r + PF - 1 < RA ? cur + (r + PF - 1) * 1024 : nxt + (r + PF - 1 - RA) * 1024);
 #pragma unroll
-                for (int rb = 0; rb < RB; ++rb) { sum[r][rb] += acc[r][rb]; acc[r][rb] = floatx4_t{0.f, 0.f, 0.f, 0.f}; }
+            for (int i = 0; i < CX; ++i) acc[r][i % RB] = mfma16(wf[r % PF], xc[i], i < RB && r % U == u ? floatx4_t{0.f, 0.f, 0.f, 0.f} : acc[r][i % RB]);
+            // the chains that restart in the next occurrence of their row: a share of their elements after every row
+#pragma unroll
+            for (int f = 0; f < RA; ++f) {
+                const bool here = r > f ? f % U == (u + 1) % U : f % U == u;            // since f's products of the k-step before
+                if (r == f || !here) continue;
+                const int j = r > f ? r - f - 1 : r - f - 1 + RA, lo = wide_folded(RA, RB, j), hi = wide_folded(RA, RB, j + 1);
+#pragma unroll
+                for (int e = lo; e < hi; ++e) sum[f][e / 4][e % 4] += acc[f][e / 4][e % 4];
             }
-#pragma unroll
-            for (int i = 0; i < CX; ++i) acc[r][i % RB] = mfma16(w[r % PF], xc[i], acc[r][i % RB]);
             __builtin_amdgcn_sched_barrier(0);                  // keeps the interleaving, and every LDS read of a k-step before the next barrier
         }
-        s_cur = s_nxt; s_req = s_req + 1 == WS ? 0 : s_req + 1;
+        at_req = at_cur; at_cur = at_nxt;                       // the slot just read takes W(t + 1 + DA)
+        kw = min(kw + 1024, k_last); kx = min(kx + 1024, k_last);
     };
     int t = 0;
-    for (; t + U <= n; t += U) {
-        step(t, x[0], x[XD % U], std::true_type{});
-#pragma unroll
-        for (int u = 1; u < U; ++u) step(t + u, x[u], x[(u + XD) % U], std::false_type{});
-    }
-    if (t < n) step(t, x[0], x[XD % U], std::true_type{});
-#pragma unroll
-    for (int u = 1; u < U - 1; ++u)
-        if (t + u < n) step(t + u, x[u], x[(u + XD) % U], std::false_type{});
+    for (; t + U <= n; t += U) static_for<U>([&](auto u) { step(u); });
+    static_for<U - 1>([&](auto u) { if (t + decltype(u)::value < n) step(u); });
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // no write to LDS may be in flight when the workgroup ends
+    const int u_end = n % U;                                    // rows r with r % U == u_end: part of their last chain is in `sum` already
 
     // the epilogue's addresses are derived from a copy of the lane index that the compiler cannot see through:
     // hoisted above the loop they would occupy registers it needs
@@ -153,7 +182,9 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(GemmArgs a)
         if (rt >= rt1) continue;
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            const floatx4_t s = sum[ra][rb] + acc[ra][rb];
+            floatx4_t s = sum[ra][rb];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e] += u_end == ra % U && rb * 4 + e < wide_folded(RA, RB, RA - 1 - ra) ? 0.f : acc[ra][rb][e];
             const float4 v = make_float4(s[0], s[1], s[2], s[3]);
             const int bl = (wave * RB + rb) * 16 + (lane_e & 15), b = bl < nb ? b0 + bl : a.B, quad = lane_e >> 4;     // b == a.B: not stored
             if (MODE == kPartial) {
@@ -169,10 +200,10 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(GemmArgs a)
 template <int KB>
 __device__ __forceinline__ float4 sum_slices_n(const GemmArgs &a, int b, int q)
 {
-    const int64_t ldp = (int64_t)a.n_tiles * 16;
+    const int64_t row = (int64_t)b * a.n_tiles * 16 + q * 4, slice = (int64_t)a.B * a.n_tiles * 16;
     float4 t[KB];
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) t[kb] = *reinterpret_cast<const float4 *>(a.part + ((int64_t)kb * a.B + b) * ldp + q * 4);
+    for (int kb = 0; kb < KB; ++kb) t[kb] = *reinterpret_cast<const float4 *>(a.part + row + kb * slice);
     float4 v = t[0];
 #pragma unroll
     for (int kb = 1; kb < KB; ++kb) { v.x += t[kb].x; v.y += t[kb].y; v.z += t[kb].z; v.w += t[kb].w; }
@@ -195,71 +226,112 @@ __device__ __forceinline__ float4 sum_slices(const GemmArgs &a, int b, int q)
 // Slice sums, then the epilogue: one thread per (row tile, batch row, quad), quads fastest, then batch rows, so that a
 // wave reads 64-byte runs of 16 rows and its SwiGLU results (packed operand, 4 bytes per lane) form 256-byte runs.
 template <int MODE>
-__global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs a)
+__global__ __launch_bounds__(256) void gemm_reduce_kernel(float *part, int B, int Kb, int n_tiles, GemmArgs a)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int per_tile = a.B * 4;
-    const int rt = (int)(i / per_tile), r = (int)(i - (int64_t)rt * per_tile);
-    if (rt >= a.n_tiles) return;
+    a.part = part; a.B = B; a.Kb = Kb; a.n_tiles = n_tiles;
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x, per_tile = B * 4;      // fewer than 2^32: B rows of n_tiles x 4 quads
+    const int rt = i / per_tile, r = i - rt * per_tile;
+    if (rt >= n_tiles) return;
     const int b = r >> 2, quad = r & 3;
     gemm_epilogue<MODE>(a, rt, quad, b, sum_slices(a, b, rt * 4 + quad));
 }
 
 // Slice sums of a residual projection, y += sums, and the RMSNorm that the next projection applies to y, written as
 // its packed split-bf16 operand: one workgroup per batch row, so that the row's sum of squares is at hand without a
-// kernel (and a pass over y) of its own.  Up to 4 x 2048 features stay in registers; wider rows re-read their y.
-// A reduction and a norm launch took 7.7 + 7.2 us at 256 rows of 4096 features, 4.7 + 5.1 us at 60.
+// kernel (and a pass over y) of its own.  What bounds it is the latency of its loads: a thread requests the slices and y of
+// its KEEP x 4 features together (up to 4 x 2048 features of a row; wider rows take more rounds and re-read their y).
+// One quad after another: 9.9 us for 180 rows of 8192 features in two slices, 8.7 for 256 of 4096 in four; with them together a
+// step of the 70B TP = 8 shard at 180 rows is 7 us per layer faster.
 constexpr int kNormThreads = 512;
-__global__ __launch_bounds__(kNormThreads) void gemm_reduce_norm_kernel(GemmArgs a)
+template <int KB>
+__global__ __launch_bounds__(kNormThreads) void gemm_reduce_norm_kernel(const float *part, float *y0, const uint16_t *gains, uint4 *hi, uint4 *lo, int n_tiles, int ldy, int64_t slice,
+                                                                        int s_h, float s_eps)
 {
     constexpr int KEEP = 4;
     __shared__ float wsum[kNormThreads / 64];
-    const int b = blockIdx.x, quads = a.n_tiles * 4, KSo = a.n_tiles >> 1;
-    float *y = a.y + (int64_t)b * a.ldy;
-    float4 keep[KEEP];
+    const int b = blockIdx.x, quads = n_tiles * 4, KSo = n_tiles >> 1;
+    float4 *y = reinterpret_cast<float4 *>(y0 + (int64_t)b * ldy);
+    const float4 *p = reinterpret_cast<const float4 *>(part) + (int64_t)b * quads;
     float ss = 0.f;
-    auto take = [&](int q) {
-        float4 v = sum_slices(a, b, q);
-        const float4 c = *reinterpret_cast<const float4 *>(y + q * 4);
-        v.x += c.x; v.y += c.y; v.z += c.z; v.w += c.w;
-        *reinterpret_cast<float4 *>(y + q * 4) = v;
-        ss += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
-        return v;
-    };
+    float4 keep[KEEP];
+    uint2 gk[KEEP];
 #pragma unroll
-    for (int i = 0; i < KEEP; ++i) {
-        const int q = threadIdx.x + i * kNormThreads;
-        keep[i] = q < quads ? take(q) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    for (int q = threadIdx.x + KEEP * kNormThreads; q < quads; q += kNormThreads) (void)take(q);
+    for (int i = 0; i < KEEP; ++i) gk[i] = *reinterpret_cast<const uint2 *>(gains + min((int)threadIdx.x + i * kNormThreads, quads - 1) * 4);
+    auto round = [&](int q0, bool kept) {
+        float4 t[KEEP][KB], c[KEEP];
+#pragma unroll
+        for (int i = 0; i < KEEP; ++i) {
+            const int q = min(q0 + i * kNormThreads, quads - 1);               // past the row: a clamped, unused load
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) t[i][kb] = p[q + kb * slice];
+            c[i] = y[q];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < KEEP; ++i) {
+            const int q = q0 + i * kNormThreads;
+            if (q >= quads) break;
+            float4 v = t[i][0];
+#pragma unroll
+            for (int kb = 1; kb < KB; ++kb) { v.x += t[i][kb].x; v.y += t[i][kb].y; v.z += t[i][kb].z; v.w += t[i][kb].w; }
+            v.x += c[i].x; v.y += c[i].y; v.z += c[i].z; v.w += c[i].w;
+            y[q] = v;
+            ss += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
+            if (kept) keep[i] = v;
+        }
+    };
+    round(threadIdx.x, true);
+    for (int q0 = threadIdx.x + KEEP * kNormThreads; q0 < quads; q0 += KEEP * kNormThreads) round(q0, false);
     ss = wave_sum(ss);
     if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = ss;
     __syncthreads();
     float tot = 0.f;
 #pragma unroll
     for (int w = 0; w < kNormThreads / 64; ++w) tot += wsum[w];
-    const float inv = 1.0f / sqrtf(tot / (float)a.s_h + a.s_eps);
-    auto emit = [&](int q, float4 v) {
-        const uint2 gv = *reinterpret_cast<const uint2 *>(a.ngains + q * 4);
+    const float inv = 1.0f / sqrtf(tot / (float)s_h + s_eps);
+    auto emit = [&](int q, float4 v, uint2 gv) {
         uint16_t h[4], l[4];
         split_bf16(v.x * inv * bf16lo(gv.x), h[0], l[0]); split_bf16(v.y * inv * bf16hi(gv.x), h[1], l[1]);
         split_bf16(v.z * inv * bf16lo(gv.y), h[2], l[2]); split_bf16(v.w * inv * bf16hi(gv.y), h[3], l[3]);
         const int64_t off = packed_elem_offset(b, q * 4, KSo);
-        *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(a.npk_hi) + off) = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
-        *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(a.npk_lo) + off) = make_uint2((uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16));
+        *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(hi) + off) = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
+        *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(lo) + off) = make_uint2((uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16));
     };
 #pragma unroll
     for (int i = 0; i < KEEP; ++i) {
         const int q = threadIdx.x + i * kNormThreads;
-        if (q < quads) emit(q, keep[i]);
+        if (q < quads) emit(q, keep[i], gk[i]);
     }
-    for (int q = threadIdx.x + KEEP * kNormThreads; q < quads; q += kNormThreads) emit(q, *reinterpret_cast<const float4 *>(y + q * 4));
+    for (int q = threadIdx.x + KEEP * kNormThreads; q < quads; q += kNormThreads) emit(q, y[q], *reinterpret_cast<const uint2 *>(gains + q * 4));
+}
+
+template <int KB>
+hipError_t launch_reduce_norm_t(const GemmArgs &a, hipStream_t s)
+{
+    gemm_reduce_norm_kernel<KB><<<(unsigned)a.B, kNormThreads, 0, s>>>(a.part, a.y, a.ngains, a.npk_hi, a.npk_lo, a.n_tiles, a.ldy, (int64_t)a.B * a.n_tiles * 4, a.s_h, a.s_eps);
+    return hipGetLastError();
+}
+
+hipError_t launch_reduce_norm(const GemmArgs &a, hipStream_t s)
+{
+    switch (a.Kb) {                                             // max_slices() is at most 8
+    case 1: return launch_reduce_norm_t<1>(a, s);
+    case 2: return launch_reduce_norm_t<2>(a, s);
+    case 3: return launch_reduce_norm_t<3>(a, s);
+    case 4: return launch_reduce_norm_t<4>(a, s);
+    case 5: return launch_reduce_norm_t<5>(a, s);
+    case 6: return launch_reduce_norm_t<6>(a, s);
+    case 7: return launch_reduce_norm_t<7>(a, s);
+    default: return launch_reduce_norm_t<8>(a, s);
+    }
 }
 
 template <int RA, int RB, int MODE>
 hipError_t launch_wide_t(const GemmArgs &a, hipStream_t s)
 {
-    gemm_wide_kernel<RA, RB, MODE><<<(unsigned)(a.Rg * a.Kb * a.NG), 256, wide_lds_bytes<RA, RB>(), s>>>(a);
+    const unsigned total = (unsigned)(a.Rg * a.Kb * a.NG);
+    gemm_wide_kernel<RA, RB, MODE><<<total, 256, wide_lds_bytes<RA, RB>(), s>>>(a.w, a.xhi, a.xlo, a.KS, a.B, total, (uint32_t)a.NG | (uint32_t)a.GB << 16, (uint32_t)a.Rg,
+                                                                                (uint32_t)(a.KS / a.Kb) | (uint32_t)(a.KS % a.Kb) << 24, a.n_tiles / a.Rg, a.n_tiles % a.Rg, a);
     return hipGetLastError();
 }
 
@@ -381,15 +453,14 @@ hipError_t launch_gemm_wide(const GemmArgs &a0, const GemmPlan &p, int mode, hip
         return hipSuccess;
     }
     if (mode == kGemmAccum && a.ngains != nullptr) {
-        gemm_reduce_norm_kernel<<<(unsigned)a.B, kNormThreads, 0, s>>>(a);
-        return hipGetLastError();
+        return launch_reduce_norm(a, s);
     }
     const unsigned blocks = (unsigned)(((int64_t)a.B * a.n_tiles * 4 + 255) / 256);
     switch (mode) {
-    case kGemmStore: gemm_reduce_kernel<kGemmStore><<<blocks, 256, 0, s>>>(a); break;
-    case kGemmAccum: gemm_reduce_kernel<kGemmAccum><<<blocks, 256, 0, s>>>(a); break;
-    case kGemmQKV: gemm_reduce_kernel<kGemmQKV><<<blocks, 256, 0, s>>>(a); break;
-    default: gemm_reduce_kernel<kGemmSwiGLU><<<blocks, 256, 0, s>>>(a); break;
+    case kGemmStore: gemm_reduce_kernel<kGemmStore><<<blocks, 256, 0, s>>>(a.part, a.B, a.Kb, a.n_tiles, a); break;
+    case kGemmAccum: gemm_reduce_kernel<kGemmAccum><<<blocks, 256, 0, s>>>(a.part, a.B, a.Kb, a.n_tiles, a); break;
+    case kGemmQKV: gemm_reduce_kernel<kGemmQKV><<<blocks, 256, 0, s>>>(a.part, a.B, a.Kb, a.n_tiles, a); break;
+    default: gemm_reduce_kernel<kGemmSwiGLU><<<blocks, 256, 0, s>>>(a.part, a.B, a.Kb, a.n_tiles, a); break;
     }
     return hipGetLastError();
 }
