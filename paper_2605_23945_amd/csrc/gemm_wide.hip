@@ -58,6 +58,7 @@ template <> struct WideRings<12, 1> { static constexpr int XD = 7, WS = 11; };
 template <> struct WideRings<4, 2> { static constexpr int XD = 7, WS = 12; };
 template <> struct WideRings<8, 2> { static constexpr int XD = 7, WS = 11; };
 template <> struct WideRings<12, 2> { static constexpr int XD = 5, WS = 9; };
+template <> struct WideRings<16, 2> { static constexpr int XD = 5, WS = 8; };
 template <int RA, int RB> constexpr int wide_lds_bytes() { return WideRings<RA, RB>::WS * RA * 1024; }
 
 // elements of a wave's row tile that are added to the second sums after j of the RA - 1 other row tiles
@@ -347,12 +348,13 @@ hipError_t launch_wide_modes(const GemmArgs &a, int mode, hipStream_t s)
     }
 }
 
-// mode: kPartial, kGemmStore, or (8 and 12 row tiles) any other epilogue in the kernel
+// mode: kPartial, kGemmStore, or (8, 12 and 16 row tiles) any other epilogue in the kernel
 template <int RB>
 hipError_t launch_wide_rb(const GemmArgs &a, int RA, int mode, hipStream_t s)
 {
     if (RA == 4) return mode == kPartial ? launch_wide_t<4, RB, kPartial>(a, s) : launch_wide_t<4, RB, kGemmStore>(a, s);
     if (RA == 8) return launch_wide_modes<8, RB>(a, mode, s);
+    if constexpr (RB == 2) { if (RA == 16) return launch_wide_modes<16, RB>(a, mode, s); }
     return launch_wide_modes<12, RB>(a, mode, s);
 }
 
@@ -394,21 +396,24 @@ int max_slices(int n_tiles, int KS, int n_cu)
 
 hipError_t gemm_wide_prepare_device()
 {
-    const hipError_t e = wide_set_lds_limits<1>();
-    return e == hipSuccess ? wide_set_lds_limits<2>() : e;
+    hipError_t e = wide_set_lds_limits<1>();
+    if (e == hipSuccess) e = wide_set_lds_limits<2>();
+    return e == hipSuccess ? wide_set_lds_limit_modes<16, 2>() : e;
 }
 
-// Row tiles per workgroup (4, 8, 12), batch tiles per wave (1, 2: groups of up to 64 or 128 rows) and K slices, by a cost
-// model fitted to 6910 measured launches: every cut of 17 projections (1280..32000 features, K 1024..11008) at 16 live
-// batches of 33..1024 rows, the residual ones with the RMSNorm that follows (rms error 7 %; the cut it picks is within 3 % of
-// the best measured in 91 % of the 272 cases, within 10 % in 97 %, 0.8 % off on average).  A launch takes 9.1 us plus its
-// k-steps, each the longest of the matrix products (0.0215 us per tile pair), the operand fetch (0.0194 us per KiB of weights
-// and 0.0104 per KiB of batch fragments of a workgroup) and the weight stream (0.037 us per KiB and workgroup with all 256
-// busy, less where groups share it).  Partial sums cost 0.88 us per MB; a following norm 7.4 us and 0.87 us per MB of
-// results as a launch of its own, 2.4 us and 0.15 per MB of results within the reduction of the slices.  Few row
+// Row tiles per workgroup (4, 8, 12, and 16 with two batch tiles per wave), batch tiles per wave (1, 2: groups of up to 64 or
+// 128 rows) and K slices, by a cost model fitted to 8039 measured launches: every cut of 17 projections (1280..32000 features,
+// K 1024..11008) at 16 live batches of 33..1024 rows, the residual ones with the RMSNorm that follows (rms error 7 %; the cut it
+// picks is 0.9 % off the best measured on average, within 3 % in 90 % of the 272 cases, within 10 % in 96 %).  A launch takes
+// 8.7 us plus its k-steps, each the longest of the matrix products (0.067 us and 0.0183 per tile pair), the operand fetch (0.0194
+// us per KiB of weights and 0.0105 per KiB of batch fragments of a workgroup) and the weight stream (0.038 us per KiB and
+// workgroup with all 256 busy, less where groups share it).  Partial sums cost 0.83 us per MB; a following norm 6.8 us and 0.89 us
+// per MB of results as a launch of its own, 2.2 us and 0.24 per MB of results within the reduction of the slices.  16 row
+// tiles read the least per product and need one round of workgroups where 8 need two: 7168 x 8192 at 1024 rows 184 us against
+// 207, 8192 x 3584 92 against 105, 8192 x 1024 35 against 41.  Few row
 // tiles per workgroup and few slices suit narrow projections (1280 x 8192, 64 rows: 4 tiles 16.9 us, 8 tiles 20.3), many
 // tiles wide ones (22016 x 4096, 256 rows: 12 tiles 86 us, 8 tiles 115).  A projection without scratch for partial sums takes
-// the 8- or 12-tile kernels, which exist with every epilogue; part_bytes bounds the slices (B rows of partial sums each).
+// the kernels of 8 tiles and more, which exist with every epilogue; part_bytes bounds the slices (B rows of partial sums each).
 void plan_wide(int n_tiles, int KS, int B, int n_cu, int64_t part_bytes, bool norm, GemmPlan &p)
 {
     const int kb_max = max_slices(n_tiles, KS, n_cu);
@@ -416,17 +421,17 @@ void plan_wide(int n_tiles, int KS, int B, int n_cu, int64_t part_bytes, bool no
     for (int RB = 1; RB <= 2; ++RB) {
         const int ng = (B + 64 * RB - 1) / (64 * RB), gb = ((B + ng - 1) / ng + 15) / 16 * 16;
         if (RB == 2 && gb <= 64) continue;                                         // as with one tile per wave
-        for (int RA = 4; RA <= 12; RA += 4)
+        for (int RA = 4; RA <= (RB == 1 ? 12 : 16); RA += 4)
             for (int kb = 1; kb <= kb_max; ++kb) {
                 const int64_t bytes = (int64_t)kb * B * n_tiles * 64;
                 if (bytes > part_bytes && (kb > 1 || RA == 4)) continue;             // without scratch: one slice, kernels with every epilogue
                 const int rg = (n_tiles + RA - 1) / RA, wgs = rg * kb * ng, rounds = (wgs + n_cu - 1) / n_cu;
                 const double busy = std::min(1.0, (double)wgs / n_cu);
-                const double step = std::max({0.0215 * RA * RB, 0.0065 + 0.0194 * RA + 0.0832 * RB, 0.037 * RA * busy * (ng > 1 ? 0.3 : 1.0)});
+                const double step = std::max({0.067 + 0.0183 * RA * RB, 0.0074 + 0.0194 * RA + 0.084 * RB, 0.0383 * RA * busy * (ng > 1 ? 0.49 : 1.0)});
                 const bool direct = kb == 1 && RA != 4;
                 const double mb = 1e-6 * (double)bytes, y_mb = mb / kb;
-                const double tail = norm ? (direct ? 7.4 + 0.87 * y_mb : 2.4 + 0.8 * mb + 0.15 * y_mb) : direct ? 0.0 : 0.6 + 0.88 * mb;
-                const double cost = 9.1 + rounds * ((KS + kb - 1) / kb) * step + tail;
+                const double tail = norm ? (direct ? 6.8 + 0.89 * y_mb : 2.2 + 0.72 * mb + 0.24 * y_mb) : direct ? 0.0 : 0.08 + 0.83 * mb;
+                const double cost = 8.7 + rounds * ((KS + kb - 1) / kb) * step + tail;
                 if (best == 0.0 || cost < best) { best = cost; p.Kb = kb; p.Rg = rg; p.MT = RA; p.NB = 4 * RB; p.NG = ng; p.GB = gb; }
             }
     }

@@ -9,11 +9,11 @@ from gpu_util import DEV
 
 pytestmark = pytest.mark.gpu
 
-# rows: both sides of every batch-tile count; row tiles: one, a workgroup's 4 / 8 / 12 and one more, several ranges;
+# rows: both sides of every batch-tile count; row tiles: one, a workgroup's 4 / 8 / 12 / 16 and one more or less, several ranges;
 # k-steps: fewer than the rings hold, a multiple of their unrolling and one more or less, slices of unequal length
 CASES = [(16, 32, 33), (16, 160, 64), (64, 192, 65), (80, 224, 128), (128, 256, 129), (192, 288, 192), (208, 352, 193),
          (400, 416, 256), (64, 512, 34), (80, 544, 255), (784, 608, 63), (144, 1056, 127), (208, 2080, 191), (1200, 832, 80),
-         (3088, 544, 40), (3088, 480, 250), (33024, 96, 36), (33024, 64, 200)]
+         (3088, 544, 40), (3088, 480, 250), (33024, 96, 36), (33024, 64, 200), (32752, 192, 131), (28688, 224, 250), (32000, 96, 256)]
 
 
 @pytest.mark.parametrize("n,k,b", CASES)
