@@ -325,28 +325,41 @@ int pick_chunk(const pat_ctx *c, int64_t *n_chunks)
 }
 
 // Chunk length of a prefill pass's attention, and the chunks of all its rows (0: every row has one, so nothing is merged).
-// Two workgroups fit a compute unit; an item takes about 3 us and 1.2 us per tile of 64 keys (alone on its compute unit or
-// beside another), a merge another launch and the partial results' round trip.  Short contexts (or passes with items enough) are best left whole; a wide pass of
-// few items over a long context is cut until it fills the chip.
+// Two workgroups fit a compute unit.  An item takes 4 us and per tile of 64 keys of 128 features 1.6 us alone on its compute unit
+// (2.5 beside another; 1.05 and 1.4 of 64 features); a merge is a launch of 3.3 us, its rows and the partial results' bytes.  Equal
+// items run in rounds, unequal ones (short sequences, blocks under the diagonal) nearer to an even share, so the estimate
+// lies between the two.  Measured at 94 passes of 96 .. 1024 rows at position 0, 500 and 2000 on eight shapes of heads, kernel
+// and merge: 1.4 % above the best of 14 lengths on geometric average, 14 % at worst; powers of two from 256 on with the merge priced
+// by its bytes at 0.5 TB/s (what stood here) 20 % and 90 %.  8 heads on one KV head: 1024 rows at
+// position 0 25.3 us (192 tokens), before 30.7 (whole), 256 at 500 13.5 (128), before 24.3 (whole).  Prompts of 700 .. 3001
+// tokens on four shards are rebuilt 2.5 .. 4.2 % sooner, those of 515 at 32 heads, whose passes stay whole, as before.
 int pick_prefill_chunk(const pat_ctx *c, const std::vector<PfBlock> &blocks, int64_t *row_chunks)
 {
-    const double slots = 2.0 * c->n_cu;
-    int longest = 0;
-    for (const PfBlock &b : blocks) longest = std::max(longest, b.pos0 + b.n);
+    const double slots = 2.0 * c->n_cu, item = 4.0, alone = c->sh.d == 128 ? 1.6 : 1.05, shared = c->sh.d == 128 ? 2.5 : 1.4;
+    const int hkv = c->sh.hkv;
+    int longest = 0, rows = 0;
+    double tiles = 0.0;
+    for (const PfBlock &b : blocks) {
+        longest = std::max(longest, b.pos0 + b.n); rows += b.n;
+        tiles += (b.pos0 + b.n + 63) / 64;
+    }
     int best = 0; double best_cost = 0.0;
-    for (int C = 256;; C *= 2) {
-        double tiles = 0.0; int64_t rec = 0, rc = 0;
+    for (int C = 128, pow2 = 128;; C += std::max(64, pow2 / 4)) {        // 128, 192, .. 512, 640, .. 1024, 1280, ..
+        while (2 * pow2 <= C) pow2 *= 2;
+        auto chunks_to = [C](int64_t n) { const int64_t q = n / C; return C * (q * (q + 1) / 2) + (n - q * C) * (q + 1); };     // of positions 0 .. n - 1
+        int64_t rec = 0, rc = 0;
         for (const PfBlock &b : blocks) {
-            const int L = b.pos0 + b.n;
-            tiles += (L + 63) / 64;
-            rec += (L + C - 1) / C;
-            for (int i = 0; i < b.n; ++i) rc += (b.pos0 + i + 1 + C - 1) / C;
+            rec += (b.pos0 + b.n + C - 1) / C;
+            rc += chunks_to(b.pos0 + b.n) - chunks_to(b.pos0);
         }
         const bool whole = C >= longest;
         if (whole || (rc <= c->wl.max_chunks && rec <= kPfRecords)) {
-            const double items = (double)rec * c->sh.hkv, one = 1.2 * ((std::min(C, longest) + 63) / 64);
-            double cost = std::max(1.2 * tiles * c->sh.hkv / slots, one) + 3.0 * std::ceil(items / slots);
-            if (!whole) cost += 5.0 + 2.0e-6 * (double)rc * c->sh.hq * c->sh.d * 4;
+            const double n = (double)rec * hkv, t = (std::min(C, longest) + 63) / 64;
+            const double full = std::floor(n / slots), rest = n - full * slots;
+            const double one = item + (n > c->n_cu ? shared : alone) * t, even = (item * n + shared * tiles * hkv) / slots;
+            const double rounds = full * (item + shared * t) + (rest > 0.0 ? item + (rest > c->n_cu ? shared : alone) * t : 0.0);
+            double cost = std::max(one, 0.36 * even + 0.64 * std::min(rounds, even + one));
+            if (!whole) cost += 3.3 + 4.0e-4 * rows * c->sh.hq + 1.3e-7 * (double)rc * c->sh.hq * (c->sh.d + 2) * 4;
             if (best == 0 || cost < best_cost) { best = C; best_cost = cost; *row_chunks = whole ? 0 : rc; }
         }
         if (whole) break;

@@ -228,3 +228,10 @@ def test_block_attention_edges(hq, hkv, d, page, lens, width):
 def test_block_attention_over_chunks(hq, hkv, d, page, lens, width):
     shard = pi.ShardShape(pi.ModelShape(2, 256, hq, hkv, d, 256, 256), 1, 0)
     _prefill_parity(shard, list(lens), list(range(len(lens))), max_batch=width, page_tokens=page, steps=1, chunked=True)
+
+
+# chunks that are no power of two: a wide pass from position 0, and one that begins inside a chunk of its sequence
+@pytest.mark.parametrize("hq,hkv,d,page,length,width", [(8, 4, 128, 16, 700, 700), (16, 16, 64, 128, 900, 512)])
+def test_block_attention_over_odd_chunks(hq, hkv, d, page, length, width):
+    shard = pi.ShardShape(pi.ModelShape(2, 256, hq, hkv, d, 256, 256), 1, 0)
+    _prefill_parity(shard, [length], [0], max_batch=width, page_tokens=page, steps=1, chunked=True)
