@@ -18,7 +18,8 @@
 // More than 128 rows are cut into NG equal groups in ONE launch: the groups of a row range are neighbours on one XCD and
 // share its weight stream in L2.  That is faster than one group of up to 256 rows with one set of sums (22016 x 4096 at 256
 // rows 85 us against 101, 8192 x 1024 16 against 31) but for wide projections of 129..192 rows (22016 x 4096 at 130 rows 81
-// against 72) and of passes of about 1000 (1024 rows: 325 against 310; 7168 x 8192 213 against 191).
+// against 72) and of passes of about 1000 (1024 rows: 325 against 310; 7168 x 8192 213, now 184 by
+// 16 row tiles, against 191).
 //
 // What bounds it: up to 128 rows the weight stream from HBM (the per-k-step requests of all workgroups in flight,
 // up to 130 KB per compute unit, are what hides its latency).  From 256 rows on the chip's power limit: with random operands
