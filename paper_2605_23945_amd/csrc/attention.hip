@@ -28,14 +28,23 @@ constexpr int kAttnThreads = 256;
 // V are read once: as streamed (nontemporal) loads they arrive 6-13 % faster.  Kernel and merge, microseconds, before and now:
 // one sequence of 2047 tokens on 8 heads 9.1, 7.9; two of about 2900 on 32 25.8, 20.6; 27 of about 1777 on 20 94, 80.7; 60 of
 // about 1100 on 32 194, 165 (6.6 TB/s); 256 of about 620 456, 397.
-template <int D, int G>
-__global__ __launch_bounds__(kAttnThreads) void attn_stream_kernel(const int32_t *meta, const uint16_t *kbase, const uint16_t *vbase, const float *qkv, uint32_t hkv,
+// Sums: a lane adds one token of TPR per sub-round.  In chunks of more than 128 tokens (FOLD) its sums go to a second set every 128
+// tokens and start again from zero, so that the rounding does not grow with the chunk.  Weighted sum of N(0, 1) values under N(0, 1)
+// scores against float64, this order restated on the host, one chain and folded (in chunks of 128 tokens): 620 tokens whole
+// 1.55e-7, 1.22e-7 (1.24e-7); 930 whole 1.73e-7, 1.27e-7 (1.26e-7); 2000 in chunks of 384 1.49e-7, 1.36e-7 (1.37e-7).  What it
+// costs, a layer with its projections, microseconds: 60 sequences of about 1100 tokens on 32 heads 201.9, 202.0; 256 of about 620
+// 438, 440; two query heads per KV head, 64 of about 2500 on 8 KV heads in chunks of 384 148.7, 149.1.  The registers of the second
+// set leave three workgroups per compute unit of 128 features (held to 128 for four, 16 of about 1500 on 32 heads took 90.1, not 87.8).
+constexpr int kFoldTokens = 128;
+template <int D, int G, bool FOLD>
+__global__ __launch_bounds__(kAttnThreads, !FOLD ? 1 : G == 2 ? 3 : D == 64 ? 4 : 1) void attn_stream_kernel(const int32_t *meta, const uint16_t *kbase, const uint16_t *vbase, const float *qkv, uint32_t hkv,
                                                                    int ldq, int lgP, int C, AttnArgs a)
 {
     constexpr int LPT = D / 8;                  // lanes per token row
     constexpr int TPR = kAttnThreads / LPT;     // token rows per sub-round of the workgroup
     constexpr int UR = 4;                       // sub-rounds per round
     constexpr int RT = TPR * UR;                // tokens per round
+    static_assert(RT == kFoldTokens || 2 * RT == kFoldTokens, "folds at every or every other round");
     __shared__ float red[4 * G * D];
     __shared__ float wml[4 * G * 2];
 
@@ -94,13 +103,25 @@ __global__ __launch_bounds__(kAttnThreads) void attn_stream_kernel(const int32_t
         q[g][0] = q0.x * scale; q[g][1] = q0.y * scale; q[g][2] = q0.z * scale; q[g][3] = q0.w * scale;
         q[g][4] = q1.x * scale; q[g][5] = q1.y * scale; q[g][6] = q1.z * scale; q[g][7] = q1.w * scale;
     }
-    float acc[G][8], den[G], M[G];
+    // acc, den: of the tokens since the last fold; sum, dsum: of those before it, relative to Ms, the maximum at that fold
+    float acc[G][8], den[G], M[G], sum[G][8], dsum[G], Ms[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-        den[g] = 0.f; M[g] = -INFINITY;
+        den[g] = dsum[g] = 0.f; M[g] = Ms[g] = -INFINITY;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[g][j] = 0.f;
+        for (int j = 0; j < 8; ++j) acc[g][j] = sum[g][j] = 0.f;
     }
+    auto fold = [&] {
+        if (!FOLD) return;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (M[g] == -INFINITY) continue;                     // this wave has seen no token yet: nothing to add, nothing to scale
+            const float corr = expf(Ms[g] - M[g]);               // 0 at the first fold
+            dsum[g] = fmaf(dsum[g], corr, den[g]); den[g] = 0.f; Ms[g] = M[g];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) { sum[g][j] = fmaf(sum[g][j], corr, acc[g][j]); acc[g][j] = 0.f; }
+        }
+    };
 
     auto consume = [&](int r0, const u32x4_t (&kr)[UR], const u32x4_t (&vr)[UR]) {
         float sv[UR][G];
@@ -160,20 +181,24 @@ __global__ __launch_bounds__(kAttnThreads) void attn_stream_kernel(const int32_t
         const bool second = r0 + RT < cnt;
         if (second) fetch(r0 + RT, kB, vB);
         consume(r0, kA, vA);
+        if (RT >= kFoldTokens) fold();
         if (second) {
             if (r0 + 2 * RT < cnt) fetch(r0 + 2 * RT, kA, vA);
             consume(r0 + RT, kB, vB);
+            if (RT >= kFoldTokens) fold();
         }
+        if (RT < kFoldTokens) fold();
     }
 
     // the wave's rows: lanes at distance LPT, 2 LPT, ... hold the same feature segment
 #pragma unroll
     for (int g = 0; g < G; ++g) {
+        if (FOLD) den[g] = dsum[g];
 #pragma unroll
         for (int o = 32; o >= LPT; o >>= 1) den[g] += __shfl_xor(den[g], o, 64);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            float v = acc[g][j];
+            float v = FOLD ? sum[g][j] : acc[g][j];
 #pragma unroll
             for (int o = 32; o >= LPT; o >>= 1) v += __shfl_xor(v, o, 64);
             acc[g][j] = v;
@@ -291,6 +316,13 @@ __global__ __launch_bounds__(kMergeWaves * 64) void attn_merge_wide_kernel(const
 // 403 against 423; short ones need the four (3 sequences of about 2900: 28 against 36).
 constexpr size_t kTwoPerCu = 54 * 1024;
 
+template <int D, int G>
+void launch_stream(const AttnArgs &a, int grid, size_t lds, int lgP, const uint16_t *kb, const uint16_t *vb, hipStream_t s)
+{
+    if (a.chunk_tokens > kFoldTokens) attn_stream_kernel<D, G, true><<<grid, kAttnThreads, lds, s>>>(a.chunk_meta, kb, vb, a.qkv, (uint32_t)a.kv.hkv, a.ldq, lgP, a.chunk_tokens, a);
+    else attn_stream_kernel<D, G, false><<<grid, kAttnThreads, lds, s>>>(a.chunk_meta, kb, vb, a.qkv, (uint32_t)a.kv.hkv, a.ldq, lgP, a.chunk_tokens, a);
+}
+
 template <int D>
 hipError_t launch_partial_d(const AttnArgs &a, int grid, hipStream_t s)
 {
@@ -298,8 +330,8 @@ hipError_t launch_partial_d(const AttnArgs &a, int grid, hipStream_t s)
     const uint16_t *kb = a.kv.pool + a.kv.base(a.layer, 0), *vb = a.kv.pool + a.kv.base(a.layer, 1);
     const size_t lds = attn_stream_two_per_cu(G, D, a.kv_bytes) ? kTwoPerCu : 0;
     switch (G) {
-    case 1: attn_stream_kernel<D, 1><<<grid, kAttnThreads, lds, s>>>(a.chunk_meta, kb, vb, a.qkv, (uint32_t)a.kv.hkv, a.ldq, lgP, a.chunk_tokens, a); break;
-    case 2: attn_stream_kernel<D, 2><<<grid, kAttnThreads, lds, s>>>(a.chunk_meta, kb, vb, a.qkv, (uint32_t)a.kv.hkv, a.ldq, lgP, a.chunk_tokens, a); break;
+    case 1: launch_stream<D, 1>(a, grid, lds, lgP, kb, vb, s); break;
+    case 2: launch_stream<D, 2>(a, grid, lds, lgP, kb, vb, s); break;
     case 4: case 8: return launch_attn_gqa(a, s);
     default: return hipErrorInvalidValue;
     }

@@ -141,3 +141,44 @@ def test_long_streams_equal_the_same_sequences_in_a_short_batch(heads, n, longes
     short, ref = step(rows)
     assert short[0] == 64
     assert np.max(np.abs(out[rows] - ref)) <= 2e-4 * float(ref.std())
+
+
+@pytest.mark.parametrize("hq,hkv,d,n,length,period,page", [
+    (32, 32, 128, 8, 383, 384, 64),            # an item per compute unit: whole sequences of 384
+    (32, 16, 128, 16, 383, 384, 128),
+    (32, 32, 64, 8, 383, 384, 32),
+    (32, 16, 64, 16, 383, 384, 16),
+    (16, 16, 128, 61, 1151, 384, 64),          # 500 MB: three chunks of 384
+    (32, 32, 128, 130, 1023, 1024, 16),        # 16 items per compute unit: whole sequences of 1024, 64 pages each
+])
+def test_terms_of_a_long_chunk_are_not_lost_beside_its_large_sums(hq, hkv, d, n, length, period, page):
+    """All keys are zero, so every weight is 1.  Of `period` values the first 128 are 2^20, the last 128 -2^20, those between
+    1/8: a lane's sum of the first is 2^22 or 2^23, where one 1/8 after another is rounded away and 4 or 8 of them together
+    (128 tokens) are exact.  The last token is the appended one, whose value is zero; its lane has one 2^20 less too."""
+    import paper_2605_23945_amd as pat
+    H, tok, rows = 256, 7, 2048 // d                # token rows that a lane position of the kernel stands for
+    shard = pi.shard_of(pi.ModelShape(1, H, hq, hkv, d, 256, 512), 1, 0)
+    w = {k: v.clone() for k, v in pi.layer_weights(shard, 0, device=DEV).items()}
+    w["wqkv"][hq * d:] = 0
+    w["wd"][:] = 0
+    final, embed = pi.final_weights(shard, device=DEV), pi.embedding_table(shard, device=DEV)
+    t = torch.arange(length, device=DEV) % period
+    small = (t >= 128) & (t < period - 128)
+    value = torch.where(t < 128, 2.0 ** 20, torch.where(small, 0.125, -2.0 ** 20))
+    value[(t == rows - 1) | (t == period - 1)] = 0
+    sign = torch.randint(0, 2, (d,), generator=torch.Generator().manual_seed(3)).to(DEV) * 2.0 - 1.0
+    kv = torch.zeros(1, 2, hkv, length * n, d, dtype=torch.bfloat16, device=DEV)
+    kv[0, 1] = (value[:, None] * sign).to(torch.bfloat16).repeat(n, 1)
+    dec = pat.Decoder(pat.make_cfg(shard, n, length + 4, n * (length + 2 * page), page), DEV)
+    dec.pat_load_layer(0, w)
+    dec.pat_load_final(dict(final, embed=embed))
+    dec.pat_decode_admit(list(range(n)), [tok] * n, [length] * n, [4] * n)
+    dec.pat_kv_inject(list(range(n)), kv, layer0=0)
+    assert dec.pat_attention_cut()["step"] == (period, n * (length + 1) // period)
+    logits = torch.empty(n, shard.vocab, device=DEV)
+    dec.pat_decode_step(False, torch.empty(n, dtype=torch.int32, device=DEV), logits)
+    o = 0.125 * float(small.sum()) / (length + 1) * sign.double().repeat(hq)
+    x = embed[tok].double() + w["wo"].double() @ o
+    x = x / torch.sqrt((x * x).mean() + shard.model.rms_eps) * final["gf"].double()
+    check_logits(logits.cpu().numpy(), (final["wlm"].double() @ x).cpu().numpy()[None].repeat(n, 0))
+    dec.close()
