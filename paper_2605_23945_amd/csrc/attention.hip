@@ -328,7 +328,7 @@ hipError_t launch_partial_d(const AttnArgs &a, int grid, hipStream_t s)
 {
     const int G = a.hq / a.kv.hkv, lgP = __builtin_ctz(a.kv.P);
     const uint16_t *kb = a.kv.pool + a.kv.base(a.layer, 0), *vb = a.kv.pool + a.kv.base(a.layer, 1);
-    const size_t lds = attn_stream_two_per_cu(G, D, a.kv_bytes) ? kTwoPerCu : 0;
+    const size_t lds = a.two_per_cu ? kTwoPerCu : 0;
     switch (G) {
     case 1: launch_stream<D, 1>(a, grid, lds, lgP, kb, vb, s); break;
     case 2: launch_stream<D, 2>(a, grid, lds, lgP, kb, vb, s); break;

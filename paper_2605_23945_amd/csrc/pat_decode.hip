@@ -273,7 +273,11 @@ int64_t live_kv_bytes(const pat_ctx *c)
     return tokens * c->sh.hkv * c->sh.d * 4;
 }
 
-int pick_chunk(const pat_ctx *c, int64_t *n_chunks)
+// How the decode attention is cut: tokens of a chunk, chunks of the live batch, and whether long streams run two workgroups
+// per compute unit (attn_stream_kernel).  Decided once, for every launch of the step.
+struct AttnCut { int chunk; int64_t n_chunks; bool two_per_cu; };
+
+AttnCut pick_chunk(const pat_ctx *c)
 {
     auto count = [&](int C) { int64_t n = 0; for (int i = 0; i < c->live; ++i) n += (c->kv_len[i] + 1 + C - 1) / C; return n; };
     int longest = 0;
@@ -300,8 +304,7 @@ int pick_chunk(const pat_ctx *c, int64_t *n_chunks)
                                 (C < longest ? 4.2 + 0.024 * ((longest + C - 1) / C) + 0.001 * c->sh.hq * c->live : 0.0);
             if (best_n == 0 || cost < best_cost) { best = C; best_n = n; best_cost = cost; }
         }
-        *n_chunks = best_n;
-        return best;
+        return AttnCut{best, best_n, false};
     }
     // One-pass kernel of G < 4, by the bytes of K and V that a launch reads (kernel and merge, measured at 28 batches of 1 .. 256
     // sequences on 8, 16, 20 and 32 heads; all within 3 % of the best cut measured, microseconds):
@@ -314,14 +317,13 @@ int pick_chunk(const pat_ctx *c, int64_t *n_chunks)
     // a long stream of 16 items per compute unit up to the longest chunk (256 of about 620: 397 against 403).
     const int G = c->sh.hq / c->sh.hkv, d = c->sh.d, round = d == 128 ? 64 : 128;
     const int64_t items = (int64_t)c->live * c->sh.hkv, bytes = live_kv_bytes(c);
-    const bool two = attn_stream_two_per_cu(G, d, bytes);
-    if (longest <= 192 || (longest <= 384 && items >= c->n_cu) || (two && longest <= kAttnMaxChunk && items >= 16 * (int64_t)c->n_cu)) { *n_chunks = c->live; return longest; }
+    const bool two = G == 1 && d == 128 && bytes >= 500000000;
+    if (longest <= 192 || (longest <= 384 && items >= c->n_cu) || (two && longest <= kAttnMaxChunk && items >= 16 * (int64_t)c->n_cu)) return AttnCut{longest, c->live, two};
     int best = round;
     if (two) best = 384;
     else if (G == 1) best = bytes >= 300000000 && d == 128 ? 192 : round;
     else best = bytes >= 300000000 ? 4 * round : count(128) * c->sh.hkv >= 2 * (int64_t)c->n_cu ? 128 : round;
-    *n_chunks = count(best);
-    return best;
+    return AttnCut{best, count(best), two};
 }
 
 // Chunk length of a prefill pass's attention, and the chunks of all its rows (0: every row has one, so nothing is merged).
@@ -664,7 +666,7 @@ int pat_attention_cut(pat_ctx *c, int32_t step[2], int32_t prefill[2])
     if (!c) return PAT_EINVAL;
     if (step) {
         step[0] = step[1] = 0;
-        if (c->live > 0) { int64_t n = 0; step[0] = pick_chunk(c, &n); step[1] = (int32_t)n; }
+        if (c->live > 0) { const AttnCut cut = pick_chunk(c); step[0] = cut.chunk; step[1] = (int32_t)cut.n_chunks; }
     }
     if (prefill) { prefill[0] = c->pf_cut[0]; prefill[1] = c->pf_cut[1]; }
     return PAT_OK;
@@ -676,8 +678,10 @@ int pat_attention_cut(pat_ctx *c, int32_t step[2], int32_t prefill[2])
 // of a prefill pass (the block kernel), n_chunks still counts the rows' own chunks (0: one chunk per row, whose
 // output the block kernel writes itself).  Leaves the rows'
 // final hidden states in x.
-static int run_layers(pat_ctx *c, int B, int C, int64_t n_chunks, const int32_t *pos, const int32_t *row_slot, int64_t n_blocks)
+static int run_layers(pat_ctx *c, int B, const AttnCut &cut, const int32_t *pos, const int32_t *row_slot, int64_t n_blocks)
 {
+    const int C = cut.chunk;
+    const int64_t n_chunks = cut.n_chunks;
     const Shard &s = c->sh;
     void *W = c->bufs.work;
     const WorkLayout &w = c->wl;
@@ -711,7 +715,7 @@ static int run_layers(pat_ctx *c, int B, int C, int64_t n_chunks, const int32_t 
     if (n_blocks == 0) {
         for (int i = 0; i < B; ++i) aa.longest_chunks = std::max(aa.longest_chunks, (c->kv_len[i] + C) / C);
         aa.direct = aa.longest_chunks == 1;
-        aa.kv_bytes = live_kv_bytes(c);
+        aa.two_per_cu = cut.two_per_cu;
     }
 
     for (int l = 0; l < s.NL; ++l) {
@@ -764,7 +768,7 @@ static int run_layers(pat_ctx *c, int B, int C, int64_t n_chunks, const int32_t 
 // The decode step of a live batch of at most 16 rows: per layer the attention partials and ONE fused launch
 // (merge, O, gate/up, down, next layer's QKV or the vocabulary head; see layer_fused.hip).  Leaves the logits
 // in `logits`.
-static int run_layers_fused(pat_ctx *c, int B, int C, int64_t n_chunks, float *logits)
+static int run_layers_fused(pat_ctx *c, int B, const AttnCut &cut, float *logits)
 {
     const Shard &s = c->sh;
     void *W = c->bufs.work;
@@ -777,11 +781,11 @@ static int run_layers_fused(pat_ctx *c, int B, int C, int64_t n_chunks, float *l
 
     AttnArgs aa{};
     aa.kv = c->kv; aa.qkv = qkv; aa.ldq = s.qkv_rows; aa.hq = s.hq; aa.B = B; aa.kv_len = c->st.kv_len; aa.row_slot = nullptr;
-    aa.page_table = c->st.page_table; aa.max_pages = s.max_pages; aa.chunk_start = c->st.chunk_start; aa.chunk_meta = c->st.chunk_meta; aa.chunk_tokens = C;
+    aa.page_table = c->st.page_table; aa.max_pages = s.max_pages; aa.chunk_start = c->st.chunk_start; aa.chunk_meta = c->st.chunk_meta; aa.chunk_tokens = cut.chunk; aa.two_per_cu = cut.two_per_cu;
     aa.part_acc = at<float>(W, w.part_acc); aa.part_ml = at<float>(W, w.part_ml);
     aa.ml_unit = attn_decode_unit(s.hq / s.hkv);
     aa.ohi = at<uint4>(W, w.o_hi); aa.olo = at<uint4>(W, w.o_lo);
-    aa.n_items = (int)(n_chunks * s.hkv);
+    aa.n_items = (int)(cut.n_chunks * s.hkv);
 
     FusedArgs fa{};
     fa.B = B; fa.H = s.H; fa.merge = aa;
@@ -871,9 +875,9 @@ int pat_decode_step(pat_ctx *c, pat_step_report *report_host, int32_t *next_tok_
         new_pages += (c->kv_len[i] % P) == 0;
     }
     if (new_pages > c->n_free) return fail(c, PAT_ENOMEM, "step: %lld new pages needed, %lld free", (long long)new_pages, (long long)c->n_free);
-    int64_t n_chunks = 0;
-    const int C = pick_chunk(c, &n_chunks);
-    if (n_chunks > c->wl.max_chunks) return fail(c, PAT_ENOMEM, "step: %lld attention chunks exceed the workspace (%lld)", (long long)n_chunks, (long long)c->wl.max_chunks);
+    const AttnCut cut = pick_chunk(c);
+    const int C = cut.chunk;
+    if (cut.n_chunks > c->wl.max_chunks) return fail(c, PAT_ENOMEM, "step: %lld attention chunks exceed the workspace (%lld)", (long long)cut.n_chunks, (long long)c->wl.max_chunks);
 
     void *W = c->bufs.work;
     const WorkLayout &w = c->wl;
@@ -887,7 +891,7 @@ int pat_decode_step(pat_ctx *c, pat_step_report *report_host, int32_t *next_tok_
 
     if (B <= kFusedMaxBatch && c->fused_ok) {
         { TimeScope t(c, 2); PAT_HIP(c, launch_plan_step(c->st, B, C, st)); }
-        if (int rc = run_layers_fused(c, B, C, n_chunks, logits)) return rc;
+        if (int rc = run_layers_fused(c, B, cut, logits)) return rc;
     } else {
         const bool fold = norm_is_folded(B);
         const uint16_t *g0 = (const uint16_t *)(s.NL > 0 ? Wb + c->wt.layer0 + c->wt.g1 : Wb + c->wt.gf);     // gains of the first RMSNorm
@@ -899,7 +903,7 @@ int pat_decode_step(pat_ctx *c, pat_step_report *report_host, int32_t *next_tok_
                 PAT_HIP(c, launch_embed((const uint16_t *)(Wb + c->wt.embed), s.H, c->st.tok, B, x, st));
             }
         }
-        if (int rc = run_layers(c, B, C, n_chunks, c->st.kv_len, nullptr, 0)) return rc;
+        if (int rc = run_layers(c, B, cut, c->st.kv_len, nullptr, 0)) return rc;
         if (!fold && s.NL == 0) { TimeScope t(c, 2); PAT_HIP(c, launch_rmsnorm_pack(x, (const uint16_t *)(Wb + c->wt.gf), B, s.H, c->cfg.rms_eps, a_hi, a_lo, st)); }
         {
             GemmArgs g = gemm_args(Wb + c->wt.wlm, s.Vs, s.H, a_hi, a_lo, B, logits, s.Vs, gpart, w.gemm_part_bytes);
@@ -1007,7 +1011,7 @@ int pat_prefill(pat_ctx *c, int32_t n, const int32_t *slots, const int32_t *toke
         else PAT_HIP(c, launch_embed((const uint16_t *)(Wb + c->wt.embed), s.H, rows, R, at<float>(W, c->wl.x), c->stream));
         PAT_HIP(c, hipEventRecord(c->pf_done[set], c->stream));          // the set is free once the copies above have run
         c->pf_used[set] = true;
-        if (int rc = run_layers(c, R, C, chunks, rows + 2 * MB, rows + MB, n_rec)) return rc;
+        if (int rc = run_layers(c, R, AttnCut{C, chunks, false}, rows + 2 * MB, rows + MB, n_rec)) return rc;
         ++pass;
     }
     PAT_HIP(c, hipStreamSynchronize(c->stream));         // the caller's token array is not read after return, and errors surface here

@@ -103,13 +103,11 @@ struct AttnArgs {
     uint4 *ohi, *olo;          // merged output as packed split-bf16 [B, hq*d]
     int n_items;               // n_chunks_total * hkv (host mirror)
     int longest_chunks;        // most chunks of one row (0: unknown), for the choice of the merge kernel
-    int64_t kv_bytes;          // K and V that a launch of the decode kernels reads
+    bool two_per_cu;           // attn_stream_kernel: two workgroups per compute unit (see pick_chunk)
     bool direct;               // every row has one chunk: its workgroups write ohi / olo, nothing is merged
 };
 constexpr float kLn2 = 0.69314718f;
 inline float attn_decode_unit(int G) { return G >= 4 ? kLn2 : 1.f; }      // ml_unit of launch_attn_partial, by query heads per KV head; launch_attn_prefill: kLn2
-// attn_stream_kernel: from this many bytes of K and V on, two workgroups per compute unit read longer chunks (see pick_chunk)
-inline bool attn_stream_two_per_cu(int G, int d, int64_t kv_bytes) { return G == 1 && d == 128 && kv_bytes >= 500000000; }
 hipError_t launch_attn_partial(const AttnArgs &a, hipStream_t s);
 hipError_t launch_attn_gqa(const AttnArgs &a, hipStream_t s);        // the case of 4 or 8 query heads per KV head
 int attn_prefill_block(int G);            // positions per block record
