@@ -306,23 +306,35 @@ AttnCut pick_chunk(const pat_ctx *c)
         }
         return AttnCut{best, best_n, false};
     }
-    // One-pass kernel of G < 4, by the bytes of K and V that a launch reads (kernel and merge, measured at 28 batches of 1 .. 256
-    // sequences on 8, 16, 20 and 32 heads; all within 3 % of the best cut measured, microseconds):
-    //  * short launches want many items: a round of the kernel (64 tokens of 128 features, 128 of 64) is a chunk.  2 sequences of about
-    //    2900 tokens on 32 heads: 20.6 at 64 tokens, 21.6 at 128, 21.0 at 192; one of 2047 on 8: 8.0, 8.9, 9.6;
-    //  * from 300 MB on (one query head per KV head) 192 tokens: 16 of about 1500 on 32 heads 67.6, 68.2, 66.4;
-    //  * long streams want few and long ones, two workgroups per compute unit: 60 of about 1100 on 32 heads 182 at 128 tokens,
-    //    166 at 256, 165 at 384 and 512, 167 at 768.
-    // Whole sequences need no merge: up to 192 tokens, up to 384 when their heads give every compute unit an item, and in
-    // a long stream of 16 items per compute unit up to the longest chunk (256 of about 620: 397 against 403).
+    // One-pass kernel of G < 4, by the bytes of K and V that a launch reads.  Measured: every cut (multiples of 64 from 64 to 1024,
+    // whole, with and without two workgroups per compute unit) of 1038 batches of 1 .. 256 sequences of 200 .. 120 000 tokens, some
+    // of one long and many short ones: 318 of one query head on 8 .. 40 heads of 128 features, 263 of 64 features, 259 and 198
+    // of two query heads.  The cut this picks is 0.6 % slower than the best on average, 3.2 % in one of twenty, 13 % at worst (two query
+    // heads, one sequence of 64 000).  Lines below with both sides, a layer with its projections, microseconds:
+    //  * short launches want many items: a round of the kernel (64 tokens of 128 features, 128 of 64) is a chunk, 128 where two query
+    //    heads of 128 features leave every compute unit two.  8 sequences of about 1500 tokens on 32 heads 55.5 at 64, 58.3 at 128; 64
+    //    features, one of 8000 on 8 heads 25.2 at 64, 24.5 at 128, 25.7 at 256;
+    //  * middle ones want fewer: one query head of 128 features from 300 MB on 192 tokens (13 of about 2000 on 32 heads 2 % faster than
+    //    64, 6 % than 128); two query heads of 128 features from there on 320 (64 of about 2500 on 8: 154 at 128, 149), of 64 features from
+    //    100 MB on 384 (128 of about 900 on 16: 144 at 128, 129); with 64 features and one query head 128 stays best;
+    //  * long streams of one query head want few and long ones, two workgroups per compute unit: 60 of about 1100 on 32 heads 217 at
+    //    128, 207 at 192, 202 at 384.  From 700 MB on, where the longest has three such chunks from 500 (below, and below 700,
+    //    384 was 4 .. 11 % slower than 192: 256 of about 620 on 8 heads 151 against 142);
+    //  * the merge takes 64 chunks of 128 features, or 128 of 64, in a round of loads: no sequence has more than 192.  One of 64 000 on 8 heads 75 at 64 tokens, 68 at 384; one of 16 000 35.0 at 64, 33.4 at 128.
+    // Whole sequences need no merge: up to 192 tokens, up to 384 when their heads give every compute unit an item, and up to the longest
+    // chunk where two query heads have four items per compute unit (256 of about 620 on 16 heads of 64 features 168 at 384, 151) or
+    // a long stream has 16 (256 of about 620 on 32 447 at 384, 438; with four workgroups up to 448 tokens: 256 of about 200 189 with two, 179).
     const int G = c->sh.hq / c->sh.hkv, d = c->sh.d, round = d == 128 ? 64 : 128;
-    const int64_t items = (int64_t)c->live * c->sh.hkv, bytes = live_kv_bytes(c);
-    const bool two = G == 1 && d == 128 && bytes >= 500000000;
-    if (longest <= 192 || (longest <= 384 && items >= c->n_cu) || (two && longest <= kAttnMaxChunk && items >= 16 * (int64_t)c->n_cu)) return AttnCut{longest, c->live, two};
-    int best = round;
+    const int64_t items = (int64_t)c->live * c->sh.hkv, n_cu = c->n_cu, bytes = live_kv_bytes(c);
+    const bool two = G == 1 && d == 128 && (bytes >= 700000000 || (bytes >= 500000000 && longest > 1200));
+    if (longest <= 192 || (longest <= 384 && items >= n_cu) || (longest <= kAttnMaxChunk && ((G == 2 && items >= 4 * n_cu) || (two && items >= 16 * n_cu))))
+        return AttnCut{longest, c->live, two && longest > 448};
+    int best;
     if (two) best = 384;
-    else if (G == 1) best = bytes >= 300000000 && d == 128 ? 192 : round;
-    else best = bytes >= 300000000 ? 4 * round : count(128) * c->sh.hkv >= 2 * (int64_t)c->n_cu ? 128 : round;
+    else if (G == 1) best = d == 128 && bytes >= 300000000 ? 192 : round;
+    else if (d == 64) best = bytes >= 100000000 ? 384 : round;
+    else best = bytes >= 300000000 ? 320 : count(128) * c->sh.hkv >= 2 * n_cu ? 128 : round;
+    best = std::max(best, std::min(kAttnMaxChunk, cdiv(longest, 192 * round) * round));
     return AttnCut{best, count(best), two};
 }
 

@@ -42,6 +42,29 @@ def test_whole_sequences_and_wide_merges_vs_oracle(hq, hkv, d, page, lens, whole
     dec.close()
 
 
+@pytest.mark.parametrize("hq,hkv,d,page,lens,chunk", [
+    (2, 2, 128, 64, (12287, 40), 64),          # 192 chunks
+    (2, 2, 128, 64, (12288,), 128),
+    (4, 2, 128, 16, (26000, 300), 192),
+    (2, 2, 64, 128, (24575,), 128),
+    (4, 2, 64, 16, (24600, 1000, 5), 256),
+])
+def test_long_contexts_take_longer_chunks_vs_oracle(hq, hkv, d, page, lens, chunk):
+    shard = pi.shard_of(pi.ModelShape(1, 256, hq, hkv, d, 512, 512), 1, 0)
+    import paper_2605_23945_amd as pat
+    n, req = len(lens), _requests(shard, lens)
+    dec = make_decoder(shard, n, max(lens) + 8, int(sum(lens)) + 2 * page * n + 64, page)
+    pat.admit_synthetic(dec, shard, req, DEV)
+    odec = make_oracle_decoder(shard)
+    oracle_admit(odec, shard, req, range(n), 4)
+    assert dec.pat_attention_cut()["step"] == (chunk, sum((l + chunk) // chunk for l in lens))
+    ref_logits, ref_next, _ = odec.step()
+    logits, nxt, _ = _gpu_step(dec, n, shard.vocab)
+    check_logits(logits, ref_logits)
+    assert np.array_equal(nxt, ref_next)
+    dec.close()
+
+
 @pytest.mark.parametrize("hq,hkv,d", [(4, 4, 128), (4, 2, 64), (8, 1, 128)])
 def test_page_length_does_not_change_a_whole_sequence(hq, hkv, d):
     """The page ids come from the chunk's record or from the wave's lanes; the arithmetic is the same, bit by bit."""
@@ -108,14 +131,34 @@ def test_long_streams_equal_the_same_sequences_in_a_short_batch(heads, n, longes
     """Rows of a batch whose K and V are hundreds of megabytes against the same sequences alone, which are cut into chunks of one
     round.  The sums' order differs, and the projections' kernels (more than 32 rows, at most 32): both are within 1e-4 of the
     logits' scale of float64 in their own tests."""
+    _rows_of_a_long_batch(heads, heads, 128, n, longest, chunk, 64)
+
+
+@pytest.mark.parametrize("hq,hkv,d,n,longest,chunk,page", [
+    (16, 16, 128, 40, 1290, 192, 128),         # chunks begin inside a page
+    (16, 16, 128, 61, 1420, 384, 16),          # 24 pages per chunk, from the wave's lanes
+    (32, 32, 128, 130, 700, 0, 16),
+    (32, 32, 128, 150, 400, 0, 64),            # whole, four workgroups per compute unit
+    (16, 8, 128, 80, 1290, 320, 64),           # two query heads: five pages
+    (16, 8, 128, 80, 1290, 320, 128),
+    (16, 8, 128, 130, 1000, 0, 16),            # four items per compute unit: whole, 63 pages
+    (16, 8, 64, 60, 1290, 384, 32),
+    (16, 8, 64, 130, 900, 0, 128),
+    (32, 32, 64, 60, 1000, 128, 16),           # 64 features, one query head: a round whatever the bytes
+])
+def test_cuts_of_long_batches_and_page_lengths(hq, hkv, d, n, longest, chunk, page):
+    """As above, over heads, features and page lengths."""
+    _rows_of_a_long_batch(hq, hkv, d, n, longest, chunk, page)
+
+
+def _rows_of_a_long_batch(hq, hkv, d, n, longest, chunk, page):
     import paper_2605_23945_amd as pat
-    d, page = 128, 64
-    shard = pi.shard_of(pi.ModelShape(1, 256, heads, heads, d, 512, 512), 1, 0)
+    shard = pi.shard_of(pi.ModelShape(1, 256, hq, hkv, d, 512, 512), 1, 0)
     lens = np.array([longest - (i * longest) // (2 * n) for i in range(n)], np.int32)
     lens[[0, n - 1]] = lens[[n - 1, 0]]
     off = np.concatenate(([0], np.cumsum(lens)))
     g = torch.Generator(device=DEV).manual_seed(n)
-    kv = torch.empty(1, 2, heads, int(off[-1]), d, dtype=torch.bfloat16, device=DEV).normal_(0, 1, generator=g)
+    kv = torch.empty(1, 2, hkv, int(off[-1]), d, dtype=torch.bfloat16, device=DEV).normal_(0, 1, generator=g)
     weights, final = pi.layer_weights(shard, 0, device=DEV), pi.final_weights(shard, device=DEV)
     final = dict(final, embed=pi.embedding_table(shard, device=DEV))
 
@@ -139,7 +182,7 @@ def test_long_streams_equal_the_same_sequences_in_a_short_batch(heads, n, longes
     assert cut == ((longest + 1, n) if chunk == 0 else (chunk, int(sum((l + chunk) // chunk for l in lens))))
     rows = [0, n // 2, n - 1]
     short, ref = step(rows)
-    assert short[0] == 64
+    assert short[0] == (64 if d == 128 else 128)
     assert np.max(np.abs(out[rows] - ref)) <= 2e-4 * float(ref.std())
 
 
@@ -148,7 +191,7 @@ def test_long_streams_equal_the_same_sequences_in_a_short_batch(heads, n, longes
     (32, 16, 128, 16, 383, 384, 128),
     (32, 32, 64, 8, 383, 384, 32),
     (32, 16, 64, 16, 383, 384, 16),
-    (16, 16, 128, 61, 1151, 384, 64),          # 500 MB: three chunks of 384
+    (16, 16, 128, 80, 1151, 384, 64),          # 700 MB: three chunks of 384
     (32, 32, 128, 130, 1023, 1024, 16),        # 16 items per compute unit: whole sequences of 1024, 64 pages each
 ])
 def test_terms_of_a_long_chunk_are_not_lost_beside_its_large_sums(hq, hkv, d, n, length, period, page):
