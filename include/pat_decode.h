@@ -279,6 +279,10 @@ int64_t pat_op_gemm_scratch_bytes(int32_t n, int32_t k, int32_t b);
  * workgroups, plan[2] row ranges, plan[3] batch tiles held per workgroup.
  * Returns PAT_EINVAL for shapes pat_op_gemm rejects. */
 int pat_op_gemm_plan(int32_t n, int32_t k, int32_t b, int32_t plan[4]);
+/* The cut of an [n, k] projection of 33 .. 1024 rows (the widest prefill pass) with `scratch_bytes` for partial sums, followed by an
+ * RMSNorm if `norm` (diagnostics, host only): cut[0] row tiles of a workgroup, cut[1] batch tiles of a wave, cut[2] K slices, cut[3] row
+ * ranges, cut[4] groups of rows.  Returns PAT_EINVAL for other row counts. */
+int pat_op_gemm_cut(int32_t n, int32_t k, int32_t b, int64_t scratch_bytes, int32_t norm, int32_t cut[5]);
 int pat_op_gemm(const void *w_packed, int32_t n, int32_t k, const void *xhi, const void *xlo, int32_t b,
                 float *y, int32_t ldy, void *y_hi, void *y_lo, int32_t mode, void *scratch, void *hip_stream);
 /* pat_op_gemm for callers that cannot allocate device memory or hand over a work buffer: code under HIP

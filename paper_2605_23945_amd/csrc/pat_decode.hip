@@ -1280,6 +1280,14 @@ int pat_op_gemm_plan(int32_t n, int32_t k, int32_t b, int32_t plan[4])
     return PAT_OK;
 }
 
+int pat_op_gemm_cut(int32_t n, int32_t k, int32_t b, int64_t scratch_bytes, int32_t norm, int32_t cut[5])
+{
+    if (!cut || n <= 0 || k <= 0 || k % 32 || b <= 32 || b > 1024 || scratch_bytes < 0) return PAT_EINVAL;
+    const GemmPlan p = gemm_plan(cdiv(n, 16), k / 32, b, scratch_bytes, norm != 0);
+    cut[0] = p.MT; cut[1] = p.NB / 4; cut[2] = p.Kb; cut[3] = p.Rg; cut[4] = p.NG;
+    return PAT_OK;
+}
+
 int pat_op_gemm(const void *w_packed, int32_t n, int32_t k, const void *xhi, const void *xlo, int32_t b, float *y,
                 int32_t ldy, void *y_hi, void *y_lo, int32_t mode, void *scratch, void *stream)
 {

@@ -214,3 +214,17 @@ def test_device_barrier_probe_runs_and_its_bounded_wait_ends(pat):
         pat.pat_op_barrier_probe(n_cu + 1, iters=4)                # more workgroups than are resident at once: refused
     assert e.value.code == -1
     assert pat.pat_op_barrier_probe(n_cu, iters=20) > 0.0          # and the next call starts from clean words
+
+
+def test_rounding_to_bf16_is_to_nearest_even(pat):
+    """Every upper half of a float with the lower halves around a tie: the packed operand's high terms against torch's rounding
+    on the host.  Subnormals, the step to infinity and NaN are among them."""
+    low = torch.tensor([0, 1, 0x7FFF, 0x8000, 0x8001, 0xFFFF], dtype=torch.int64)
+    bits32 = ((torch.arange(1 << 16, dtype=torch.int64)[:, None] << 16) | low[None]).reshape(-1)
+    x = torch.where(bits32 >= 1 << 31, bits32 - (1 << 32), bits32).to(torch.int32).view(torch.float32).view(-1, 4096)
+    want = x.bfloat16().float().numpy().astype(np.float64)
+    hi, lo = pat.pat_op_pack_act(x.to(DEV))
+    got = pat.unpack_act(hi, torch.zeros_like(lo), *x.shape)
+    nan = np.isnan(want)
+    assert np.array_equal(np.isnan(got), nan) and nan.any() and np.isinf(want).any()
+    assert np.array_equal(got[~nan], want[~nan])

@@ -28,7 +28,7 @@ def _kv_bits(dec, slot, n_layers, L):
     return out
 
 
-def _prefill_parity(shard, kv_lens, slots, max_batch, page_tokens=64, steps=2, chunked=None):
+def _prefill_parity(shard, kv_lens, slots, max_batch, page_tokens=64, steps=2, chunked=None, chunk=None):
     pat = _pat()
     n = len(kv_lens)
     req = pi.rollout_requests(shard, n, (1, 2), steps=steps + 1)
@@ -43,6 +43,7 @@ def _prefill_parity(shard, kv_lens, slots, max_batch, page_tokens=64, steps=2, c
     dec.pat_prefill(slots, np.concatenate(toks) if toks else np.zeros(0, np.int32))
     if chunked is not None:
         assert (dec.pat_attention_cut()["prefill"][1] > 0) == chunked
+    assert chunk is None or dec.pat_attention_cut()["prefill"][0] == chunk
     for j, t in zip(slots, toks):
         prefill(odec, j, t)
     st = dec.pat_get_state()
@@ -231,7 +232,7 @@ def test_block_attention_over_chunks(hq, hkv, d, page, lens, width):
 
 
 # chunks that are no power of two: a wide pass from position 0, and one that begins inside a chunk of its sequence
-@pytest.mark.parametrize("hq,hkv,d,page,length,width", [(8, 4, 128, 16, 700, 700), (16, 16, 64, 128, 900, 512)])
-def test_block_attention_over_odd_chunks(hq, hkv, d, page, length, width):
+@pytest.mark.parametrize("hq,hkv,d,page,length,width,chunk", [(8, 4, 128, 16, 700, 700, 192), (16, 16, 64, 128, 900, 512, 192)])
+def test_block_attention_over_odd_chunks(hq, hkv, d, page, length, width, chunk):
     shard = pi.ShardShape(pi.ModelShape(2, 256, hq, hkv, d, 256, 256), 1, 0)
-    _prefill_parity(shard, [length], [0], max_batch=width, page_tokens=page, steps=1, chunked=True)
+    _prefill_parity(shard, [length], [0], max_batch=width, page_tokens=page, steps=1, chunked=True, chunk=chunk)

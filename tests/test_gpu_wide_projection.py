@@ -6,6 +6,8 @@ import torch
 
 import pat_inputs as pi
 from gpu_util import DEV
+from test_gpu_step import _sampled_rows_parity
+from wide_cuts import MODELS, OPERATORS, VOCAB, cut_of, cuts_of
 
 pytestmark = pytest.mark.gpu
 
@@ -18,6 +20,30 @@ CASES = [(16, 32, 33), (16, 160, 64), (64, 192, 65), (80, 224, 128), (128, 256, 
 
 @pytest.mark.parametrize("n,k,b", CASES)
 def test_edges_of_tiles_rings_and_slices(n, k, b):
+    _all_epilogues(n, k, b)
+
+
+@pytest.mark.parametrize("n,k,b", OPERATORS)
+def test_every_kernel_past_a_turn_of_its_ring(n, k, b):
+    import paper_2605_23945_amd as pat
+    assert cut_of(pat.load_library(), n, k, b) == OPERATORS[n, k, b]
+    _all_epilogues(n, k, b)
+
+
+@pytest.mark.parametrize("model", MODELS, ids=lambda m: "-".join(map(str, m)))
+def test_every_kernel_with_the_step_s_own_epilogues(model):
+    """Rotary embedding and append, residual with the next RMSNorm, SwiGLU, in a decode step of one layer; rows at the edges of
+    the batch tiles and row groups."""
+    import paper_2605_23945_amd as pat
+    h, hq, hkv, d, f, rows = model
+    got = cuts_of(pat.load_library(), model)
+    assert all(got[p] == c for p, c in MODELS[model].items()), got
+    shard = pi.shard_of(pi.ModelShape(1, h, hq, hkv, d, f, VOCAB), 1, 0)
+    edges = sorted({0, 15, 16, min(63, rows - 2), (rows // 2) & ~15, rows - 1})
+    _sampled_rows_parity(shard, rows, (1, 6), edges, page_tokens=16)
+
+
+def _all_epilogues(n, k, b):
     import paper_2605_23945_amd as pat
     lib = pat.load_library()
     w = pi.normal_bf16(pi.stream_key(0x31DE, n, k), torch.arange(n * k, dtype=torch.int64, device=DEV), 0.05).view(n, k)
