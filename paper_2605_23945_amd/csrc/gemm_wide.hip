@@ -22,12 +22,13 @@
 // 16 row tiles, against 191).
 //
 // What bounds it: up to 128 rows the weight stream from HBM (the per-k-step requests of all workgroups in flight,
-// up to 130 KB per compute unit, are what hides its latency).  From 256 rows on the chip's power limit: with random operands
-// the clock falls to 1.8 .. 2.0 GHz (all-zero ones: 2.4), and what the operands' way from L2 and through LDS takes of
-// the power is missing at the matrix cores.  Between, the issue of the one wave that a SIMD has: a product of 16 clocks leaves
-// room for one other instruction, so the loop has 57 others to 32 products (8 x 2 tiles) where it had 75; with one batch tile
-// per wave LDS (4 waves read every weight: 125 bytes per clock at the products' rate).  Clocks per k-step with all-zero operands, of
-// products / alone without loads / in all: 8 x 2 tiles 512 / 599 / 791, 12 x 2 768 / 899 / 1109, 12 x 1 384 / 445 / 768.
+// up to 130 KB per compute unit, are what hides its latency).  Above, two things in turn.  The operands' delivery: clocks per k-step
+// with all-zero operands, of products / alone without loads / in all, are 512 / 599 / 791 with 8 x 2 tiles, 768 / 899 / 1109 with
+// 12 x 2, 384 / 445 / 768 with 12 x 1, so 31 to 50 % of a k-step is not products.  The one wave that a SIMD has issues everything (a
+// product of 16 clocks leaves room for one other instruction: the loop has 57 others to 32 products, 8 x 2 tiles, where it had 75), and
+// with one batch tile per wave LDS is the bound (4 waves read every weight: 125 bytes per clock at the products' rate).  Then the
+// chip's power limit: with random operands the clock falls to 1.8 .. 2.0 GHz (all-zero ones: 2.4), and what the operands' way from L2
+// and through LDS takes of the power is missing at the matrix cores.
 // Staging the weights through registers into LDS, with exact waits, took the same time (8 x 2) or 10 % more (12 x 2); other
 // cache policies of the weights' loads changed nothing.
 // Measured against the kernel it replaced (batch
@@ -64,8 +65,8 @@ template <int RA, int RB> constexpr int wide_lds_bytes() { return WideRings<RA, 
 
 // elements of a wave's row tile that are added to the second sums after j of the RA - 1 other row tiles
 __host__ __device__ constexpr int wide_folded(int RA, int RB, int j) { return j * 4 * RB / (RA - 1); }
-template <int N, class F, int... I> __device__ __forceinline__ void static_for_i(F &&f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
-template <int N, class F> __device__ __forceinline__ void static_for(F &&f) { static_for_i<N>(f, std::make_integer_sequence<int, N>{}); }
+template <class F, int... I> __device__ __forceinline__ void static_for_i(F &&f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F> __device__ __forceinline__ void static_for(F &&f) { static_for_i(f, std::make_integer_sequence<int, N>{}); }
 
 // MODE kPartial: the tile's sums go to a.part[kb][b][n_tiles * 16] (kb = K slice); otherwise (one slice) the epilogue runs here.
 constexpr int kPartial = -1;
@@ -99,7 +100,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint4 *w, const ui
     // per k-step: row tiles past the range repeat its last one and batch tiles past the live batch the last live one
     // (neither is stored), k-steps past the slice repeat its last one (never multiplied).  One wave per SIMD issues
     // everything, so what stands between its matrix instructions is kept short: bases in scalar registers, one offset per
-    // operand and k-step (vw, vx) that stops at the slice's last k-step, ring slots as byte offsets.
+    // operand and k-step (kw, kx) that stops at the slice's last k-step, ring slots as byte offsets.
     const char *wsrc[CW], *xsrc[CX];
 #pragma unroll
     for (int i = 0; i < CW; ++i) wsrc[i] = reinterpret_cast<const char *>(w) + (uint64_t)(uint32_t)(min(rt0 + wave * CW + i, rt1 - 1) * KS + ks0) * 1024;
@@ -139,7 +140,7 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const uint4 *w, const ui
 
     // One k-step.  The wait covers this wave's part of W(t + 1) (its requests are followed by those of DA - 2 whole
     // k-steps); after the barrier all parts are in LDS and every wave is done with the slot of W(t - 1), which takes W(t + DA).
-    // FR: rows r with r % U == u start a new chain in this k-step; their sums so far were added to `sum` since their last products.
+    // Rows r with r % U == u start a new chain in this k-step; their sums so far were added to `sum` since their last products.
     auto step = [&](auto uu) {
         constexpr int u = decltype(uu)::value;
         const u32x4_t (&xc)[CX] = x[u];

@@ -196,7 +196,8 @@ __global__ __launch_bounds__(kBlk) void argmax_kernel(const float *logits, int n
 
 struct ReportDev { int32_t live, n_fin; int64_t sum_ctx; int32_t n_free, step; };
 
-// Sixteen words of leading arguments: what the rows need is in registers when the workgroup starts (see gemm_xs_kernel).
+// Fourteen words of leading arguments: what the rows need is in registers when the workgroup starts (see gemm_xs_kernel); the
+// counters' address, which one thread needs, is fetched beside their loads.
 __global__ __launch_bounds__(kBlk) void finish_kernel(const int32_t *next_tok, int32_t *gen, int32_t *kv_len, const int32_t *target, int32_t *tok, int32_t *fin, int B, int eos,
                                                       int32_t *scalars, ReportDev *rep)
 {
