@@ -10,8 +10,8 @@
 //
 // Sums: every XD + 1 k-steps a row tile's accumulators are added to a second set and start again from zero.  One chain over all
 // of K rounds 2 K / 32 times at the size of the result; against float64 sums of the same operands that gave 5.7e-7 (2-norm,
-// K = 4096), 8.1e-7 (K = 8192); in blocks it is 1.4e-7 .. 1.9e-7 at every K up to 11008.  The second set is why a wave takes at
-// most two batch tiles.  The row tiles start their chains at different k-steps, and a tile's additions are spread between the
+// K = 4096), 8.1e-7 (K = 8192); in blocks it is 1.34e-7 .. 1.63e-7 over 102 pairs of shape and rows with K up to 11008.  The second
+// set is why a wave takes at most two batch tiles.  The row tiles start their chains at different k-steps, and a tile's additions are spread between the
 // products of the others: all tiles at once, in one k-step of the ring, they held up the matrix cores for 90 (8 x 2 tiles) to
 // 180 (12 x 2) clocks per k-step.
 //
