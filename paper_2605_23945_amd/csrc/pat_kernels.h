@@ -1,6 +1,7 @@
 // Host-side launchers of the HIP kernels (internal to libpat_decode.so).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace pat {
@@ -103,9 +104,11 @@ struct AttnArgs {
     uint4 *ohi, *olo;          // merged output as packed split-bf16 [B, hq*d]
     int n_items;               // n_chunks_total * hkv (host mirror)
     int longest_chunks;        // most chunks of one row (0: unknown), for the choice of the merge kernel
-    bool two_per_cu;           // attn_stream_kernel: two workgroups per compute unit (see pick_chunk)
     bool direct;               // every row has one chunk: its workgroups write ohi / olo, nothing is merged
+    bool two_per_cu;           // attn_stream_kernel: two workgroups per compute unit (see pick_chunk); read by the host alone
 };
+// At another byte of its word the compiler shifts `direct` out ahead of the first loads of K and V, and waits there for all arguments.
+static_assert(offsetof(AttnArgs, direct) % 4 == 0, "the decode kernels test the low byte of a word");
 constexpr float kLn2 = 0.69314718f;
 inline float attn_decode_unit(int G) { return G >= 4 ? kLn2 : 1.f; }      // ml_unit of launch_attn_partial, by query heads per KV head; launch_attn_prefill: kLn2
 hipError_t launch_attn_partial(const AttnArgs &a, hipStream_t s);
